@@ -507,7 +507,7 @@ def main() -> int:
             "kernel_ms": ms / 3, "wall_ms": tw * 1e3, "samples_per_s": 1000 / tw,
             "lost_fraction": float((drawn >= 400).double().mean())}
         # every output amplitude of 10 photons in 16 modes (3268760 outputs):
-        # the default form (the contraction at this size), then the sweep
+        # the default form (photon by photon), then the sweep
         U16 = torch.from_numpy(workloads.haar(16, 1)).to(dev)
         S16 = [1] * 10 + [0] * 6
         forms = {}
@@ -527,7 +527,7 @@ def main() -> int:
             forms[form] = (ms / 3, tw, abs(float(torch.sum(torch.abs(amp16) ** 2)) - 1.0))
         eng.all_outputs_gemm("auto")
         batched["all_outputs_10_in_16"] = {
-            "outputs": pq.fock_count(16, 10), "form": "contraction (rocBLAS zgemm per degree split)",
+            "outputs": pq.fock_count(16, 10), "form": "photon by photon",
             "kernel_ms": forms["auto"][0], "wall_ms": forms["auto"][1] * 1e3,
             "outputs_per_s": pq.fock_count(16, 10) / forms["auto"][1],
             "completeness_error": forms["auto"][2],

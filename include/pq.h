@@ -358,9 +358,7 @@ int pq_perm_grad(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  * pq_perm_all_outputs -- perm(U_{T,S}) and amp = perm / sqrt(prod S! prod T!)
  * for every output pattern T with sum T = sum S = n on m modes, in ascending
  * lexicographic order of (T_0, ..., T_{m-1}): T = (0, ..., 0, n) first,
- * (n, 0, ..., 0) last; pq_fock_count(m, n) = C(n+m-1, n) outputs.  One
- * Gray-code sum over the input side serves every T: a term's m column sums
- * c_i = sum_j delta_j U[i][j] give w prod_i c_i^{t_i} for all T at once.
+ * (n, 0, ..., 0) last; pq_fock_count(m, n) = C(n+m-1, n) outputs.
  *   U      device, m x m row-major, leading dimension ldu >= m.
  *   S      host int32[m] input occupations, sum n <= 48.
  *   perm   device, pq_fock_count(m, n) complex, written.
@@ -368,8 +366,14 @@ int pq_perm_grad(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  * Limits (PQ_ERANGE): m <= 64; at most PQ_ALL_MAX_OUTPUTS outputs; at most
  * 2^20 Gray terms (prod over occupied input modes of (s_j + 1), halved on the
  * smallest).  n == 0 writes the single vacuum output perm = amp = 1.
- * Two forms compute the same sum (pq_all_outputs_gemm picks between them):
- *   - the sweep: one thread per output T, terms staged through LDS;
+ * By default the values are built photon by photon,
+ *   perm_k(T) = sum_i t_i U[i][j_k] perm_{k-1}(T - e_i),
+ * in workspace for the two levels below the outputs (16 bytes per vector of
+ * n - 1 and of n - 2 photons in m modes), as long as that is at most 1 GiB.
+ * Two forms compute the signed sum instead (pq_all_outputs_gemm picks them):
+ *   - the sweep: a term's m column sums c_i = sum_j delta_j U[i][j] give
+ *     w prod_i c_i^{t_i} for all T at once; one thread per output T, terms
+ *     staged through LDS;
  *   - the contraction: with the output modes split into halves a and b,
  *     prod_i c_i^{t_i} = M_a(T_a) M_b(T_b) (the monomials of each half), so
  *     for each degree k = |T_a| the outputs are one complex matrix product
@@ -381,7 +385,7 @@ int pq_perm_grad(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  *     (one complex per term and composition of at most n photons in either
  *     half) take workspace of up to 1 GiB, its products as much as the
  *     outputs.
- * The two forms agree to rounding (another order of the sum over terms).
+ * All forms agree to rounding.
  */
 #define PQ_ALL_MAX_OUTPUTS (1ll << 31)
 int pq_perm_all_outputs(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m, const int32_t* S,
@@ -389,9 +393,10 @@ int pq_perm_all_outputs(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m, c
 
 /*
  * pq_all_outputs_gemm -- which form pq_perm_all_outputs takes:
- *   PQ_ALL_GEMM_AUTO (default): the contraction when its tables fit 1 GiB
- *     and outputs x terms >= 2^29 (below that its fixed cost, about 0.2 ms
- *     of launches, outweighs the sweep); the sweep otherwise;
+ *   PQ_ALL_GEMM_AUTO (default): photon by photon when the two lower levels
+ *     fit 1 GiB; otherwise the contraction when its tables fit 1 GiB and
+ *     outputs x terms >= 2^29 (below that its fixed cost, about 0.2 ms of
+ *     launches, outweighs the sweep), else the sweep;
  *   PQ_ALL_GEMM_ALWAYS: the contraction whenever its tables fit;
  *   PQ_ALL_GEMM_NEVER: the sweep.
  * PQ_ALL_GEMM=auto|always|never in the environment sets it at pq_create.

@@ -200,6 +200,73 @@ int all_cache(pq_ctx* ctx, AllCache** out) {
     return PQ_OK;
 }
 
+// The ladder form (see all.h).  done = false when its lower levels do not fit
+// kAllLadderBytes: nothing was launched then.
+int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int32_t* S, double norm_s,
+               uint64_t outputs, cplx* perm, cplx* amp, hipStream_t st, bool& done) {
+    done = false;
+    const uint64_t c1 = compositions(m, n - 1, (uint64_t)kAllMaxOutputs);
+    const uint64_t c2 = n > 1 ? compositions(m, n - 2, (uint64_t)kAllMaxOutputs) : 1;
+    if ((c1 + c2) * sizeof(cplx) > kAllLadderBytes) return PQ_OK;
+    done = true;
+    Carve cv;
+    const size_t oBuf[2] = {cv.take(sizeof(cplx) * (size_t)c1), cv.take(sizeof(cplx) * (size_t)c2)};
+    char* ws = (char*)ctx->workspace(cv.off);
+    if (!ws) return PQ_ENOMEM;
+    AllLevelArgs la;
+    memset(&la, 0, sizeof(la));
+    AllLadderArgs& a = la.a;
+    a.U = U;
+    a.ldu = ldu;
+    a.m = m;
+    a.n = n;
+    int k = 0;
+    for (int j = 0; j < m; ++j)
+        for (int c = 0; c < S[j]; ++c) a.col[k++] = (uint8_t)j;
+    a.norm_s = norm_s;
+    a.perm = perm;
+    a.amp = amp;
+    // level n - 1 goes to the first buffer, n - 2 to the second, and so on
+    auto level_buf = [&](int lv) { return (cplx*)(ws + oBuf[(n - 1 - lv) & 1]); };
+    // the small kernel starts at level 3 at the latest (levels 1 to 3 need no
+    // level below); every level but its last stays in LDS
+    auto small = [&](int lv, int limit) {
+        return m * lv <= kAllLadderCols && compositions(m, lv, (uint64_t)kAllMaxOutputs) <= (uint64_t)limit;
+    };
+    a.k0 = 1;
+    while (a.k0 < n && small(a.k0 + 1, kAllLadderFirst) && (a.k0 < 3 || small(a.k0, kAllLadderSmall))) ++a.k0;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    int rc;
+    if (ctx->profiling) {
+        e0 = ctx->take_event();
+        e1 = ctx->take_event();
+        if (!e0 || !e1) return ctx->fail(PQ_EDEVICE, "profile: hipEventCreate failed");
+        rc = ctx->check(hipEventRecord(e0, st), "profile: record");
+        if (rc) return rc;
+    }
+    rc = ctx->check(launch_all_ladder_small(a, a.k0 < n ? level_buf(a.k0) : nullptr, st), "all-outputs ladder");
+    if (rc) return rc;
+    for (int lv = a.k0 + 1; lv <= n; ++lv) {
+        const uint64_t count = lv == n ? outputs : compositions(m, lv, (uint64_t)kAllMaxOutputs);
+        la.k = lv;
+        la.count = (uint32_t)count;
+        // up to 16 workgroups per CU, each a run of consecutive outputs
+        const uint64_t most = (uint64_t)ctx->num_cu * 16;
+        const uint64_t per = (count + most - 1) / most;
+        la.run = (uint32_t)((per + kBlock - 1) / kBlock * kBlock);
+        la.in = level_buf(lv - 1);
+        la.out = lv < n ? level_buf(lv) : nullptr;
+        rc = ctx->check(launch_all_ladder_level(la, st), "all-outputs ladder");
+        if (rc) return rc;
+    }
+    if (ctx->profiling) {
+        rc = ctx->check(hipEventRecord(e1, st), "profile: record");
+        if (rc) return rc;
+        ctx->ev_used.emplace_back(e0, e1);
+    }
+    return PQ_OK;
+}
+
 }  // namespace
 }  // namespace pq
 
@@ -300,6 +367,12 @@ int pq_perm_all_outputs(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m, c
             return ctx->fail(PQ_ERANGE, "pq_perm_all_outputs: more than %llu Gray terms", (unsigned long long)kAllMaxTerms);
     }
     sa.terms = terms;
+    const double norm_s = exp(-0.5 * lfs);
+    if (ctx->all_gemm == PQ_ALL_GEMM_AUTO) {
+        bool done = false;
+        const int rc_ = run_ladder(ctx, (const cplx*)U, ldu, m, n, S, norm_s, outputs, (cplx*)perm, (cplx*)amp, st, done);
+        if (rc_ || done) return rc_;
+    }
     // composition counts: [mm][nn] = compositions of nn into mm + 1 parts
     const int rows = m > 1 ? m - 1 : 1;
     std::vector<uint64_t> cnt((size_t)rows * (size_t)(n + 1), 0);
@@ -372,7 +445,6 @@ int pq_perm_all_outputs(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m, c
         rc = ctx->check(hipEventRecord(e0, st), "profile: record");
         if (rc) return rc;
     }
-    const double norm_s = exp(-0.5 * lfs);
     if (gemm) {
         AllTableArgs ta;
         ta.csum_t = sa.csum_t;

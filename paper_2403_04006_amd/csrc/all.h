@@ -54,7 +54,59 @@ struct AllOutArgs {
     cplx* amp;               // may be null
 };
 
-// The contraction form (taken when its tables fit kAllGemmTableBytes):
+// The ladder form: photon by photon instead of a signed sum.  With the input
+// photons in modes j_1, ..., j_n, expanding along the last column gives
+//   perm_k(T) = sum_{i: t_i > 0} t_i U[i][j_k] perm_{k-1}(T - e_i),
+// so every level's values are short sums over the level below: at most
+// min(k, m) complex multiply-adds per output (6 on average at 10 photons in 16
+// modes) where the signed sum takes one per Gray term (512), and no term
+// larger than the result's own scale.  An output is its photons' modes in
+// ascending order, q the mode counted from the last: with G(r, q) =
+// C(r + q - 1, r) (the ways to put r photons into the last q modes), photons
+// p = 0..k-1 and r_p = k - p,
+//   rank(T) = sum_p G(r_p, q_p),
+//   rank(T without photon p) = sum_{p' < p} G(r_p' - 1, q_p') + sum_{p' > p} G(r_p', q_p'),
+// so ranks need no per-output tables, and since every output is at photon p
+// in the same step, the searches for q_p and the loads run without branches.
+// One workgroup runs the levels of a few thousand values in LDS, one launch
+// each of the others; two levels below the outputs live in workspace.
+// Whole calls (sweep or contraction -> ladder): 23 -> 16 us at 5 photons in 12
+// modes, 47 -> 31 us at 8 in 12, 97 -> 44 us at 8 in 16, 1268 -> 111 us at 11 in
+// 14 and 850 -> 112 us at 10 in 16; no measured size was faster in another form,
+// so by default it is taken whenever its two lower levels fit kAllLadderBytes.
+constexpr uint64_t kAllLadderBytes = 1ull << 30;   // workspace of the two lower levels
+constexpr int kAllLadderSmall = 2048;              // values of a level kept in LDS
+constexpr int kAllLadderFirst = 4096;              // values of the last level that the small kernel takes
+constexpr int kAllLadderCols = 512;                // modes x levels of the small kernel
+constexpr int kAllLadderBlock = 1024;              // threads of the small levels' workgroup
+
+struct AllLadderArgs {
+    const cplx* U;
+    int64_t ldu;
+    int32_t m, n;
+    int32_t k0;                        // levels 1..k0 of the first kernel
+    uint8_t col[kAllMaxPhotons];       // input mode of photon k + 1
+    double norm_s;                     // 1 / sqrt(prod S!)
+    cplx* perm;
+    cplx* amp;                         // may be null
+};
+
+// Level k from level k - 1 (in); out: the level's values, or the outputs when
+// k == n (perm and amp of AllLadderArgs).
+struct AllLevelArgs {
+    AllLadderArgs a;
+    int32_t k;
+    uint32_t count;                    // outputs of level k
+    uint32_t run;                      // consecutive outputs per workgroup, a multiple of kBlock
+    const cplx* in;
+    cplx* out;
+};
+
+hipError_t launch_all_ladder_small(const AllLadderArgs& a, cplx* out, hipStream_t s);
+hipError_t launch_all_ladder_level(const AllLevelArgs& a, hipStream_t s);
+
+// The contraction form (on request, or where the ladder's levels do not fit;
+// its tables have to fit kAllGemmTableBytes):
 // split the output modes into a = 0..ma-1 and b = ma..m-1, T = (T_a, T_b).
 // Then prod_i c_i^{t_i} = M_a(delta, T_a) M_b(delta, T_b) with M the
 // monomials of each half, and for |T_a| = k
@@ -66,7 +118,7 @@ struct AllOutArgs {
 // in a block-ordered buffer and a scatter puts each row of T_b's at its
 // T_a's place in the output order.
 constexpr uint64_t kAllGemmTableBytes = 1ull << 30;
-// by default the contraction from this many (term, output) pairs on: below
+// without the ladder, the contraction from this many (term, output) pairs on: below
 // it the sweep is faster (the contraction's launches and stream joins cost
 // about 0.2 ms; 8 photons in 16 modes, 6.3e7 pairs: sweep 0.10 ms,
 // contraction 0.22 ms; 10 photons in 16 modes, 1.7e9 pairs: 1.9 ms and
