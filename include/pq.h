@@ -514,10 +514,15 @@ int pq_lhaf_pack(pq_ctx* ctx, int mode);
 /*
  * pq_lhaf_many -- pq_lhaf for npat repetition vectors on one matrix (the
  * probabilities of many output patterns of one Gaussian state), in one
- * submission: every pattern is planned on the host, its Gray range is cut
- * into chunks (four per workgroup, all of one pattern), one launch per
- * kernel variant sweeps them, and each pattern's chunk sums are added in
- * chunk order (results do not depend on timing).
+ * submission.  Where the vectors of at most max N photons in the occupied
+ * modes (at most 32) are cheaper to tabulate than the patterns are to sweep,
+ * their values are built level by level in workspace (at most 1 GiB),
+ *   h(r) = gamma_i h(r - e_i) + sum_k (r - e_i)_k A_ik h(r - e_i - e_k),
+ * and each pattern's value is read from the table.  Otherwise every pattern
+ * is planned on the host, its Gray range is cut into chunks (four per
+ * workgroup, all of one pattern), one launch per kernel variant sweeps them,
+ * and each pattern's chunk sums are added in chunk order (results do not
+ * depend on timing).
  *   reps   host int32[npat * d], pattern q at offset q * d.
  *   out    device, npat complex, written (out[q] for pattern q).
  * Limits and errors as for pq_lhaf, per pattern; npat == 0 does nothing.

@@ -242,6 +242,122 @@ int describe(pq_ctx* ctx, const int32_t* reps, int d, int N, bool loops, HafDesc
     return PQ_OK;
 }
 
+// The table form (see haf.h): plan for a list of patterns, or false where it
+// does not apply (an invalid pattern, left to the sweeps' checks, included).
+// Taken when it is the cheaper one, in ns: about 5000 per launch and 2 per 1000
+// photon steps, against the sweeps' 25000, 120 per pattern (the host plans
+// each) and 2 (loops: 6) per 1000 Gray terms.  Both sides measured (sweeps ->
+// table, us a call): 10 patterns of 2 photons 28 -> 16; 1820 of 12 in 5 modes
+// 248 -> 33; 6435 of 8 in 8 with loops 872 -> 60; 20349 of 16 in 6 2830 -> 125
+// (3070 -> 132 with loops), there 50 us of kernels and 75 us of packing the
+// patterns on the host.
+bool plan_ladder(const int32_t* reps, int d, int npat, bool loops, HafLadderArgs& a) {
+    memset(&a, 0, sizeof(a));
+    std::vector<int32_t> top((size_t)d, 0);
+    int32_t* __restrict tp = top.data();
+    int N = 0;
+    bool any = false;
+    for (int q = 0; q < npat; ++q) {
+        const int32_t* __restrict r = reps + (size_t)q * d;
+        uint32_t all = 0;
+        int n = 0;
+        for (int i = 0; i < d; ++i) {
+            all |= (uint32_t)r[i];
+            n += r[i] & 127;
+            tp[i] = std::max(tp[i], r[i]);
+        }
+        // entries above 127 (negative ones included) leave a bit in `all`;
+        // sums of smaller ones are exact
+        if (all > 127u || n > kHafMaxN) return false;
+        if (n == 0 || (!loops && (n & 1))) continue;
+        any = true;
+        N = std::max(N, n);
+    }
+    if (!any) return false;
+    for (int i = 0; i < d; ++i) {
+        if (top[(size_t)i] == 0) continue;
+        if (a.d == kHafLadderModes || i > 255) return false;
+        a.mode[a.d++] = (uint8_t)i;
+    }
+    a.N = N;
+    a.npat = npat;
+    // vectors per level: C(s + d - 1, s); odd levels are empty without loops
+    double steps = 0.0;
+    uint64_t off = 0, count = 1;
+    int launches = 1;
+    for (int s = 0; s <= N; ++s) {
+        if (s > 0) count = (uint64_t)((unsigned __int128)count * (unsigned)(s + a.d - 1) / (unsigned)s);
+        const uint64_t here = loops || !(s & 1) ? count : 0;
+        if (off + here > kHafLadderBytes / sizeof(cplx)) return false;
+        a.off[s] = (uint32_t)off;
+        off += here;
+        a.off[s + 1] = (uint32_t)off;
+        steps += (double)here * s;
+        if (here <= (uint64_t)kHafLadderSmall && a.s0 + 1 >= s) a.s0 = s;
+        else if (here) ++launches;
+    }
+    if (a.s0 < N) ++launches;
+    const double ladder_ns = 5000.0 * launches + 0.002 * steps;
+    double sweep_ns = 25000.0 + 120.0 * npat;
+    for (int q = 0; q < npat && ladder_ns >= sweep_ns; ++q) {
+        double terms = 0.5;
+        for (int i = 0; i < d; ++i) terms *= (double)(reps[(size_t)q * d + i] + 1);
+        sweep_ns += (loops ? 0.006 : 0.002) * terms;
+    }
+    return ladder_ns < sweep_ns;
+}
+
+int run_haf_ladder(pq_ctx* ctx, HafLadderArgs& a, const cplx* A, int64_t lda, int d, const cplx* gamma,
+                   const int32_t* reps, cplx* out, hipStream_t st) {
+    Carve cv;
+    const size_t oR = cv.take((size_t)a.npat * (size_t)a.d);
+    const size_t upload = cv.off;
+    const size_t oH = cv.take(sizeof(cplx) * (size_t)a.off[a.N + 1]);
+    char* ws = (char*)ctx->workspace(cv.off);
+    if (!ws) return PQ_ENOMEM;
+    uint8_t* stage = (uint8_t*)ctx->staging(upload);
+    if (!stage) return PQ_ENOMEM;
+    uint8_t* __restrict w = stage + oR;
+    const int32_t* __restrict src = reps;
+    const size_t all = (size_t)a.npat * (size_t)d;
+    if (a.d == d) {
+        for (size_t e = 0; e < all; ++e) w[e] = (uint8_t)src[e];
+    } else {
+        int mode[kHafLadderModes];
+        for (int i = 0; i < a.d; ++i) mode[i] = a.mode[i];
+        const int k = a.d;
+        for (size_t q = 0; q < all; q += (size_t)d, w += k)
+            for (int i = 0; i < k; ++i) w[i] = (uint8_t)src[q + (size_t)mode[i]];
+    }
+    int rc = ctx->upload(ws, stage, upload, st);
+    if (rc) return rc;
+    a.A = A;
+    a.lda = lda;
+    a.gamma = gamma;
+    a.reps = (const uint8_t*)(ws + oR);
+    a.h = (cplx*)(ws + oH);
+    a.out = out;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (ctx->profiling) {
+        e0 = ctx->take_event();
+        e1 = ctx->take_event();
+        if (!e0 || !e1) return ctx->fail(PQ_EDEVICE, "profile: hipEventCreate failed");
+        rc = ctx->check(hipEventRecord(e0, st), "profile: record");
+        if (rc) return rc;
+    }
+    rc = ctx->check(launch_haf_ladder_small(a, st), "hafnian table");
+    for (int s = a.s0 + 1; s <= a.N && !rc; ++s)
+        if (a.off[s + 1] > a.off[s]) rc = ctx->check(launch_haf_ladder_level(a, s, st), "hafnian table");
+    if (!rc && a.s0 < a.N) rc = ctx->check(launch_haf_ladder_gather(a, st), "hafnian table");
+    if (rc) return rc;
+    if (ctx->profiling) {
+        rc = ctx->check(hipEventRecord(e1, st), "profile: record");
+        if (rc) return rc;
+        ctx->ev_used.emplace_back(e0, e1);
+    }
+    return PQ_OK;
+}
+
 }  // namespace
 
 int pq_lhaf(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq_c128* gamma, const int32_t* reps,
@@ -363,6 +479,14 @@ int pq_lhaf_many(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq
     if (npat == 0) return PQ_OK;
     if (!out || (d > 0 && !reps)) return ctx->fail(PQ_EINVAL, "pq_lhaf_many: NULL reps or out");
     const bool loops = gamma != nullptr;
+    {
+        HafLadderArgs la;
+        if (A && lda >= d && plan_ladder(reps, d, npat, loops, la)) {
+            DeviceGuard guard(ctx->device);
+            return run_haf_ladder(ctx, la, (const cplx*)A, lda, d, (const cplx*)gamma, reps, (cplx*)out,
+                                  (hipStream_t)stream);
+        }
+    }
     std::vector<HafDesc> descs((size_t)npat);
     HafPlan p;   // each pattern's plan, kept only while its descriptor is filled in
     std::vector<int32_t> modes;

@@ -214,4 +214,37 @@ hipError_t launch_haf_many_prep(const HafManyPrepArgs& a, int npat, hipStream_t 
 hipError_t launch_haf_many(bool loops, int nl, int rr, const HafManyArgs& a, int blocks, hipStream_t s);
 hipError_t launch_haf_many_final(const HafManyFinalArgs& a, hipStream_t s);
 
+// Tables of many patterns on few modes (pq_lhaf_many): instead of a signed sum
+// per pattern, the values of all vectors r of at most N photons in the
+// occupied modes, level by level (s = sum r).  Matching the first photon (mode
+// i) with itself or another one,
+//   h(r) = gamma_i h(r - e_i) + sum over its other photons p
+//                               A[i][mode p] h(r - e_i - e_mode(p)),
+// N complex multiply-adds per vector, and no cancellation between terms larger
+// than the sum's own.  Without loops only the even levels exist.  Every
+// pattern's value is then read at its rank (ladder.h).
+constexpr int kHafLadderModes = 32;
+constexpr int kHafLadderSmall = 2048;        // vectors of a level that the small kernel takes
+constexpr int kHafLadderBlock = 1024;        // threads of the small levels' workgroup
+constexpr uint64_t kHafLadderBytes = 1ull << 30;   // all levels' values
+
+struct HafLadderArgs {
+    const cplx* A;
+    int64_t lda;
+    const cplx* gamma;                // may be null
+    int32_t d;                        // occupied modes
+    int32_t N;                        // largest level
+    int32_t s0;                       // last level of the small kernel
+    int32_t npat;
+    uint8_t mode[kHafLadderModes];    // occupied modes, ascending
+    uint32_t off[kHafMaxN + 2];       // first value of level s
+    const uint8_t* reps;              // [npat][d]
+    cplx* h;                          // the levels' values
+    cplx* out;                        // [npat]
+};
+
+hipError_t launch_haf_ladder_small(const HafLadderArgs& a, hipStream_t s);
+hipError_t launch_haf_ladder_level(const HafLadderArgs& a, int level, hipStream_t s);
+hipError_t launch_haf_ladder_gather(const HafLadderArgs& a, hipStream_t s);
+
 }  // namespace pq
