@@ -9,9 +9,8 @@
 #include "plan.h"
 #include "runtime.h"
 
-// Validate the jobs and build the cache key.  Returns PQ_OK or an error.
-int pq_validate_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs,
-                     std::vector<int64_t>& key) {
+// Returns PQ_OK or an error.
+int pq_validate_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs) {
     using namespace pq;
     std::vector<std::pair<int64_t, int64_t>> ranges;
     ranges.reserve(njobs);
@@ -47,14 +46,8 @@ int pq_validate_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs,
             if (!(J.op == PQ_OP_PERM && sr != sc))
                 return ctx->fail(PQ_ERANGE, "job %d: more than %d photons", k, PQ_MAX_N);
         ranges.emplace_back(J.out_offset, J.op == PQ_OP_EXTEND_ROW ? (int64_t)m : 1);
-        key.push_back(J.op);
-        key.push_back(J.nr);
-        key.push_back(J.nc);
-        key.push_back(J.out_offset);
-        for (int i = 0; i < J.nr; ++i) key.push_back(((int64_t)J.row_idx[i] << 32) | (uint32_t)J.row_mult[i]);
-        for (int i = 0; i < J.nc; ++i) key.push_back(((int64_t)J.col_idx[i] << 32) | (uint32_t)J.col_mult[i]);
     }
-    std::sort(ranges.begin(), ranges.end());
+    if (!std::is_sorted(ranges.begin(), ranges.end())) std::sort(ranges.begin(), ranges.end());
     for (size_t i = 1; i < ranges.size(); ++i)
         if (ranges[i].first < ranges[i - 1].first + ranges[i - 1].second)
             return ctx->fail(PQ_EINVAL, "output ranges of two jobs overlap");

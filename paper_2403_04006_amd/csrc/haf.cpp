@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <vector>
 
@@ -150,7 +151,7 @@ void haf_tables(const HafPlan& p, std::vector<HafStep>& tab) {
 //   quad: e1, e2, e3, e4 of prod (x + b y) = x^4 + e1 x^3 y + ... + e4 y^4
 //   pair: e1, e2;  single: b.
 // That is floor(N/2) values in all.
-void hermite_factors(int N, double* out) {
+void find_hermite_factors(int N, double* out) {
     // number of eigenvalues below x: negative pivots of T - x I
     auto below = [N](long double x) {
         int cnt = 0;
@@ -171,6 +172,7 @@ void hermite_factors(int N, double* out) {
         long double lo = 0.0L, hi = bound;
         for (int it = 0; it < 200; ++it) {
             const long double mid = 0.5L * (lo + hi);
+            if (mid == lo || mid == hi) break;   // no number lies between: further halvings change nothing
             if (below(mid) >= want) hi = mid;
             else lo = mid;
         }
@@ -190,6 +192,15 @@ void hermite_factors(int N, double* out) {
         k += 2;
     }
     if (k < J) out[k] = (double)b[k];
+}
+
+// The factors of N, found once per process (they depend on N alone; the roots
+// take 0.1 to 1 ms of a call, as much as the sweep at 16 modes).
+const double* hermite_factors(int N) {
+    static double table[kHafMaxN + 1][kHafFactors];
+    static std::once_flag once[kHafMaxN + 1];
+    std::call_once(once[N], [N] { find_hermite_factors(N, table[N]); });
+    return table[N];
 }
 
 // Validate one repetition vector: N in *N, PQ_OK or an error status.
@@ -440,7 +451,7 @@ int pq_lhaf(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq_c128
     a.tab = (const HafStep*)(ws + oT);
     a.partials = (double*)(ws + oP);
     a.waves = (uint32_t)waves;
-    if (loops) hermite_factors(N, a.hb);
+    if (loops) memcpy(a.hb, hermite_factors(N), sizeof(a.hb));
     a.work = work;
     a.pk = pk;
     a.d = D;
@@ -522,7 +533,7 @@ int pq_lhaf_many(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq
             if (ih == hb_of.end()) {
                 ih = hb_of.emplace(N, (int64_t)hbs.size()).first;
                 hbs.resize(hbs.size() + kHafFactors, 0.0);
-                hermite_factors(N, hbs.data() + ih->second);
+                memcpy(hbs.data() + ih->second, hermite_factors(N), sizeof(double) * kHafFactors);
             }
             D.hb_off = ih->second;
         }

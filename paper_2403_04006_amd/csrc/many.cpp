@@ -40,7 +40,12 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
                   kTuneCandidates[0].chunks_per_wave == ChunkPolicy().chunks_per_wave &&
                   kTuneCandidates[0].min_chunk == ChunkPolicy().min_chunk,
               "the first candidate is the default policy");
-constexpr int kMaxManyEntries = 4;
+// Cached plans: four whatever their size, more while their device blocks
+// stay within kMaxManyBytes together, kMaxManyEntries at most (a training loop
+// holds a forward and a reverse plan for each of its pattern sets).
+constexpr int kMinManyEntries = 4;
+constexpr int kMaxManyEntries = 16;
+constexpr size_t kMaxManyBytes = (size_t)1 << 30;
 struct ManyClass;
 int walk_occupancy(pq_ctx* ctx, const ManyClass& C);
 
@@ -52,8 +57,18 @@ struct ManyClass {
     int64_t slot_off = 0;    // doubles
 };
 
+// What a plan was built for, compared in full on every call.
+struct ManyKey {
+    int mode = -1;               // kModeFwd: a job list; kModeAdj: dense patterns
+    int32_t m = 0, count = 0, walk_variant = 0;
+    // job list: per job op, nr, nc, the output offset's two halves, then the
+    // four lists; dense patterns: S, then T
+    std::vector<int32_t> flat;
+};
+
 struct ManyEntry {
-    std::vector<int64_t> key;
+    ManyKey key;
+    size_t bytes = 0;            // device block
     int mode = 0;                // kModeFwd (forward and extend jobs) or kModeAdj
     int npat = 0, ntab = 0;      // npat: distinct patterns (identical ones are swept once)
     bool fuse_dred = false;      // adjoint: the final kernel reduces the derivative slots
@@ -124,26 +139,49 @@ struct ManyCache {
     }
 };
 
-struct PatternSpec {
+// One job, its lists in the caller's memory (or in a gradient call's).
+struct PatRef {
     int op;            // kOpPerm / kOpExtend
-    Side rows, cols;
+    int32_t nr, nc;
+    const int32_t *row_idx, *row_mult, *col_idx, *col_mult;
     int64_t out;
 };
 
-// Identity of a pattern for deduplication: op, then both sides (modes and
-// multiplicities in the caller's order).
-std::vector<int32_t> pattern_key(const PatternSpec& ps) {
-    std::vector<int32_t> k;
-    k.reserve(3 + 2 * (size_t)(ps.rows.count + ps.cols.count));
-    k.push_back(ps.op);
-    k.push_back(ps.rows.count);
-    for (int i = 0; i < ps.rows.count; ++i) { k.push_back(ps.rows.mode[i]); k.push_back(ps.rows.mult[i]); }
-    k.push_back(ps.cols.count);
-    for (int i = 0; i < ps.cols.count; ++i) { k.push_back(ps.cols.mode[i]); k.push_back(ps.cols.mult[i]); }
-    return k;
+void to_side(int32_t n, const int32_t* idx, const int32_t* mult, Side& s) {
+    s.count = n;
+    for (int i = 0; i < n; ++i) {
+        s.mode[i] = idx[i];
+        s.mult[i] = mult[i];
+    }
 }
 
-int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatternSpec>& all, ManyEntry& E,
+bool same_list(const int32_t* a, const int32_t* b, int32_t n) {
+    int32_t diff = 0;
+    for (int i = 0; i < n; ++i) diff |= a[i] ^ b[i];
+    return diff == 0;
+}
+
+// Identity of a pattern for deduplication: op, then both sides (modes and
+// multiplicities in the caller's order).
+bool same_pattern(const PatRef& a, const PatRef& b) {
+    return a.op == b.op && a.nr == b.nr && a.nc == b.nc && same_list(a.row_idx, b.row_idx, a.nr) &&
+           same_list(a.row_mult, b.row_mult, a.nr) && same_list(a.col_idx, b.col_idx, a.nc) &&
+           same_list(a.col_mult, b.col_mult, a.nc);
+}
+
+uint64_t hash_pattern(const PatRef& p) {
+    uint64_t h = 1469598103934665603ull ^ (uint64_t)(p.op + 4 * p.nr + 256 * p.nc);
+    auto mix = [&h](const int32_t* v, int32_t n) {
+        for (int i = 0; i < n; ++i) h = (h ^ (uint32_t)v[i]) * 1099511628211ull;
+    };
+    mix(p.row_idx, p.nr);
+    mix(p.row_mult, p.nr);
+    mix(p.col_idx, p.nc);
+    mix(p.col_mult, p.nc);
+    return h ^ (h >> 32);
+}
+
+int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all, ManyEntry& E,
                hipStream_t st, const ChunkPolicy& pol) {
     E.mode = mode;
     E.policy = pol;
@@ -151,16 +189,22 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatternSpec>&
     // identical patterns (a sampling loss draws outputs with replacement) are
     // planned and swept once; the final kernel writes every copy's output and,
     // in the adjoint, sums the copies' cotangents
-    std::vector<PatternSpec> pats;
+    std::vector<PatRef> pats;
     std::vector<int32_t> dup_off, dup_pat;
     std::vector<int64_t> dup_out;
     {
-        std::map<std::vector<int32_t>, int32_t> seen;
-        std::vector<int32_t> dist(all.size());
+        // open addressing over at most half-full slots: distinct index or -1
+        size_t slots = 16;
+        while (slots < 2 * all.size()) slots *= 2;
+        std::vector<int32_t> seen(slots, -1), dist(all.size());
         for (size_t k = 0; k < all.size(); ++k) {
-            auto it = seen.emplace(pattern_key(all[k]), (int32_t)pats.size()).first;
-            if (it->second == (int32_t)pats.size()) pats.push_back(all[k]);
-            dist[k] = it->second;
+            size_t at = (size_t)hash_pattern(all[k]) & (slots - 1);
+            while (seen[at] >= 0 && !same_pattern(pats[(size_t)seen[at]], all[k])) at = (at + 1) & (slots - 1);
+            if (seen[at] < 0) {
+                seen[at] = (int32_t)pats.size();
+                pats.push_back(all[k]);
+            }
+            dist[k] = seen[at];
         }
         dup_off.assign(pats.size() + 1, 0);
         for (int32_t d : dist) dup_off[(size_t)d + 1] += 1;
@@ -182,11 +226,14 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatternSpec>&
     std::map<std::vector<int32_t>, int> sigs;
     std::map<std::tuple<int, int, int>, std::vector<int>> by_class;
     size_t mat_elems = 0, dpat_elems = 0;
+    Side rows, cols;
     for (size_t k = 0; k < pats.size(); ++k) {
-        const PatternSpec& ps = pats[k];
+        const PatRef& ps = pats[k];
         const bool ext = ps.op == kOpExtend;
+        to_side(ps.nr, ps.row_idx, ps.row_mult, rows);
+        to_side(ps.nc, ps.col_idx, ps.col_mult, cols);
         Plan p;
-        plan_sparse(ps.rows, ps.cols, !ext, p, ext);
+        plan_sparse(rows, cols, !ext, p, ext);
         if (p.status) return ctx->fail(p.status, "pattern %zu: planning failed", k);
         BJob& b = hj[k];
         memset(&b, 0, sizeof(b));
@@ -202,7 +249,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatternSpec>&
         bool walk = false;
         if (adj && p.binary && ncmax >= kWalkMinCols && ncmax <= kWalkMaxCols) {
             Plan pw;
-            plan_sparse(ps.rows, ps.cols, !ext, pw, ext, kWalkLaneStates);
+            plan_sparse(rows, cols, !ext, pw, ext, kWalkLaneStates);
             // the walk kernel needs four lane digits (16 terms per
             // wavefront) and at least three time digits (whole 8-state blocks)
             if (!pw.status && !pw.trivial && pw.n_lane == 4 && pw.lane_states == kWalkTerms && pw.n_time >= 3 &&
@@ -458,6 +505,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatternSpec>&
     const size_t oGs = cv.take(sizeof(cplx) * sz(adj ? pats.size() : 0));
     const size_t oQz = cv.take(sizeof(unsigned) * sz(adj ? 0 : E.classes.size()));
     if (int rc = ctx->device_alloc((void**)&E.dmem, cv.off, "many")) return rc;
+    E.bytes = cv.off;
     E.d_jobs = (BJob*)(E.dmem + oJobs);
     E.d_chunks = (MChunk*)(E.dmem + oCh);
     E.d_idx = (int32_t*)(E.dmem + oIdx);
@@ -730,12 +778,15 @@ int run_many_graph(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_
 // the number of patterns and of Gray terms in half-octave buckets, and m.
 // Job lists with the same work per class (say, other sampling runs of the
 // same size, whose output collisions differ) share a tuned policy.
-uint64_t shape_sig(int32_t m, const std::vector<PatternSpec>& pats) {
+uint64_t shape_sig(int32_t m, const std::vector<PatRef>& pats) {
     std::map<std::pair<int, int>, std::pair<double, double>> cls;   // (op, ncmax) -> (patterns, terms)
-    for (const PatternSpec& ps : pats) {
+    Side rows, cols;
+    for (const PatRef& ps : pats) {
         const bool ext = ps.op == kOpExtend;
+        to_side(ps.nr, ps.row_idx, ps.row_mult, rows);
+        to_side(ps.nc, ps.col_idx, ps.col_mult, cols);
         Plan p;
-        plan_sparse(ps.rows, ps.cols, !ext, p, ext);
+        plan_sparse(rows, cols, !ext, p, ext);
         if (p.status || p.trivial) continue;
         auto& c = cls[std::make_pair(ps.op, ((p.nc + 3) / 4) * 4)];
         c.first += 1.0;
@@ -782,7 +833,7 @@ int time_plan(pq_ctx* ctx, ManyEntry& e, int32_t m, const cplx* U, int64_t ldu, 
 }
 
 // Build one candidate plan and time it.
-int time_candidate(pq_ctx* ctx, int32_t m, const std::vector<PatternSpec>& pats, const ChunkPolicy& pol,
+int time_candidate(pq_ctx* ctx, int32_t m, const std::vector<PatRef>& pats, const ChunkPolicy& pol,
                    const cplx* U, int64_t ldu, cplx* perm, cplx* amp, hipStream_t st,
                    std::unique_ptr<ManyEntry>& out, double& ms, bool queue) {
     std::unique_ptr<ManyEntry> e(new ManyEntry());
@@ -794,27 +845,68 @@ int time_candidate(pq_ctx* ctx, int32_t m, const std::vector<PatternSpec>& pats,
     return PQ_OK;
 }
 
-// Find or build the entry for `key`.  With autotuning on (forward plans
-// only), a job-list shape seen for the first time is planned and timed
-// under every candidate chunk policy and the fastest plan is kept; later
-// job lists of that shape are planned with the recorded policy.
-int get_entry(pq_ctx* ctx, int mode, int32_t m, std::vector<int64_t>& key,
-              const std::vector<PatternSpec>& pats, hipStream_t st, ManyEntry** out,
-              const cplx* U = nullptr, int64_t ldu = 0, cplx* perm = nullptr, cplx* amp = nullptr,
+// The cached plan of exactly this job list, or null.  Every field is compared
+// on every call; a list equal to a cached one has passed its checks.
+ManyEntry* find_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs) {
+    ManyCache* cache = many_cache(ctx);
+    for (auto& e : cache->entries) {
+        const ManyKey& K = e->key;
+        if (K.mode != kModeFwd || K.m != m || K.count != njobs) continue;
+        const int32_t* f = K.flat.data();
+        bool same = true;
+        for (int k = 0; k < njobs && same; ++k) {
+            const pq_job& J = jobs[k];
+            const int32_t nr = f[1], nc = f[2];
+            same = J.op == f[0] && J.nr == nr && J.nc == nc && (int32_t)(uint32_t)J.out_offset == f[3] &&
+                   (int32_t)(J.out_offset >> 32) == f[4] && (nr == 0 || (J.row_idx && J.row_mult)) &&
+                   (nc == 0 || (J.col_idx && J.col_mult));
+            if (!same) break;
+            f += 5;
+            same = same_list(J.row_idx, f, nr) && same_list(J.row_mult, f + nr, nr) &&
+                   same_list(J.col_idx, f + 2 * nr, nc) && same_list(J.col_mult, f + 2 * nr + nc, nc);
+            f += 2 * (nr + nc);
+        }
+        if (same) {
+            e->last_use = ++cache->clock;
+            return e.get();
+        }
+    }
+    return nullptr;
+}
+
+// The same for the dense patterns of a gradient call.
+ManyEntry* find_dense(pq_ctx* ctx, int32_t m, int32_t batch, const int32_t* S, const int32_t* T) {
+    ManyCache* cache = many_cache(ctx);
+    const size_t n = (size_t)batch * (size_t)m;
+    for (auto& e : cache->entries) {
+        const ManyKey& K = e->key;
+        if (K.mode != kModeAdj || K.m != m || K.count != batch || K.walk_variant != ctx->walk_variant) continue;
+        if (n && (memcmp(K.flat.data(), S, sizeof(int32_t) * n) || memcmp(K.flat.data() + n, T, sizeof(int32_t) * n)))
+            continue;
+        e->last_use = ++cache->clock;
+        return e.get();
+    }
+    return nullptr;
+}
+
+// Build the entry for `key`.  With autotuning on (forward plans only), a
+// job-list shape seen for the first time is planned and timed under every
+// candidate chunk policy and the fastest plan is kept; later job lists of that
+// shape are planned with the recorded policy.
+int new_entry(pq_ctx* ctx, int mode, int32_t m, ManyKey& key, const std::vector<PatRef>& pats, hipStream_t st,
+              ManyEntry** out, const cplx* U = nullptr, int64_t ldu = 0, cplx* perm = nullptr, cplx* amp = nullptr,
               bool queue = false) {
     ManyCache* cache = many_cache(ctx);
-    for (auto& e : cache->entries)
-        if (e->key == key) {
-            e->last_use = ++cache->clock;
-            *out = e.get();
-            return PQ_OK;
-        }
-    if ((int)cache->entries.size() >= kMaxManyEntries) {
+    size_t held = 0;
+    for (auto& e : cache->entries) held += e->bytes;
+    while ((int)cache->entries.size() >= kMaxManyEntries ||
+           ((int)cache->entries.size() >= kMinManyEntries && held > kMaxManyBytes)) {
         auto it = std::min_element(cache->entries.begin(), cache->entries.end(),
                                    [](const std::unique_ptr<ManyEntry>& a, const std::unique_ptr<ManyEntry>& b) {
                                        return a->last_use < b->last_use;
                                    });
         hipStreamSynchronize(st);
+        held -= (*it)->bytes;
         cache->entries.erase(it);
     }
     std::unique_ptr<ManyEntry> ne;
@@ -877,20 +969,6 @@ int get_entry(pq_ctx* ctx, int mode, int32_t m, std::vector<int64_t>& key,
     return PQ_OK;
 }
 
-int side_from_dense(int m, const int32_t* v, Side& s) {
-    s.count = 0;
-    for (int i = 0; i < m; ++i) {
-        if (v[i] < 0) return PQ_EINVAL;
-        if (v[i] > 0) {
-            if (s.count >= kMaxDim) return PQ_ERANGE;
-            s.mode[s.count] = i;
-            s.mult[s.count] = v[i];
-            ++s.count;
-        }
-    }
-    return PQ_OK;
-}
-
 }  // namespace
 
 }  // namespace pq
@@ -912,27 +990,36 @@ static int perm_jobs(pq_ctx* ctx, const char* name, const pq_c128* U, int64_t ld
     if (njobs == 0) return PQ_OK;
     if (!jobs || !perm) return ctx->fail(PQ_EINVAL, "%s: NULL jobs or perm", name);
     if (m > 0 && (!U || ldu < m)) return ctx->fail(PQ_EINVAL, "%s: NULL U or ldu < m", name);
-    std::vector<int64_t> key = {0, m, njobs};
-    int rc = pq_validate_jobs(ctx, m, jobs, njobs, key);
-    if (rc) return rc;
-    DeviceGuard guard(ctx->device);
+    int rc;
     hipStream_t st = (hipStream_t)stream;
-    std::vector<PatternSpec> pats;
-    pats.reserve(njobs);
-    for (int k = 0; k < njobs; ++k) {
-        const pq_job& J = jobs[k];
-        PatternSpec ps;
-        ps.op = J.op == PQ_OP_EXTEND_ROW ? kOpExtend : kOpPerm;
-        ps.rows.count = J.nr;
-        for (int i = 0; i < J.nr; ++i) { ps.rows.mode[i] = J.row_idx[i]; ps.rows.mult[i] = J.row_mult[i]; }
-        ps.cols.count = J.nc;
-        for (int i = 0; i < J.nc; ++i) { ps.cols.mode[i] = J.col_idx[i]; ps.cols.mult[i] = J.col_mult[i]; }
-        ps.out = J.out_offset;
-        pats.push_back(ps);
+    ManyEntry* E = find_jobs(ctx, m, jobs, njobs);
+    if (!E) {
+        rc = pq_validate_jobs(ctx, m, jobs, njobs);
+        if (rc) return rc;
+        ManyKey key;
+        key.mode = kModeFwd;
+        key.m = m;
+        key.count = njobs;
+        std::vector<PatRef> pats((size_t)njobs);
+        size_t ints = 0;
+        for (int k = 0; k < njobs; ++k) ints += 5 + 2 * ((size_t)jobs[k].nr + (size_t)jobs[k].nc);
+        key.flat.reserve(ints);
+        for (int k = 0; k < njobs; ++k) {
+            const pq_job& J = jobs[k];
+            pats[(size_t)k] = PatRef{J.op == PQ_OP_EXTEND_ROW ? kOpExtend : kOpPerm, J.nr, J.nc, J.row_idx, J.row_mult,
+                                     J.col_idx, J.col_mult, J.out_offset};
+            const int32_t head[5] = {J.op, J.nr, J.nc, (int32_t)(uint32_t)J.out_offset, (int32_t)(J.out_offset >> 32)};
+            key.flat.insert(key.flat.end(), head, head + 5);
+            key.flat.insert(key.flat.end(), J.row_idx, J.row_idx + J.nr);
+            key.flat.insert(key.flat.end(), J.row_mult, J.row_mult + J.nr);
+            key.flat.insert(key.flat.end(), J.col_idx, J.col_idx + J.nc);
+            key.flat.insert(key.flat.end(), J.col_mult, J.col_mult + J.nc);
+        }
+        DeviceGuard guard(ctx->device);
+        rc = new_entry(ctx, kModeFwd, m, key, pats, st, &E, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, queue);
+        if (rc) return rc;
     }
-    ManyEntry* E = nullptr;
-    rc = get_entry(ctx, kModeFwd, m, key, pats, st, &E, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, queue);
-    if (rc) return rc;
+    DeviceGuard guard(ctx->device);
     if (queue) {
         // a plan whose every pattern is one chunk has nothing for a queue to
         // balance: one workgroup per chunk is already that schedule; a tuned
@@ -971,34 +1058,64 @@ int pq_perm_grad(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     if (!dU || lddu < m) return ctx->fail(PQ_EINVAL, "pq_perm_grad: NULL dU or lddu < m");
     if (batch > 0 && (!S || !T || !gperm)) return ctx->fail(PQ_EINVAL, "pq_perm_grad: NULL pattern or gperm");
     if (m > 0 && (!U || ldu < m)) return ctx->fail(PQ_EINVAL, "pq_perm_grad: NULL U or ldu < m");
-    std::vector<int64_t> key = {1, m, batch, ctx->walk_variant};
-    key.reserve(3 + 2 * (size_t)batch * m);
-    std::vector<PatternSpec> pats(batch);
-    for (int p = 0; p < batch; ++p) {
-        const int32_t* sp = S + (size_t)p * m;
-        const int32_t* tp = T + (size_t)p * m;
-        int rc = side_from_dense(m, sp, pats[p].cols);
-        if (rc) return ctx->fail(rc, "pq_perm_grad: pattern %d input side invalid", p);
-        rc = side_from_dense(m, tp, pats[p].rows);
-        if (rc) return ctx->fail(rc, "pq_perm_grad: pattern %d output side invalid", p);
-        if (pats[p].rows.count > PQ_GRAD_MAX_DIM || pats[p].cols.count > PQ_GRAD_MAX_DIM)
-            return ctx->fail(PQ_ERANGE, "pq_perm_grad: pattern %d has more than %d distinct modes", p, PQ_GRAD_MAX_DIM);
-        long ns = 0, nt = 0;
-        for (int i = 0; i < m; ++i) { ns += sp[i]; nt += tp[i]; }
-        if (ns == nt && ns > PQ_MAX_N) return ctx->fail(PQ_ERANGE, "pq_perm_grad: pattern %d too large", p);
-        pats[p].op = kOpPerm;
-        pats[p].out = p;
-        key.push_back(ns);
-        for (int i = 0; i < pats[p].cols.count; ++i) key.push_back(((int64_t)pats[p].cols.mode[i] << 32) | pats[p].cols.mult[i]);
-        key.push_back(-1);
-        for (int i = 0; i < pats[p].rows.count; ++i) key.push_back(((int64_t)pats[p].rows.mode[i] << 32) | pats[p].rows.mult[i]);
-        key.push_back(-2);
+    hipStream_t st = (hipStream_t)stream;
+    ManyEntry* E = find_dense(ctx, m, batch, S, T);
+    if (!E) {
+        // every pattern's occupied modes, input side then output side
+        std::vector<int32_t> lists;
+        std::vector<PatRef> pats((size_t)batch);
+        for (int pass = 0; pass < 2; ++pass) {
+            size_t at = 0;
+            for (int p = 0; p < batch; ++p) {
+                int64_t sum[2] = {0, 0};
+                for (int side = 0; side < 2; ++side) {
+                    const int32_t* v = (side ? T : S) + (size_t)p * m;
+                    int32_t count = 0;
+                    bool bad = false;
+                    for (int i = 0; i < m; ++i) {
+                        bad = bad || v[i] < 0;
+                        count += v[i] > 0;
+                        sum[side] += v[i];
+                    }
+                    if (bad || count > kMaxDim)
+                        return ctx->fail(bad ? PQ_EINVAL : PQ_ERANGE, "pq_perm_grad: pattern %d %s side invalid", p,
+                                         side ? "output" : "input");
+                    if (pass == 1) {
+                        int32_t *idx = lists.data() + at, *mult = idx + count;
+                        for (int i = 0, q = 0; i < m; ++i)
+                            if (v[i] > 0) {
+                                idx[q] = i;
+                                mult[q++] = v[i];
+                            }
+                        PatRef& R = pats[(size_t)p];
+                        (side ? R.nr : R.nc) = count;
+                        (side ? R.row_idx : R.col_idx) = idx;
+                        (side ? R.row_mult : R.col_mult) = mult;
+                    } else {
+                        (side ? pats[(size_t)p].nr : pats[(size_t)p].nc) = count;
+                    }
+                    at += 2 * (size_t)count;
+                }
+                if (pats[(size_t)p].nr > PQ_GRAD_MAX_DIM || pats[(size_t)p].nc > PQ_GRAD_MAX_DIM)
+                    return ctx->fail(PQ_ERANGE, "pq_perm_grad: pattern %d has more than %d distinct modes", p, PQ_GRAD_MAX_DIM);
+                if (sum[0] == sum[1] && sum[0] > PQ_MAX_N) return ctx->fail(PQ_ERANGE, "pq_perm_grad: pattern %d too large", p);
+                pats[(size_t)p].op = kOpPerm;
+                pats[(size_t)p].out = p;
+            }
+            if (pass == 0) lists.resize(at);
+        }
+        ManyKey key;
+        key.mode = kModeAdj;
+        key.m = m;
+        key.count = batch;
+        key.walk_variant = ctx->walk_variant;
+        key.flat.reserve(2 * (size_t)batch * (size_t)m);
+        key.flat.insert(key.flat.end(), S, S + (size_t)batch * m);
+        key.flat.insert(key.flat.end(), T, T + (size_t)batch * m);
+        DeviceGuard guard(ctx->device);
+        if (int rc = new_entry(ctx, kModeAdj, m, key, pats, st, &E)) return rc;
     }
     DeviceGuard guard(ctx->device);
-    hipStream_t st = (hipStream_t)stream;
-    ManyEntry* E = nullptr;
-    int rc = get_entry(ctx, kModeAdj, m, key, pats, st, &E);
-    if (rc) return rc;
     return run_many(ctx, *E, (const cplx*)U, ldu, m, (cplx*)perm, nullptr, (const cplx*)gperm, (cplx*)dU,
                     lddu, st);
 }

@@ -29,6 +29,17 @@ bool term_count(const Side& it, uint64_t& terms, int& fixed_index) {
 // Choose lane digits among the free rows: the subset whose radix product is
 // the largest value <= cap (first subset found in row order for each product).
 static void choose_lane_digits(int nfree, const int* radix, int cap, int* chosen, int& nchosen, int& product) {
+    // all binary: the first rows whose product fits (what the search below finds)
+    bool binary = true;
+    for (int i = 0; i < nfree; ++i) binary = binary && radix[i] == 2;
+    if (binary) {
+        nchosen = 0;
+        for (product = 1; nchosen < nfree && 2 * product <= cap; product *= 2) {
+            chosen[nchosen] = nchosen;
+            ++nchosen;
+        }
+        return;
+    }
     // reach[p] = bitmask (over free rows, nfree <= 48) giving product p
     uint64_t reach[65];
     bool ok[65];
@@ -62,8 +73,10 @@ void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan&
     for (int j = 0; j < cols.count; ++j) nc_ += cols.mult[j];
     // normaliser 1/sqrt(prod S! prod T!) in log2
     double lg = 0.0;
-    for (int i = 0; i < rows.count; ++i) lg += lgamma((double)rows.mult[i] + 1.0);
-    for (int j = 0; j < cols.count; ++j) lg += lgamma((double)cols.mult[j] + 1.0);
+    for (int i = 0; i < rows.count; ++i)
+        if (rows.mult[i] > 1) lg += lgamma((double)rows.mult[i] + 1.0);
+    for (int j = 0; j < cols.count; ++j)
+        if (cols.mult[j] > 1) lg += lgamma((double)cols.mult[j] + 1.0);
     p.log2_norm = -0.5 * lg / log(2.0);
     p.norm = exp2(p.log2_norm);
     if (extend) {

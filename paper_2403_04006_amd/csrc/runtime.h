@@ -134,8 +134,8 @@ struct pq_ctx {
 void pq_release_many_cache(pq_ctx* ctx);
 void pq_release_all_cache(pq_ctx* ctx);
 // Validate pq_job descriptions (modes, multiplicities, photon counts, output
-// overlap) and append them to `key`.
-int pq_validate_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs, std::vector<int64_t>& key);
+// overlap).
+int pq_validate_jobs(pq_ctx* ctx, int32_t m, const pq_job* jobs, int32_t njobs);
 
 namespace pq {
 
