@@ -109,35 +109,12 @@ int plan_haf(const int32_t* reps, int d, HafPlan& p, const char** why) {
 // Inner Gray block tables: forward positions 0..M-1 are inner ranks 0..M-1,
 // reflected positions are ranks M-1..0.
 void haf_tables(const HafPlan& p, std::vector<HafStep>& tab) {
-    const int M = p.M, n_in = p.n_in;
-    auto rad = [&](int i) { return p.rad[p.to + i]; };
-    std::vector<int> prev(n_in > 0 ? n_in : 1, 0), cur(n_in > 0 ? n_in : 1, 0);
+    const int M = p.M;
     tab.assign((size_t)2 * M, HafStep{0, 0, 0.0});
-    for (int r = 0; r < M; ++r) {
-        double w = 1.0;
-        gray_digits_desc(n_in, rad, (uint64_t)r, 0, [&](int i, int g) {
-            cur[i] = g;
-            w *= digit_weight(rad(i), g);
-        });
-        HafStep& e = tab[r];
-        e.w = w;
-        if (r > 0) {
-            for (int i = 0; i < n_in; ++i)
-                if (cur[i] != prev[i]) {
-                    e.t = i;
-                    e.dx = cur[i] > prev[i] ? -2 : 2;
-                }
-        }
-        prev = cur;
-    }
-    for (int pos = 0; pos < M; ++pos) {
-        HafStep& e = tab[(size_t)M + pos];
-        e.w = tab[(size_t)(M - 1 - pos)].w;
-        if (pos > 0) {
-            // reflected step pos-1 -> pos is forward step M-pos undone
-            e.t = tab[(size_t)(M - pos)].t;
-            e.dx = -tab[(size_t)(M - pos)].dx;
-        }
+    for (int q = 0; q < M; ++q) {
+        const GrayStep g = gray_step(p.n_in, [&](int i) { return p.rad[p.to + i]; }, M, q);
+        tab[(size_t)q] = q > 0 ? HafStep{g.fwd, g.fwd_up ? -2 : 2, g.w} : HafStep{0, 0, g.w};
+        tab[(size_t)(2 * M - 1 - q)] = q < M - 1 ? HafStep{g.bwd, g.bwd_up ? -2 : 2, g.w} : HafStep{0, 0, g.w};
     }
 }
 
@@ -216,12 +193,10 @@ int check_reps(pq_ctx* ctx, const int32_t* reps, int d, int* N, const char* who)
     return PQ_OK;
 }
 
-// Plan one pattern: its descriptor (offsets left to the caller), plan and,
-// when tab is not null, step tables.  Trivial patterns (N = 0; odd N without
+// Plan one pattern: its descriptor (offsets left to the caller) and plan.  Trivial patterns (N = 0; odd N without
 // loops) get nchunks = 0 and their value.  The loop factors (kHafFactors)
 // are the caller's: they depend only on N.
-int describe(pq_ctx* ctx, const int32_t* reps, int d, int N, bool loops, HafDesc& D, HafPlan& p,
-             std::vector<HafStep>* tab, const char* who) {
+int describe(pq_ctx* ctx, const int32_t* reps, int d, int N, bool loops, HafDesc& D, HafPlan& p, const char* who) {
     memset(&D, 0, sizeof(D));
     D.N = N;
     if (N == 0 || (!loops && (N & 1))) {
@@ -232,7 +207,6 @@ int describe(pq_ctx* ctx, const int32_t* reps, int d, int N, bool loops, HafDesc
     const char* why = "";
     int rc = plan_haf(reps, d, p, &why);
     if (rc) return ctx->fail(rc, "%s: %s", who, why);
-    if (tab) haf_tables(p, *tab);
     D.time_states = p.time_states;
     D.k = p.k;
     D.nl = p.nl;
@@ -385,8 +359,7 @@ int pq_lhaf(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq_c128
     const bool loops = gamma != nullptr;
     HafDesc D;
     HafPlan p;
-    std::vector<HafStep> tab;
-    rc = describe(ctx, reps, d, N, loops, D, p, &tab, "pq_lhaf");
+    rc = describe(ctx, reps, d, N, loops, D, p, "pq_lhaf");
     if (rc) return rc;
     if (D.nchunks == 0) return ctx->check(launch_fill((cplx*)out, nullptr, D.trivial, st), "fill");
 
@@ -416,21 +389,24 @@ int pq_lhaf(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq_c128
     const uint64_t max_waves = (uint64_t)ctx->num_cu * (uint64_t)occ * kWavesPerBlock * kHafRounds;
     uint64_t waves = (work + kHafMinChunk - 1) / kHafMinChunk;
     if (waves > max_waves) waves = max_waves;
+    // a sweep too short to give every resident wavefront that many states is
+    // spread over them in shorter shares
+    const uint64_t resident = max_waves / kHafRounds;
+    if (waves < resident) {
+        const uint64_t least = loops ? kHafSpreadLoops : kHafSpread;
+        waves = (work + least - 1) / least;
+        if (waves > resident) waves = resident;
+    }
     if (waves < 1) waves = 1;
     const int grid = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
 
     Carve cv;
     const size_t oA = cv.take(sizeof(cplx) * (size_t)p.k * (size_t)p.k);
     const size_t oG = cv.take(sizeof(cplx) * (size_t)p.k);
-    const size_t oT = cv.take(sizeof(HafStep) * tab.size());
+    const size_t oT = cv.take(sizeof(HafStep) * 2 * (size_t)p.M);
     const size_t oP = cv.take(sizeof(double) * 4 * (size_t)waves);
     char* ws = (char*)ctx->workspace(cv.off);
     if (!ws) return PQ_ENOMEM;
-    char* stage = (char*)ctx->staging(sizeof(HafStep) * tab.size());
-    if (!stage) return PQ_ENOMEM;
-    memcpy(stage, tab.data(), sizeof(HafStep) * tab.size());
-    rc = ctx->upload(ws + oT, stage, sizeof(HafStep) * tab.size(), st);
-    if (rc) return rc;
 
     HafPrepArgs pa;
     memset(&pa, 0, sizeof(pa));
@@ -441,6 +417,10 @@ int pq_lhaf(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq_c128
     for (int i = 0; i < p.k; ++i) pa.mode[i] = p.mode[i];
     pa.Ac = (cplx*)(ws + oA);
     pa.gc = (cplx*)(ws + oG);
+    pa.n_in = p.n_in;
+    pa.M = p.M;
+    for (int i = 0; i < p.n_in; ++i) pa.rad[i] = p.rad[p.to + i];
+    pa.tab = (HafStep*)(ws + oT);
     rc = ctx->check(launch_haf_prep(pa, st), "hafnian prep");
     if (rc) return rc;
 
@@ -513,7 +493,7 @@ int pq_lhaf_many(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq
         int N = 0;
         int rc = check_reps(ctx, r, d, &N, "pq_lhaf_many");
         if (rc) return rc;
-        rc = describe(ctx, r, d, N, loops, descs[q], p, nullptr, "pq_lhaf_many");
+        rc = describe(ctx, r, d, N, loops, descs[q], p, "pq_lhaf_many");
         if (rc) return rc;
         if (descs[q].nchunks == 0) continue;
         any = true;

@@ -47,7 +47,14 @@ constexpr int kHafMaxTime = 32;    // time digits
 constexpr int kHafMaxLane = 7;     // lane digits (six of radix >= 2 and a radix-1 fixed mode)
 constexpr int kHafMaxN = 64;       // vertices (photons)
 constexpr int kHafInner = 2048;    // inner (table-driven) Gray block
-constexpr uint64_t kHafMinChunk = 256;   // time states per wavefront, at least
+constexpr uint64_t kHafMinChunk = 256;   // time states per wavefront, at least, in a sweep that fills the device
+// In one that does not, a share of fewer states still pays for its wavefront's
+// set-up (loop-free and loop steps).  Twice as many or twice as few were slower or
+// level: 10, 12 and 14 doubled modes at 4, 8, 16 and 64 states took 18, 27, 48 /
+// 19, 27, 45 / 22, 28, 43 / 33, 43, 51 us (90, 128, 136 at 256), with loops
+// 22, 30, 54 / 27, 33, 55 / 34, 40, 60 / 82, 88, 109 us (261, 300, 358 at 256).
+constexpr uint64_t kHafSpread = 8;
+constexpr uint64_t kHafSpreadLoops = 4;
 // A hafnian sweep splits its steps evenly over this many rounds of the
 // resident wavefronts (each at least kHafMinChunk states): later rounds go to
 // the CUs that finish first.  On 2 x 20 modes 1, 2, 4, 8 and 16 rounds took
@@ -74,6 +81,9 @@ struct HafPrepArgs {
     int32_t mode[kHafMaxModes];       // digit order -> mode of A
     cplx* Ac;                         // [k][k]
     cplx* gc;                         // [k]
+    int32_t n_in, M;                  // inner time digits and their block length
+    int32_t rad[kHafMaxTime];         // their radices
+    HafStep* tab;                     // [2][M]: forward block, reflected block
 };
 
 // Plan of one loop hafnian sweep: digits, term polynomial and (batched path)

@@ -60,44 +60,17 @@ hipError_t launch_bprep(const BPrepArgs& a, hipStream_t s) {
 // Same construction as the single-permanent table kernel, for every signature
 // (n_inner, m_inner, ncmax, radices): forward entries at tabs + t*2*kMaxInner,
 // reflected entries kMaxInner further.
-__device__ static void btable_state(int n_inner, const int32_t* radix, int q, int32_t* g, double& w) {
-    gray_unrank(n_inner, radix, (uint64_t)q, g);
-    w = 1.0;
-    for (int k = 0; k < n_inner; ++k) w *= digit_weight(radix[k], g[k]);
-}
-
-__device__ static int32_t btable_step(int n_inner, int nc, const int32_t* g0, const int32_t* g1) {
-    for (int k = 0; k < n_inner; ++k)
-        if (g0[k] != g1[k]) return (int32_t)(((size_t)k * 2 + (g1[k] > g0[k] ? 0 : 1)) * nc);
-    return 0;
-}
-
 __global__ __launch_bounds__(kBlock) void btable_kernel(const BTableArgs a) {
     const int t = blockIdx.y;
     if (t >= a.ntab) return;
     const int32_t* sg = a.sig + (size_t)t * kSigInts;
     const int n_inner = sg[0], M = sg[1], nc = sg[2];
-    int32_t radix[16];
-    for (int k = 0; k < n_inner; ++k) radix[k] = sg[3 + k];
     StepEntry* tf = a.tabs + (size_t)t * 2 * kMaxInner;
     StepEntry* tb = tf + kMaxInner;
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < M; q += gridDim.x * blockDim.x) {
-        int32_t g[16], gp[16];
-        double w, wp;
-        btable_state(n_inner, radix, q, g, w);
-        StepEntry f{0, 0, w};
-        if (q > 0) {
-            btable_state(n_inner, radix, q - 1, gp, wp);
-            f.off = btable_step(n_inner, nc, gp, g);
-        }
-        tf[q] = f;
-        const int p = M - 1 - q;
-        StepEntry b{0, 0, w};
-        if (p > 0) {
-            btable_state(n_inner, radix, q + 1, gp, wp);
-            b.off = btable_step(n_inner, nc, gp, g);
-        }
-        tb[p] = b;
+        const GrayStep e = gray_step(n_inner, [&](int k) { return sg[3 + k]; }, M, q);
+        tf[q] = StepEntry{q > 0 ? (2 * e.fwd + (e.fwd_up ? 0 : 1)) * nc : 0, 0, e.w};
+        tb[M - 1 - q] = StepEntry{q < M - 1 ? (2 * e.bwd + (e.bwd_up ? 0 : 1)) * nc : 0, 0, e.w};
     }
 }
 

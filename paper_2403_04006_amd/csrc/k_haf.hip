@@ -8,7 +8,8 @@ namespace pq {
 
 // Compact matrix from the upper triangle of A (the definition reads the
 // pairs i < j; A_ii is the weight between two copies of mode i) and the loop
-// weights, both in digit order.
+// weights, both in digit order, and the step tables of the inner Gray block
+// (position p of the reflected block is rank M - 1 - p).
 __global__ __launch_bounds__(kBlock) void haf_prep_kernel(const HafPrepArgs a) {
     const int e = (int)(blockIdx.x * kBlock + threadIdx.x);
     const int kk = a.k * a.k;
@@ -24,6 +25,11 @@ __global__ __launch_bounds__(kBlock) void haf_prep_kernel(const HafPrepArgs a) {
     } else if (e < kk + a.k) {
         const int i = e - kk;
         a.gc[i] = a.gamma ? a.gamma[a.mode[i]] : cplx{0.0, 0.0};
+    }
+    for (int q = e; q < a.M; q += (int)(gridDim.x * kBlock)) {
+        const GrayStep g = gray_step(a.n_in, [&](int i) { return a.rad[i]; }, a.M, q);
+        a.tab[q] = q > 0 ? HafStep{g.fwd, g.fwd_up ? -2 : 2, g.w} : HafStep{0, 0, g.w};
+        a.tab[2 * a.M - 1 - q] = q < a.M - 1 ? HafStep{g.bwd, g.bwd_up ? -2 : 2, g.w} : HafStep{0, 0, g.w};
     }
 }
 
@@ -73,7 +79,8 @@ __global__ __launch_bounds__(kBlock) void haf_many_final_kernel(const HafManyFin
 
 
 hipError_t launch_haf_prep(const HafPrepArgs& a, hipStream_t s) {
-    const int n = a.k * a.k + a.k;
+    if (a.M < 1 || !a.tab) return hipErrorInvalidValue;
+    const int n = a.k * a.k + a.k > a.M ? a.k * a.k + a.k : a.M;
     const int blocks = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(haf_prep_kernel, dim3((unsigned)(blocks > 0 ? blocks : 1)), dim3(kBlock), 0, s, a);
     return hipGetLastError();

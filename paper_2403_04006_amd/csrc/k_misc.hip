@@ -49,52 +49,16 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
 // Per-step table of the inner digits.  Forward traversal: position q is the
 // Gray state of rank q.  Reflected traversal: position p is the state of rank
 // M-1-p (the inner code run backwards).  Entry p holds the row offset of the
-// step from position p-1 to p and the signed binomial weight of state p.
-__device__ static void table_state(const TableArgs& a, int q, int32_t* g, double& w) {
-    gray_unrank(a.n_inner, a.radix, (uint64_t)q, g);
-    w = 1.0;
-    for (int k = 0; k < a.n_inner; ++k) w *= digit_weight(a.radix[k], g[k]);
-}
-
-// Offset of the row applied when moving from state g0 to state g1 (one digit
-// differs by one): digit up -> -2B row (sel 0), down -> +2B row (sel 1).
-__device__ static int32_t table_step(const TableArgs& a, const int32_t* g0, const int32_t* g1) {
-    for (int k = 0; k < a.n_inner; ++k) {
-        if (g0[k] != g1[k]) {
-            const int sel = g1[k] > g0[k] ? 0 : 1;
-            return (int32_t)(((size_t)k * 2 + sel) * a.nc);
-        }
-    }
-    return 0;
-}
-
+// step from position p-1 to p (digit up -> -2B row, down -> +2B row) and the
+// signed binomial weight of state p.
 __global__ __launch_bounds__(kBlock) void table_kernel(const TableArgs a) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= a.m_inner) return;
-    int32_t g[16], gp[16];
-    double w, wp;
-    table_state(a, q, g, w);
-    StepEntry f;
-    f.pad = 0;
-    f.w = w;
-    f.off = 0;
-    if (q > 0) {
-        table_state(a, q - 1, gp, wp);
-        f.off = table_step(a, gp, g);
-    }
-    a.tab_fwd[q] = f;
-    // reflected traversal: position p = M-1-q holds state q; its step comes
-    // from state q+1
-    const int p = a.m_inner - 1 - q;
-    StepEntry b;
-    b.pad = 0;
-    b.w = w;
-    b.off = 0;
-    if (p > 0) {
-        table_state(a, q + 1, gp, wp);
-        b.off = table_step(a, gp, g);
-    }
-    a.tab_bwd[p] = b;
+    const GrayStep e = gray_step(a.n_inner, [&](int k) { return a.radix[k]; }, a.m_inner, q);
+    const int32_t of = (int32_t)((2 * e.fwd + (e.fwd_up ? 0 : 1)) * a.nc);
+    const int32_t ob = (int32_t)((2 * e.bwd + (e.bwd_up ? 0 : 1)) * a.nc);
+    a.tab_fwd[q] = StepEntry{q > 0 ? of : 0, 0, e.w};
+    a.tab_bwd[a.m_inner - 1 - q] = StepEntry{q < a.m_inner - 1 ? ob : 0, 0, e.w};
 }
 
 hipError_t launch_table(const TableArgs& a, hipStream_t s) {

@@ -137,8 +137,15 @@ struct FinalArgs {
 PQ_HD void gray_unrank(int d, const int32_t* radix, uint64_t rank, int32_t* g, int parity_in = 0) {
     int32_t a[kMaxDim];
     for (int k = 0; k < d; ++k) {
-        a[k] = (int32_t)(rank % (uint64_t)radix[k]);
-        rank /= (uint64_t)radix[k];
+        if (rank >> 32) {
+            a[k] = (int32_t)(rank % (uint64_t)radix[k]);
+            rank /= (uint64_t)radix[k];
+        } else {
+            // a 64-bit division costs a kernel six times a 32-bit one
+            const uint32_t r = (uint32_t)rank, q = r / (uint32_t)radix[k];
+            a[k] = (int32_t)(r - q * (uint32_t)radix[k]);
+            rank = q;
+        }
     }
     int par = parity_in;
     for (int k = d - 1; k >= 0; --k) {
@@ -147,19 +154,55 @@ PQ_HD void gray_unrank(int d, const int32_t* radix, uint64_t rank, int32_t* g, i
     }
 }
 
+// x / d for a divisor d of x (odd ones by their inverse modulo 2^64).
+PQ_HD uint64_t exact_div(uint64_t x, uint32_t d) {
+    switch (d) {
+        case 1: return x;
+        case 2: return x >> 1;
+        case 3: return x * 0xAAAAAAAAAAAAAAABull;
+        case 4: return x >> 2;
+        case 5: return x * 0xCCCCCCCCCCCCCCCDull;
+        case 6: return (x >> 1) * 0xAAAAAAAAAAAAAAABull;
+        default: return x / d;
+    }
+}
+
+// x / y and x mod y where the quotient is small (below 2^20).
+PQ_HD uint32_t small_quotient(uint64_t x, uint64_t y, uint64_t& rem) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    // an estimate that is off by one at most, then corrected
+    uint32_t q = (uint32_t)((double)x * __builtin_amdgcn_rcp((double)y));
+    int64_t r = (int64_t)(x - (uint64_t)q * y);
+    if (r < 0) {
+        --q;
+        r += (int64_t)y;
+    } else if (r >= (int64_t)y) {
+        ++q;
+        r -= (int64_t)y;
+    }
+    rem = (uint64_t)r;
+    return q;
+#else
+    rem = x % y;
+    return (uint32_t)(x / y);
+#endif
+}
+
 // The same digits without a digit array: f(k, g_k) for k = d-1 down to 0,
-// with radix(k) the radix of digit k.  Each digit is recovered by dividing by
-// the product of the radices below it, so every value stays wavefront-uniform.
-// Returns the parity of the digit sum (with parity_in).
+// with radix(k) the radix of digit k.  Each digit is the quotient by the
+// product of the radices below it, so every value stays wavefront-uniform.
+// Ranks and products stay below 2^62.  Returns the parity of the digit sum
+// (with parity_in).  Plain 64-bit divisions here (three a digit, about 150
+// instructions each) were most of a short sweep: 84 us of 2 x 15 rows.
 template <class Radix, class F>
 PQ_HD int gray_digits_desc(int d, Radix radix, uint64_t rank, int parity_in, F&& f) {
     uint64_t below = 1;
     for (int k = 0; k < d; ++k) below *= (uint64_t)radix(k);
     int par = parity_in;
     for (int k = d - 1; k >= 0; --k) {
-        const uint64_t rk = (uint64_t)radix(k);
-        below /= rk;
-        const int a = (int)((rank / below) % rk);
+        const uint32_t rk = (uint32_t)radix(k);
+        below = exact_div(below, rk);
+        const int a = (int)small_quotient(rank, below, rank);
         const int g = par ? (int)rk - 1 - a : a;
         par ^= g & 1;
         f(k, g);
@@ -170,8 +213,10 @@ PQ_HD int gray_digits_desc(int d, Radix radix, uint64_t rank, int parity_in, F&&
 // C(a, b) for small non-negative integers, exact in double (a <= 48).
 PQ_HD double binom_d(int a, int b) {
     if (b < 0 || b > a) return 0.0;
-    double r = 1.0;
-    for (int k = 1; k <= b; ++k) r = r * (double)(a - b + k) / (double)k;
+    if (b > a - b) b = a - b;
+    if (b == 0) return 1.0;
+    double r = (double)(a - b + 1);
+    for (int k = 2; k <= b; ++k) r = r * (double)(a - b + k) / (double)k;   // C(a - b + k, k): exact
     return r;
 }
 
@@ -179,6 +224,41 @@ PQ_HD double binom_d(int a, int b) {
 PQ_HD double digit_weight(int rho, int d) {
     double w = binom_d(rho - 1, d);
     return (d & 1) ? -w : w;
+}
+
+// One state of a Gray block of n digits (M states, at most 2^16): its signed
+// binomial weight w, and the digits that move on the steps into it, from rank
+// q - 1 (fwd, q >= 1) and from rank q + 1 (bwd, q <= M - 2): the lowest counter
+// digit that does not wrap, up or down by the parity of the digits above it.
+struct GrayStep {
+    double w;
+    int fwd, bwd;            // digit
+    int fwd_up, bwd_up;      // 1: the digit rises
+};
+
+template <class Radix>
+PQ_HD GrayStep gray_step(int n, Radix radix, int M, int q) {
+    GrayStep e{1.0, 0, 0, 0, 0};
+    uint32_t below = (uint32_t)M, rem = (uint32_t)q;
+    int par = 0;
+    for (int k = n - 1; k >= 0; --k) {
+        const uint32_t rk = (uint32_t)radix(k);
+        below /= rk;
+        const uint32_t a = rem / below;
+        rem -= a * below;
+        if (a != 0) {
+            e.fwd = k;
+            e.fwd_up = !par;
+        }
+        if (a != rk - 1) {
+            e.bwd = k;
+            e.bwd_up = par;
+        }
+        const int g = par ? (int)(rk - 1 - a) : (int)a;
+        e.w *= digit_weight((int)rk, g);
+        par ^= g & 1;
+    }
+    return e;
 }
 
 // Even split of [0, total) over `parts`: [start, start + count) of part w.

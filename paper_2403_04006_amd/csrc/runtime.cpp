@@ -199,6 +199,9 @@ namespace pq {
 // Fewest time steps per wavefront worth a wavefront's start-up (the column
 // sums are rebuilt from the digits, about (digits x NC) multiply-adds).
 static constexpr uint64_t kMinStepsPerWave = 32;
+// and in a sweep that leaves the device part empty at that share, where a
+// wavefront more costs nothing else: 20 photons 30 -> 24 us, 2 x 11 rows 35 -> 25
+static constexpr uint64_t kSpreadSteps = 8;
 
 // Sweep kernel kind of a plan (see kernels.h).
 int sweep_kind(const Plan& p) {
@@ -212,11 +215,24 @@ int sweep_waves_per_cu(pq_ctx* ctx, const Plan& p, int rounds) {
     return ctx->occupancy(sweep_kind(p), p.nc) * kWavesPerBlock * rounds;
 }
 
-Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu) {
+Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread) {
     Geometry g;
     const uint64_t full = (uint64_t)(waves_per_cu > 0 ? waves_per_cu : 1) * (uint64_t)ctx->num_cu;
+    const uint64_t round = (uint64_t)ctx->occupancy(sweep_kind(p), p.nc) * kWavesPerBlock * (uint64_t)ctx->num_cu;
     uint64_t waves = (p.time_states + kMinStepsPerWave - 1) / kMinStepsPerWave;
     if (waves > full) waves = full;
+    if (!spread) {
+        // the share alone
+    } else if (waves > round) {
+        // whole rounds: one begun for a few wavefronts costs a whole one
+        // (2 x 15 rows, 1.08 rounds: 83 us, one round: 74)
+        waves = waves / round * round;
+    } else {
+        // too short for a full round at that share: spread over one
+        waves = (p.time_states + kSpreadSteps - 1) / kSpreadSteps;
+        if (waves > round) waves = round;
+        if (waves > full) waves = full;
+    }
     if (waves < 1) waves = 1;
     g.waves = (uint32_t)waves;
     g.grid = (int)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
@@ -275,9 +291,9 @@ int timed_sweep(pq_ctx* ctx, int kind, int nc, const GlynnArgs& a, int grid, hip
     return PQ_OK;
 }
 
-SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu) {
+SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread) {
     SingleLayout L;
-    L.geo = sweep_geometry(ctx, p, waves_per_cu);
+    L.geo = sweep_geometry(ctx, p, waves_per_cu, spread);
     const int r = p.r, nc = p.nc;
     const size_t ntab = p.binary ? 0 : (size_t)p.m_inner;
     Carve cv;

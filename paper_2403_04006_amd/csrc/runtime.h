@@ -166,14 +166,16 @@ struct Geometry {
     uint32_t waves = 1; // active wavefronts
 };
 // The sweep splits its time-state range evenly over num_cu * waves_per_cu
-// wavefronts (each at least 32 states).  The default is two rounds of the
+// wavefronts (each at least 32 states).  With `spread`, whole rounds of the
+// resident wavefronts, and one round, each at least 8 states, where that share
+// does not fill one.  The default is two rounds of the
 // resident wavefronts: the dispatcher hands the second round's workgroups to
 // the CUs that finish their first ones early, which evens out unequal CU and
 // XCD speeds that a single round leaves on the critical path.
 constexpr int kSweepRounds = 2;
 // rounds x the resident wavefronts per CU of the plan's sweep kernel
 int sweep_waves_per_cu(pq_ctx* ctx, const Plan& p, int rounds = kSweepRounds);
-Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu);
+Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread = true);
 // Shape signature of a single permanent's launch (kernel kind, sums, digits
 // and powers: n and the multiplicity class), for the autotuner's records.
 uint64_t single_sig(const Plan& p);
@@ -192,7 +194,7 @@ struct SingleLayout {
     size_t oB = 0, oR = 0, oBase = 0, oTf = 0, oTb = 0, oP = 0;
     size_t bytes = 0;
 };
-SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu);
+SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread = true);
 
 // Full single-permanent sequence (prep, table, sweep, final) on the scratch
 // `ws` laid out by `L`; `timed` brackets the sweep with profiling events.
