@@ -6,7 +6,6 @@
 
 namespace pq {
 
-constexpr int kChainWaves = 4;          // wavefronts per sample (workgroup)
 constexpr int kChainMaxPhotons = 24;
 constexpr int kChainMaxModes = 1024;
 

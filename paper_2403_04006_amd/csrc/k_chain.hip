@@ -3,47 +3,311 @@
 // sample's whole draw sequence.
 //
 // Step k (k = 1..n) with rows r_1..r_{k-1} drawn so far and the first k input
-// modes of the sample's order c_1..c_k:
-//   L_j = perm(U[r; c without c_j])      (the k leave-one-column-out minors)
-//   out_l = sum_j U[l, c_j] L_j = perm(U_{r + l, c})   for every mode l,
-//   r_k = the first l whose cumulative |out|^2 (in mode order) exceeds
-//         u_k times the total.
-// The minors come from one Glynn sweep over the k-1 drawn rows (repeated rows
-// are separate rows; the first row is the fixed one): every term's
-// leave-one-out products are the running sums P_j of the reverse-sweep walk,
-// with four lanes per term (walk_term).  Free row rho takes a lane digit
-// (rho = 1..4, 16 terms per wavefront), a wavefront digit (rho = 5, 6; four
-// wavefronts) or a time digit (rho >= 7).
+// modes of the sample's order c_0..c_{k-1}: the permanents of every next row l,
+//   out_l = perm(U_{r + l, c}) = sum_j U[l, c_j] M_j,
+//   M_j = 2^{-(k-1)} sum_delta (prod delta) delta_j prod_{i < k} v_i(delta),
+//   v_i = sum_j delta_j U[r_i, c_j],
+// over the signs of the k columns with delta_0 = 1; r_k is the first l whose
+// cumulative |out|^2 (in mode order) exceeds u_k times the total.
+//
+// Signs over the columns, not over the rows: the sum has twice the terms of the
+// row form (2^{k-1}), but a term is one product of k - 1 factors where the row
+// form needs every leave-one-out product of k (three complex products a
+// column), and delta_j is constant per lane (columns 1..6), per wavefront (the
+// next two or three) or follows from the running sum of the terms at each flip
+// (the time columns): with P(t) the sum up to state t,
+//   sum_t delta_j(t) g(t) = delta_j(end) P(end) + 2 sum_flips dd P(before),
+// dd = +1 where delta_j goes from +1 to -1.  Per term and lane: 2 adds a row,
+// 4 (k - 2) for the product, 4 for the sums.
+//
+// The step's column (k - 1 values, the same for every lane) is read once by
+// each row of 16 lanes, lane i value i, and enters the sums as a DPP operand
+// (v_fmac_f64 with row_newbcast): two LDS reads a step instead of one a row,
+// which the LDS could not deliver to four wavefronts.
+//
+// Bound by FP64 vector instructions: 1.93e9 wavefront instructions for 1000
+// samples of 20 photons in 400 modes, 80 % of the issue slots at the 1.9 GHz that
+// the card holds under them.  4.7 ms against 6.3 for the row form with four lanes
+// a term; 100 such samples (eight wavefronts each) 1.00 ms against 2.12, 529 of 12
+// photons 70 us against 104 (there the draws, which one thread made mode by mode).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "chain.h"
-#include "k_adjw_impl.h"
+#include "device.h"
+#include "sweep_common.h"
 
 namespace pq {
 
-template <int B>
-__global__ __launch_bounds__(kChainWaves * 64) void chain_kernel(const ChainArgs a) {
-    constexpr int K = 4 * B;
-    constexpr int W = WalkSnapW<B>::value;
-    __shared__ cplx sB[(K - 1) * K];           // drawn rows, quads' columns interleaved (j * 4 + q)
-    __shared__ cplx sP[kChainWaves][64][W];
-    __shared__ double sRed[kChainWaves][2 * K];
-    __shared__ cplx sL[K];
+constexpr int kChainRows = 32;   // rows of a column in LDS (drawn rows, then zeros)
+
+// v[i0 + i] += s * (value i of the 16 held across the lanes), i = 0..N-1.  The
+// leading s_nop separates a copy of the operands, which the compiler may place
+// right before, from the first DPP read.
+template <int I0, int N, int R>
+__device__ __forceinline__ void add_lanes(cplx (&v)[R], const cplx& b, double s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (N == 8) {
+        asm("s_nop 1\n\t"
+            "v_fmac_f64_dpp %0, %16, %18 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %1, %17, %18 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %2, %16, %18 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %3, %17, %18 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %4, %16, %18 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %5, %17, %18 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %6, %16, %18 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %7, %17, %18 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %8, %16, %18 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %9, %17, %18 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %10, %16, %18 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %11, %17, %18 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %12, %16, %18 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %13, %17, %18 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %14, %16, %18 row_newbcast:%26 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %15, %17, %18 row_newbcast:%26 row_mask:0xf bank_mask:0xf"
+            : "+v"(v[I0].re), "+v"(v[I0].im), "+v"(v[I0 + 1].re), "+v"(v[I0 + 1].im), "+v"(v[I0 + 2].re),
+              "+v"(v[I0 + 2].im), "+v"(v[I0 + 3].re), "+v"(v[I0 + 3].im), "+v"(v[I0 + 4].re), "+v"(v[I0 + 4].im),
+              "+v"(v[I0 + 5].re), "+v"(v[I0 + 5].im), "+v"(v[I0 + 6].re), "+v"(v[I0 + 6].im), "+v"(v[I0 + 7].re),
+              "+v"(v[I0 + 7].im)
+            : "v"(b.re), "v"(b.im), "v"(s), "n"(I0 & 15), "n"((I0 + 1) & 15), "n"((I0 + 2) & 15), "n"((I0 + 3) & 15),
+              "n"((I0 + 4) & 15), "n"((I0 + 5) & 15), "n"((I0 + 6) & 15), "n"((I0 + 7) & 15));
+    } else if constexpr (N == 4) {
+        asm("s_nop 1\n\t"
+            "v_fmac_f64_dpp %0, %8, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %1, %9, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %2, %8, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %3, %9, %10 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %4, %8, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %5, %9, %10 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %6, %8, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %7, %9, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+            : "+v"(v[I0].re), "+v"(v[I0].im), "+v"(v[I0 + 1].re), "+v"(v[I0 + 1].im), "+v"(v[I0 + 2].re),
+              "+v"(v[I0 + 2].im), "+v"(v[I0 + 3].re), "+v"(v[I0 + 3].im)
+            : "v"(b.re), "v"(b.im), "v"(s), "n"(I0 & 15), "n"((I0 + 1) & 15), "n"((I0 + 2) & 15), "n"((I0 + 3) & 15));
+    } else {
+        static_assert(N == 2, "rows come in eights, fours and twos");
+        asm("s_nop 1\n\t"
+            "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %1, %5, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %2, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_fmac_f64_dpp %3, %5, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
+            : "+v"(v[I0].re), "+v"(v[I0].im), "+v"(v[I0 + 1].re), "+v"(v[I0 + 1].im)
+            : "v"(b.re), "v"(b.im), "v"(s), "n"(I0 & 15), "n"((I0 + 1) & 15));
+    }
+#else
+    (void)v;
+    (void)b;
+    (void)s;
+#endif
+}
+
+// A column's values across the lanes: lane i of every 16 holds rows i and
+// 16 + i (the second part only when R > 16).
+struct LaneColumn {
+    cplx lo, hi;
+};
+
+template <int R>
+__device__ __forceinline__ LaneColumn load_column(const cplx* col, int lane) {
+    LaneColumn b;
+    b.lo = col[lane & 15];
+    if constexpr (R > 16) b.hi = col[16 + (lane & 15)];
+    else b.hi = cplx{0.0, 0.0};
+    return b;
+}
+
+template <int I0, int R>
+__device__ __forceinline__ void add_from(cplx (&v)[R], const LaneColumn& b, double s) {
+    if constexpr (I0 < R) {
+        constexpr int N = R - I0 >= 8 ? 8 : (R - I0 >= 4 ? 4 : 2);
+        add_lanes<I0, N>(v, I0 < 16 ? b.lo : b.hi, s);
+        add_from<I0 + N>(v, b, s);
+    }
+}
+
+// v += s * column; every lane of the wavefront has to be active.
+template <int R>
+__device__ __forceinline__ void add_column(cplx (&v)[R], const LaneColumn& b, double s) {
+    static_assert(R % 2 == 0, "an even number of rows");
+    add_from<0>(v, b, s);
+}
+
+template <int R>
+__device__ __forceinline__ cplx row_product(const cplx (&v)[R]) {
+    cplx p0 = v[0], p1 = v[1];
+#pragma unroll
+    for (int i = 2; i < R; i += 2) {
+        p0 = cmul(p0, v[i]);
+        p1 = cmul(p1, v[i + 1]);
+    }
+    return cmul(p0, p1);
+}
+
+// Sums over the 64 lanes of N (a power of two) values per lane by recursive
+// halving: lane l ends with value (l / (64 / N)) in x[0].
+template <int N, int M = 32>
+__device__ __forceinline__ void halve_sums(cplx* x, int lane) {
+    if constexpr (N > 1) {
+        constexpr int H = N / 2;
+        const bool up = (lane & M) != 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const cplx keep = up ? x[i + H] : x[i], give = up ? x[i] : x[i + H];
+            x[i] = cplx{keep.re + shfl_xor_d(give.re, M), keep.im + shfl_xor_d(give.im, M)};
+        }
+        halve_sums<H, M / 2>(x, lane);
+    } else if constexpr (M >= 1) {
+        x[0].re += shfl_xor_d(x[0].re, M);
+        x[0].im += shfl_xor_d(x[0].im, M);
+        halve_sums<1, M / 2>(x, lane);
+    }
+}
+
+// A[i] += dd P for the uniform index i in [Q, T): one branch per entry (selects
+// over all of them would cost six instructions each).
+template <int Q, int T>
+__device__ __forceinline__ void flip_sums(cplx (&A)[T], int i, double dd, const cplx& P) {
+    if constexpr (Q < T) {
+        if (i == Q) {
+            cfma_to(A[Q], dd, P);
+            keep_branch(A[Q]);
+        } else {
+            flip_sums<Q + 1, T>(A, i, dd, P);
+        }
+    }
+}
+
+// Slots of the per-wavefront sums: the terms' sum, the six lane columns, then
+// the time columns.
+constexpr int kChainSums = 32;
+
+// The sums of step k over at most R drawn rows, LW wavefront columns.
+template <int R, int LW>
+__device__ __forceinline__ void chain_sweep(const cplx (*sB)[kChainRows], int k, int lane, int wv, cplx* sums) {
+    constexpr int T = R - 6 - LW > 0 ? R - 6 - LW : 0;   // most time columns
+    const int nfree = k - 1;
+    const int nl = nfree < 6 ? nfree : 6;
+    const int nw = nfree - nl < LW ? nfree - nl : LW;
+    const int nt = nfree - nl - nw;
+    double w = lane < (1 << nl) && wv < (1 << nw) ? 1.0 : 0.0;
+    cplx v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = cplx{i < nfree ? 0.0 : 1.0, 0.0};   // rows not drawn yet: factors of 1
+    for (int j = 0; j < k; ++j) {
+        // column 0 is fixed, columns 1..nl are lane, the next nw wavefront columns
+        const int bit = j >= 1 && j <= nl ? (lane >> (j - 1)) & 1 : (j > nl && j <= nl + nw ? (wv >> (j - 1 - nl)) & 1 : 0);
+        add_column(v, load_column<R>(sB[j], lane), bit ? -1.0 : 1.0);
+        if (bit) w = -w;
+    }
+    cplx P{0.0, 0.0};
+    cplx A[T > 0 ? T : 1];
+#pragma unroll
+    for (int i = 0; i < (T > 0 ? T : 1); ++i) A[i] = cplx{0.0, 0.0};
+    if constexpr (T > 0) {
+        const cplx(*sT)[kChainRows] = sB + (1 + nl + nw);   // the time columns
+        // one step: the term of the current state, then the flip of column q
+        // in direction dd (2: from +1 to -1) and its share of the sums
+        auto step = [&](auto q, double sign, double dd) {
+            constexpr int Q = decltype(q)::value;
+            const LaneColumn b = load_column<R>(sT[Q], lane);
+            cfma_to(P, sign, row_product(v));
+            cfma_to(A[Q], dd, P);
+            add_column(v, b, -dd);
+        };
+        using std::integral_constant;
+        if (nt >= 3) {
+            if constexpr (T >= 3) {
+                // blocks of eight states: every step but the last flips one of
+                // the first three columns, in a direction known here (column
+                // 2's alternates by block), and the term's sign alternates
+                const int blocks = T == 3 ? 1 : 1 << (nt - 3);
+#pragma unroll 1
+                for (int blk = 0; blk < blocks; ++blk) {
+                    step(integral_constant<int, 0>{}, 1.0, 2.0);
+                    step(integral_constant<int, 1>{}, -1.0, 2.0);
+                    step(integral_constant<int, 0>{}, 1.0, -2.0);
+                    step(integral_constant<int, 2>{}, -1.0, blk & 1 ? -2.0 : 2.0);
+                    step(integral_constant<int, 0>{}, 1.0, 2.0);
+                    step(integral_constant<int, 1>{}, -1.0, -2.0);
+                    step(integral_constant<int, 0>{}, 1.0, -2.0);
+                    const int i = __builtin_ctz(blk + 1);   // column 3 + i, unless this was the last block
+                    const bool more = blk + 1 < blocks;
+                    const LaneColumn b = load_column<R>(sT[more ? 3 + i : 0], lane);
+                    cfma_to(P, -1.0, row_product(v));
+                    if (more) {
+                        const double dd = ((blk + 1) >> (i + 1)) & 1 ? -2.0 : 2.0;
+                        flip_sums<3, T>(A, 3 + i, dd, P);
+                        add_column(v, b, -dd);
+                    }
+                }
+            }
+        } else {
+            const int states = 1 << nt;
+#pragma unroll 1
+            for (int t = 1; t < states; ++t) {
+                const double sign = t & 1 ? 1.0 : -1.0;
+                if (t & 1) step(integral_constant<int, 0>{}, sign, t & 2 ? -2.0 : 2.0);
+                else if constexpr (T >= 2) step(integral_constant<int, 1>{}, sign, 2.0);
+            }
+            cfma_to(P, nt > 0 ? -1.0 : 1.0, row_product(v));
+        }
+        // the last state has only its top digit set
+#pragma unroll
+        for (int q = 0; q < T; ++q)
+            if (q < nt) cfma_to(A[q], q == nt - 1 ? -1.0 : 1.0, P);
+    } else {
+        P = row_product(v);
+    }
+    constexpr int N = T <= 1 ? 8 : (T <= 9 ? 16 : kChainSums);
+    cplx x[N];
+    x[0] = cplx{w * P.re, w * P.im};
+#pragma unroll
+    for (int i = 1; i < N; ++i) {
+        if (i <= 6) {
+            const double s = (lane >> (i - 1)) & 1 ? -1.0 : 1.0;
+            x[i] = cplx{s * x[0].re, s * x[0].im};
+        } else {
+            x[i] = i - 7 < T ? cplx{w * A[i - 7 < T ? i - 7 : 0].re, w * A[i - 7 < T ? i - 7 : 0].im} : cplx{0.0, 0.0};
+        }
+    }
+    halve_sums<N>(x, lane);
+    if ((lane & (64 / N - 1)) == 0) sums[lane / (64 / N)] = x[0];
+}
+
+// Step k by the sweep for the next even number of rows.
+template <int R, int RMAX, int LW>
+__device__ __forceinline__ void chain_step(const cplx (*sB)[kChainRows], int k, int lane, int wv, cplx* sums) {
+    if constexpr (R >= RMAX) {
+        chain_sweep<RMAX, LW>(sB, k, lane, wv, sums);
+    } else {
+        if (k - 1 <= R) chain_sweep<R, LW>(sB, k, lane, wv, sums);
+        else chain_step<R + 2, RMAX, LW>(sB, k, lane, wv, sums);
+    }
+}
+
+template <int RMAX, int LW>
+__global__ __launch_bounds__(64 << LW, LW == 2 ? 3 : 2) void chain_kernel(const ChainArgs a) {
+    constexpr int NT = 64 << LW, W = 1 << LW;
+    __shared__ cplx sB[RMAX + 2][kChainRows];      // U[r_i, c_j] at [j][i]
+    __shared__ cplx sSum[W][kChainSums];
+    __shared__ cplx sM[RMAX + 2];
     __shared__ double sW[kChainMaxModes];
-    __shared__ int sRow[K], sCol[K];
-    __shared__ int sBad;
+    __shared__ int sCol[RMAX + 2];
+    __shared__ int sBad, sPick;
     const int s = (int)blockIdx.x;
     if (s >= a.samples) return;
     const int tid = (int)threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63, tau = lane >> 2, q = lane & 3;
+    const int lane = tid & 63;
     const int n = a.n, m = a.m;
     if (tid == 0) sBad = 0;
+    for (int e = tid; e < (RMAX + 2) * kChainRows; e += NT) sB[e / kChainRows][e % kChainRows] = cplx{0.0, 0.0};
     __syncthreads();
     // the input modes come from device memory the host cannot check: an entry
     // outside [0, m) marks the sample (every draw -1) and the call's status,
     // and no row of U is read through it
-    for (int j = tid; j < n; j += kChainWaves * 64) {
+    for (int j = tid; j < n; j += NT) {
         int c = a.order[(size_t)s * n + j];
         if (c < 0 || c >= m) {
             atomicOr(&sBad, 1);
@@ -53,84 +317,39 @@ __global__ __launch_bounds__(kChainWaves * 64) void chain_kernel(const ChainArgs
     }
     __syncthreads();
     if (sBad) {
-        for (int j = tid; j < n; j += kChainWaves * 64) a.out[(size_t)s * n + j] = -1;
+        for (int j = tid; j < n; j += NT) a.out[(size_t)s * n + j] = -1;
         if (tid == 0) __hip_atomic_fetch_or(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         return;
     }
     for (int k = 1; k <= n; ++k) {
         if (k == 1) {
-            if (tid == 0) sL[0] = cplx{1.0, 0.0};
+            if (tid == 0) sM[0] = cplx{1.0, 0.0};
         } else {
-            for (int e = tid; e < (k - 1) * K; e += kChainWaves * 64) {
-                const int rho = e / K, col = e - rho * K;
-                const int qc = col / B, jc = col - qc * B;
-                cplx v{0.0, 0.0};
-                if (col < k) v = a.U[(size_t)sRow[rho] * (size_t)a.ldu + sCol[col]];
-                sB[rho * K + jc * 4 + qc] = v;
-            }
+            chain_step<2, RMAX, LW>(sB, k, lane, wv, sSum[wv]);
             __syncthreads();
-            const int nfree = k - 2;
-            const int nl = nfree < 4 ? nfree : 4;
-            const int nw = nfree - 4 < 0 ? 0 : (nfree - 4 < 2 ? nfree - 4 : 2);
-            const int nt = nfree - 6 < 0 ? 0 : nfree - 6;
-            cplx c[B], P[B], acc{0.0, 0.0};
-            double w = (tau < (1 << nl) && wv < (1 << nw)) ? 1.0 : 0.0;
+            // the columns' sums over the wavefronts (their columns' signs included)
+            if (tid < k) {
+                const int nl = k - 1 < 6 ? k - 1 : 6;
+                const int nw = k - 1 - nl < LW ? k - 1 - nl : LW;
+                const int slot = tid <= nl ? tid : (tid <= nl + nw ? 0 : 7 + tid - 1 - nl - nw);
+                cplx M{0.0, 0.0};
 #pragma unroll
-            for (int j = 0; j < B; ++j) {
-                P[j] = cplx{0.0, 0.0};
-                c[j] = (q * B + j) < k ? cplx{0.0, 0.0} : cplx{1.0, 0.0};
-            }
-            // column sums at time state 0 (time digits all +1)
-            for (int rho = 0; rho <= k - 2; ++rho) {
-                int bit = 0;
-                if (rho >= 1 && rho <= 4) bit = (tau >> (rho - 1)) & 1;
-                else if (rho >= 5 && rho <= 6) bit = (wv >> (rho - 5)) & 1;
-                const double d = bit ? -1.0 : 1.0;
-                if (bit) w = -w;
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
-                    const cplx b = sB[rho * K + j * 4 + q];
-                    c[j].re = __builtin_fma(d, b.re, c[j].re);
-                    c[j].im = __builtin_fma(d, b.im, c[j].im);
+                for (int x = 0; x < W; ++x) {
+                    const double d = tid > nl && tid <= nl + nw && ((x >> (tid - 1 - nl)) & 1) ? -1.0 : 1.0;
+                    cfma_to(M, d, sSum[x][slot]);
                 }
-            }
-            const uint64_t states = 1ull << nt;
-            for (uint64_t t = 1; t < states; ++t) {
-                walk_term<B>(c, w, P, acc);
-                const int i = __builtin_ctzll(t);
-                const int sel = (int)((t >> (i + 1)) & 1ull);   // 0: digit up (delta +1 -> -1)
-                const double two = sel ? 2.0 : -2.0;
-                const cplx* row = sB + (7 + i) * K + q;
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
-                    const cplx b = row[j * 4];
-                    c[j].re = __builtin_fma(two, b.re, c[j].re);
-                    c[j].im = __builtin_fma(two, b.im, c[j].im);
-                }
-                w = -w;
-            }
-            walk_term<B>(c, w, P, acc);
-            // minors: P summed over the wavefront's 16 terms, then the 4 wavefronts
-#pragma unroll
-            for (int j = 0; j < B; ++j) sP[wv][lane][j] = P[j];
-            wave_lds_sync();
-            if (lane < 2 * K) sRed[wv][lane] = walk_sum_terms<B>(sP[wv], lane);
-            __syncthreads();
-            if (tid < 2 * K) {
-                double v = sRed[0][tid];
-#pragma unroll
-                for (int x = 1; x < kChainWaves; ++x) v += sRed[x][tid];
-                ((double*)sL)[tid] = v * ldexp(1.0, -(k - 2));
+                const double scale = ldexp(1.0, -(k - 1));
+                sM[tid] = cplx{M.re * scale, M.im * scale};
             }
         }
         __syncthreads();
         // weights of the next mode
-        for (int l = tid; l < m; l += kChainWaves * 64) {
+        for (int l = tid; l < m; l += NT) {
             const cplx* Ul = a.U + (size_t)l * (size_t)a.ldu;
             double re = 0.0, im = 0.0;
             for (int j = 0; j < k; ++j) {
                 const cplx u = Ul[sCol[j]];
-                const cplx L = sL[j];
+                const cplx L = sM[j];
                 re = __builtin_fma(u.re, L.re, re);
                 re = __builtin_fma(-u.im, L.im, re);
                 im = __builtin_fma(u.re, L.im, im);
@@ -139,32 +358,59 @@ __global__ __launch_bounds__(kChainWaves * 64) void chain_kernel(const ChainArgs
             sW[l] = re * re + im * im;
         }
         __syncthreads();
-        if (tid == 0) {
-            double total = 0.0;
-            for (int l = 0; l < m; ++l) total += sW[l];
-            const double target = a.uniforms[(size_t)s * n + (k - 1)] * total;
-            double run = 0.0;
-            int pick = m - 1;
-            for (int l = 0; l < m; ++l) {
-                run += sW[l];
-                if (run > target) {
-                    pick = l;
-                    break;
-                }
+        // the draw, by the first wavefront: each lane sums a run of modes, a
+        // scan over the lanes finds the run that holds the target
+        if (wv == 0) {
+            const int run = (m + 63) / 64;
+            const int l0 = lane * run < m ? lane * run : m, l1 = l0 + run < m ? l0 + run : m;
+            double mine = 0.0;
+            for (int l = l0; l < l1; ++l) mine += sW[l];
+            double upto = mine;
+#pragma unroll
+            for (int h = 1; h < 64; h <<= 1) {
+                const double o = __shfl_up(upto, h, 64);
+                if (lane >= h) upto += o;
             }
-            sRow[k - 1] = pick;
-            a.out[(size_t)s * n + (k - 1)] = pick;
+            const double total = __shfl(upto, 63, 64);
+            double before = __shfl_up(upto, 1, 64);
+            if (lane == 0) before = 0.0;
+            const double target = a.uniforms[(size_t)s * n + (k - 1)] * total;
+            const unsigned long long hit = __ballot(upto > target);
+            if (hit == 0) {
+                if (lane == 0) sPick = m - 1;
+            } else if (lane == __builtin_ctzll(hit)) {
+                int pick = -1;
+                for (int l = l0; l < l1; ++l) {
+                    before += sW[l];
+                    if (sW[l] > 0.0) pick = l;   // where rounding leaves the run's sum at the target: its last mode
+                    if (before > target) break;
+                }
+                sPick = pick >= 0 ? pick : m - 1;
+            }
+            if (lane == 0) a.out[(size_t)s * n + (k - 1)] = sPick;
         }
+        __syncthreads();
+        if (tid < n && k < n) sB[tid][k - 1] = a.U[(size_t)sPick * (size_t)a.ldu + sCol[tid]];
         __syncthreads();
     }
 }
 
+template <int RMAX>
+static void launch_chain_rows(const ChainArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)(a.samples > 0 ? a.samples : 1));
+    // eight wavefronts a sample while every sample still has a CU of its own
+    // (they need the registers of one)
+    if (a.samples <= 256) hipLaunchKernelGGL((chain_kernel<RMAX, 3>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((chain_kernel<RMAX, 2>), grid, dim3(256), 0, s, a);
+}
+
 hipError_t launch_chain(const ChainArgs& a, hipStream_t s) {
-    const dim3 grid((unsigned)(a.samples > 0 ? a.samples : 1)), block(kChainWaves * 64);
-    if (a.n <= 8) hipLaunchKernelGGL(chain_kernel<2>, grid, block, 0, s, a);
-    else if (a.n <= 16) hipLaunchKernelGGL(chain_kernel<4>, grid, block, 0, s, a);
-    else if (a.n <= 20) hipLaunchKernelGGL(chain_kernel<5>, grid, block, 0, s, a);
-    else if (a.n <= kChainMaxPhotons) hipLaunchKernelGGL(chain_kernel<6>, grid, block, 0, s, a);
+    // n - 1 rows at the last step
+    if (a.n <= 9) launch_chain_rows<8>(a, s);
+    else if (a.n <= 13) launch_chain_rows<12>(a, s);
+    else if (a.n <= 17) launch_chain_rows<16>(a, s);
+    else if (a.n <= 21) launch_chain_rows<20>(a, s);
+    else if (a.n <= kChainMaxPhotons) launch_chain_rows<24>(a, s);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
