@@ -26,7 +26,7 @@ struct BJob {
     int32_t slot_base;    // first partial slot of this job (slots are consecutive)
     int32_t tab;          // table index (mixed digits), -1 when binary
     int32_t m_out;        // EXTEND: number of output modes
-    int32_t pad0;
+    int32_t ext_cols;     // EXTEND: 1 when the sweep runs over the columns' signs (kModeExtCol)
     int64_t mat_off;      // complex offset of B [r][ncmax] | rows2 [r][2][ncmax] | base [ncmax]
     int64_t idx_off;      // int32 offset of row_mode[r], row_mu[r], col_mode[nc], col_mult[nc]
     int64_t out_offset;

@@ -66,24 +66,34 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
         // (otherwise the derivative part of the slots is reduced by the two
         // dred stages)
     } else {
-        // Laplace expansion: L_j from the chunk sums, then out[l] = sum_j U[l, C_j] L_j
-        for (int j = t; j < J.nc; j += 64) {
-            cdd s{{base[4 * j], base[4 * j + 1]}, {base[4 * j + 2], base[4 * j + 3]}};
-            for (int k = 1; k < J.nchunks; ++k) {
-                const double* q = base + (size_t)k * sd + 4 * j;
+        // Laplace expansion: L_j from the chunk sums, then out[l] = sum_j U[l, C_j] L_j;
+        // a sweep over the columns' signs has the columns on its iterated side
+        const int ncol = J.ext_cols ? J.r : J.nc;
+        // lane (g, j) adds slots g, g + G, ... of column j in order; the G groups
+        // of a column are then added in order
+        const int G = 64 / ncol, g = t / ncol, jj = t - g * ncol;
+        cdd s{{0.0, 0.0}, {0.0, 0.0}};
+        if (g < G)
+            for (int k = g; k < J.nchunks; k += G) {
+                const double* q = base + (size_t)k * sd + 4 * jj;
                 s = cdd_add(s, cdd{{q[0], q[1]}, {q[2], q[3]}});
             }
-            L[j] = cplx{(s.re.hi + s.re.lo) * J.scale, (s.im.hi + s.im.lo) * J.scale};
+        for (int h = 1; h < G; ++h) {
+            const int from = h * ncol + jj;
+            const cdd o{{__shfl(s.re.hi, from, 64), __shfl(s.re.lo, from, 64)},
+                        {__shfl(s.im.hi, from, 64), __shfl(s.im.lo, from, 64)}};
+            if (g == 0) s = cdd_add(s, o);
         }
+        if (t < ncol) L[t] = cplx{(s.re.hi + s.re.lo) * J.scale, (s.im.hi + s.im.lo) * J.scale};
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int32_t* cmode = a.idx + J.idx_off + 2 * J.r;
+        const int32_t* cmode = a.idx + J.idx_off + (J.ext_cols ? 0 : 2 * J.r);
         for (int l = t; l < J.m_out; l += 64) {
             const cplx* Ul = a.U + (size_t)l * (size_t)a.ldu;
             double re = 0.0, im = 0.0;
-            for (int j = 0; j < J.nc; ++j) {
-                const cplx u = Ul[cmode[j]];
+            for (int j = 0; j < ncol; ++j) {
+                const cplx u = a.UT ? a.UT[(size_t)cmode[j] * (size_t)a.m + l] : Ul[cmode[j]];
                 re = __builtin_fma(u.re, L[j].re, re);
                 re = __builtin_fma(-u.im, L[j].im, re);
                 im = __builtin_fma(u.re, L[j].im, im);
@@ -145,6 +155,22 @@ hipError_t launch_dred(int stage, const DRedArgs& a, int nitems, hipStream_t s) 
     if (nitems <= 0) return hipSuccess;
     if (stage == 1) hipLaunchKernelGGL(dred1_kernel, dim3(nitems), dim3(64), 0, s, a);
     else hipLaunchKernelGGL(dred2_kernel, dim3(nitems), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void transpose_kernel(const TransposeArgs a) {
+    __shared__ cplx tile[16][17];
+    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+    const int r = blockIdx.y * 16 + y, c = blockIdx.x * 16 + x;
+    if (r < a.m && c < a.m) tile[y][x] = a.U[(size_t)r * (size_t)a.ldu + c];
+    __syncthreads();
+    const int tr = blockIdx.x * 16 + y, tc = blockIdx.y * 16 + x;
+    if (tr < a.m && tc < a.m) a.UT[(size_t)tr * (size_t)a.m + tc] = tile[x][y];
+}
+
+hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s) {
+    const unsigned n = (unsigned)((a.m + 15) / 16);
+    hipLaunchKernelGGL(transpose_kernel, dim3(n, n), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -230,6 +256,14 @@ static const mlaunch_fn g_m_ext[] = {PQ_MCLASS_EXT(PQ_MPTR)};
 static const mlaunch_fn g_m_adj[] = {PQ_MCLASS_ADJ(PQ_MPTR)};
 
 hipError_t launch_many(int mode, int ncmax, int var, const ManyArgs& a, hipStream_t s) {
+    if (mode == kModeExtCol) {
+        switch (ncmax) {
+#define PQ_XCASE(NC) case NC: return launch_extcol_##NC(var, a, s);
+            PQ_XCLASS(PQ_XCASE)
+#undef PQ_XCASE
+            default: return hipErrorInvalidValue;
+        }
+    }
     const int k = ncmax / 4 - 1;
     if (ncmax % 4 || k < 0) return hipErrorInvalidValue;
     if (mode == 0 && k < (int)(sizeof(g_m_fwd) / sizeof(g_m_fwd[0]))) return g_m_fwd[k](var, a, s);

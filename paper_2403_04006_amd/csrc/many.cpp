@@ -31,6 +31,16 @@ namespace {
 constexpr uint64_t kWalkMinChunk = 32;
 // shortest walk once a class is cut into more than one round of walks
 constexpr uint64_t kWalkSplitStates = 4096;
+// Chunks of a class that does not fill the device: as many as this per CU,
+// each at least so many time states (forward, extend-row, and as a power of two
+// extend-row over the columns' signs).  With the policy's 256 states a small job
+// list ran on a few wavefronts: 256 patterns of 16 photons 95 -> 49 us, 36
+// sampling runs of 16 photons 350 -> 192, 19 of 19 454 -> 236; 8, 16 and 32 states
+// gave 49, 54 and 67 us on the first and 267, 236 and 240 on the last.
+constexpr uint64_t kSpreadWaves = 12;
+constexpr uint64_t kSpreadChunk = 8;
+constexpr uint64_t kSpreadExtChunk = 32;
+constexpr int kExtColMinDigits = 5;
 // chunk policies the autotuner times (the first is the default)
 constexpr ChunkPolicy kTuneCandidates[] = {
     {64, 8, 256}, {16, 4, 64}, {4, 2, 64}, {8, 1, 64}, {8, 2, 64}, {8, 4, 64}, {16, 2, 64},
@@ -43,6 +53,9 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
 // Cached plans: four whatever their size, more while their device blocks
 // stay within kMaxManyBytes together, kMaxManyEntries at most (a training loop
 // holds a forward and a reverse plan for each of its pattern sets).
+// From this many extend-row jobs on, their final step reads U transposed (one
+// launch more; 19,000 jobs on 400 modes: 230 us of final step before).
+constexpr int kTransposeMinJobs = 512;
 constexpr int kMinManyEntries = 4;
 constexpr int kMaxManyEntries = 16;
 constexpr size_t kMaxManyBytes = (size_t)1 << 30;
@@ -75,6 +88,7 @@ struct ManyEntry {
     int max_chunks = 0;          // most chunks of any pattern (1: nothing for a work queue to balance)
     int queue_pref = -1;         // the autotuner's schedule for pq_perm_batched (1 queue, 0 static, -1 none)
     size_t mat_elems = 0, partial_doubles = 0, dpat_elems = 0;
+    cplx* d_ut = nullptr;        // U transposed (kTransposeMinJobs)
     std::vector<ManyClass> classes;
     ChunkPolicy policy;
     // device
@@ -181,6 +195,32 @@ uint64_t hash_pattern(const PatRef& p) {
     return h ^ (h >> 32);
 }
 
+// Photons up to which every EXTEND_ROW job with unit columns takes the sweep over
+// the columns' signs, in one kernel variant per four rows: 100 runs of 10 photons
+// 78 -> 47 us (91 us in a class for every two rows and either variant).
+constexpr int kExtColSmall = 12;
+
+// Plan of an EXTEND_ROW job over its columns' signs (k_extcol_impl.h), or false
+// where its row plan p is the better one: columns of multiplicity 1 only, and
+// fewer FP64 instructions by the count of either sweep's term (rows r with
+// repeats, columns k): 2^(k-1) (6 r + 4 rises + 4) against 16 k a row term.
+bool ext_over_columns(const Side& rows, const Side& cols, const Plan& p, Plan& pc) {
+    if (rows.count < 1 || p.nc < 2) return false;
+    for (int j = 0; j < cols.count; ++j)
+        if (cols.mult[j] != 1) return false;
+    plan_sparse(rows, cols, false, pc, 2);
+    if (pc.status || pc.trivial) return false;
+    PowSteps ps;
+    make_pow_steps(pc.col_kap, pc.nc, ps);
+    if (ps.general) return false;
+    const int rises = pc.col_kap[pc.nc - 1] - 1;
+    if (rises > 0 && pc.nc > kExtColMaxPowers) return false;
+    if (pc.n <= kExtColSmall) return true;   // three classes whatever the collisions (a launch costs more than they save)
+    const double by_cols = (double)pc.terms * (6.0 * pc.nc + 4.0 * (rises > 0 ? rises + 1 : 0) + 4.0);
+    const double by_rows = (double)p.terms * 16.0 * p.nc;
+    return by_cols < by_rows;
+}
+
 int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all, ManyEntry& E,
                hipStream_t st, const ChunkPolicy& pol) {
     E.mode = mode;
@@ -244,7 +284,17 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
             trivial[k] = p.trivial == 1 ? cplx{0.0, 0.0} : cplx{1.0, 0.0};
             continue;
         }
-        const int ncmax = ((p.nc + 3) / 4) * 4;
+        int ncmax = ((p.nc + 3) / 4) * 4;
+        if (ext && ncmax > kMaxExtendCols) return ctx->fail(PQ_ERANGE, "pattern %zu: more than %d columns", k, kMaxExtendCols);
+        bool extcol = false;
+        if (ext) {
+            Plan pc;
+            if (ext_over_columns(rows, cols, p, pc)) {
+                p = pc;
+                extcol = true;
+                ncmax = p.n <= kExtColSmall ? ((p.nc + 3) / 4) * 4 : ((p.nc + 1) / 2) * 2;
+            }
+        }
         // wide collision-free patterns take the walk kernel (four lanes per term)
         bool walk = false;
         if (adj && p.binary && ncmax >= kWalkMinCols && ncmax <= kWalkMaxCols) {
@@ -258,7 +308,6 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
                 walk = true;
             }
         }
-        if (ext && ncmax > kMaxExtendCols) return ctx->fail(PQ_ERANGE, "pattern %zu: more than %d columns", k, kMaxExtendCols);
         if (adj && !walk && ncmax > kManyMaxAdjCols)
             return ctx->fail(PQ_ERANGE, "pattern %zu: more than %d columns needs every mode at most once", k,
                              kManyMaxAdjCols);
@@ -271,6 +320,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         b.n_inner = p.n_inner;
         b.m_inner = p.m_inner;
         b.m_out = ext ? m : 0;
+        b.ext_cols = extcol ? 1 : 0;
         b.transposed = p.transposed;
         b.time_states = p.time_states;
         b.scale = p.r == 0 ? 1.0 : p.scale;
@@ -294,7 +344,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
             b.n_inner = ka;
             b.m_inner = mi;
         }
-        if (!bin) {
+        if (!bin) {   // (never a sweep over the columns' signs)
             std::vector<int32_t> sg(kSigInts, 0);
             sg[0] = b.n_inner;
             sg[1] = b.m_inner;
@@ -320,12 +370,12 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
             dpat_off[k] = (int64_t)dpat_elems;
             dpat_elems += (size_t)p.r * p.nc;
         }
-        const int kmode = adj ? (walk ? kModeAdjWalk : kModeAdj) : (ext ? kModeExt : kModeFwd);
+        const int kmode = adj ? (walk ? kModeAdjWalk : kModeAdj) : (ext ? (extcol ? kModeExtCol : kModeExt) : kModeFwd);
         // variant: 2 * binary digits + unit powers, + 4 for powers whose steps
         // the grouped product does not cover (forward jobs only)
         // walk classes carry the ctx's walk variant instead
-        const int var = kmode == kModeAdjWalk
-                            ? ctx->walk_variant
+        const int var = kmode == kModeAdjWalk                               ? ctx->walk_variant
+                        : kmode == kModeExtCol && p.n <= kExtColSmall       ? 2
                             : (bin ? 2 : 0) + (unit ? 1 : 0) + (!unit && kmode == kModeFwd && b.pw.general ? 4 : 0);
         by_class[std::make_tuple(kmode, ncmax, var)].push_back((int)k);
     }
@@ -346,12 +396,25 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
             rmax = std::max(rmax, hj[id].r);
             total += hj[id].time_states;
         }
-        C.slot_doubles = C.mode == kModeFwd ? 4 : (C.mode == kModeExt ? 4 * C.ncmax : 4 + 2 * rmax * C.ncmax);
+        C.slot_doubles = C.mode == kModeFwd ? 4
+                         : C.mode == kModeExt ? 4 * C.ncmax
+                         : C.mode == kModeExtCol ? 4 * rmax : 4 + 2 * rmax * C.ncmax;
         uint64_t chunk = 0;
         if (C.mode == kModeFwd || C.mode == kModeExt) {
             const uint64_t target = (uint64_t)ctx->num_cu * (uint64_t)pol.waves_per_cu * (uint64_t)pol.chunks_per_wave;
             chunk = (total + target - 1) / target;
             if (chunk < (uint64_t)pol.min_chunk) chunk = (uint64_t)pol.min_chunk;
+            // a class that would leave the device part empty in such chunks is
+            // spread over it in shorter ones
+            const uint64_t spread = (uint64_t)ctx->num_cu * kSpreadWaves;
+            if (total < chunk * spread) {
+                chunk = std::min(chunk, (total + spread - 1) / spread);
+                chunk = std::max(chunk, C.mode == kModeFwd ? kSpreadChunk : kSpreadExtChunk);
+            }
+        } else if (C.mode == kModeExtCol) {
+            int q = kExtColDigits;
+            while (q > kExtColMinDigits && (total >> q) < (uint64_t)ctx->num_cu * kSpreadWaves) --q;
+            chunk = (uint64_t)1 << q;
         } else if (C.mode == kModeAdjWalk) {
             // whole rounds of the resident wavefronts (every walk costs the
             // same), in whole 8-state blocks: one round, or up to four while
@@ -503,6 +566,9 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     const size_t oDp = cv.take(sizeof(cplx) * sz(dpat_elems));
     const size_t oRp = cv.take(sizeof(cplx) * sz(red_part));
     const size_t oGs = cv.take(sizeof(cplx) * sz(adj ? pats.size() : 0));
+    int next = 0;
+    for (const BJob& b : hj) next += b.m_out > 0;
+    const size_t oUt = cv.take(sizeof(cplx) * sz(next >= kTransposeMinJobs ? (size_t)m * (size_t)m : 0));
     const size_t oQz = cv.take(sizeof(unsigned) * sz(adj ? 0 : E.classes.size()));
     if (int rc = ctx->device_alloc((void**)&E.dmem, cv.off, "many")) return rc;
     E.bytes = cv.off;
@@ -526,6 +592,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     E.d_dup_out = (int64_t*)(E.dmem + oDut);
     E.d_gsum = (cplx*)(E.dmem + oGs);
     E.d_qzero = (unsigned*)(E.dmem + oQz);
+    E.d_ut = next >= kTransposeMinJobs ? (cplx*)(E.dmem + oUt) : nullptr;
     E.d_mat = (cplx*)(E.dmem + oMat);
     E.d_tabs = (StepEntry*)(E.dmem + oTab);
     E.d_partials = (double*)(E.dmem + oPart);
@@ -614,9 +681,16 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
         rc = ctx->check(launch_btable(ta, st), "many tables");
         if (rc) return rc;
     }
+    if (E.d_ut) {
+        TransposeArgs ta{U, ldu, m, E.d_ut};
+        rc = ctx->check(launch_transpose(ta, st), "many transpose");
+        if (rc) return rc;
+    }
     ManyFinalArgs fa;
     fa.U = U;
     fa.ldu = ldu;
+    fa.UT = E.d_ut;
+    fa.m = m;
     fa.idx = E.d_idx;
     fa.dpat_off = E.d_dpat_off;
     fa.jobs = E.d_jobs;

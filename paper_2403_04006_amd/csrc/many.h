@@ -26,6 +26,9 @@ constexpr int kModeFwd = 0;       // forward sums (PERM jobs)
 constexpr int kModeExt = 1;       // Laplace expansion along a new row (EXTEND_ROW jobs)
 constexpr int kModeAdj = 2;       // reverse sweep: derivatives and forward sums
 constexpr int kModeAdjWalk = 3;   // reverse sweep of wide collision-free patterns (k_adjw_impl.h)
+constexpr int kModeExtCol = 4;    // EXTEND_ROW jobs over the signs of unit columns (k_extcol_impl.h)
+constexpr int kExtColDigits = 8;  // most time digits that move inside one of its chunks
+constexpr int kExtColMaxPowers = 20;   // most (padded) rows of theirs when some row repeats
 constexpr int kWalkMinCols = 16;  // padded column range of the walk classes
 constexpr int kWalkMaxCols = 32;
 constexpr int kWalkLaneStates = 16;   // lane-digit states per wavefront (four lanes per term)
@@ -56,6 +59,8 @@ struct ManyArgs {
 struct ManyFinalArgs {
     const cplx* U;
     int64_t ldu;
+    const cplx* UT;            // U transposed, [m][m], or null (extend-row jobs)
+    int32_t m;
     const int32_t* idx;
     const int64_t* dpat_off;   // [npat]: complex offset of the pattern's D block
     const BJob* jobs;
@@ -79,6 +84,16 @@ struct ManyFinalArgs {
     cplx* dpat;                // adjoint: per pattern r x nc complex d perm / d B (scaled)
     const cplx* gperm;         // adjoint: the caller's per-copy cotangents
     cplx* gsum;                // adjoint: per distinct pattern, the sum of its copies' cotangents
+};
+
+// U transposed for the extend-row jobs' final step: its lanes are consecutive
+// output modes, whose entries of one column are a row of the transpose (in U
+// itself every lane reads another line).
+struct TransposeArgs {
+    const cplx* U;
+    int64_t ldu;
+    int32_t m;
+    cplx* UT;
 };
 
 // Persistent work queue over one class's chunks (forward and extend-row

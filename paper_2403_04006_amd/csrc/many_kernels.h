@@ -13,6 +13,9 @@ namespace pq {
 // reverse-sweep walk classes (binary digits, unit powers), padded column counts
 #define PQ_WCLASS(X) X(16) X(20) X(24) X(28) X(32)
 
+// extend-row sweeps over the columns' signs, padded row counts
+#define PQ_XCLASS(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24)
+
 // variant: 2 * binary_walk + unit_powers
 #define PQ_MDECL(MODE, NC) hipError_t launch_many_##MODE##_##NC(int var, const ManyArgs& a, hipStream_t s);
 PQ_MCLASS_FWD(PQ_MDECL)
@@ -24,6 +27,9 @@ PQ_MCLASS_ADJ(PQ_MDECL)
     hipError_t occupancy_adjw_##NC(int variant, int* blocks);
 PQ_WCLASS(PQ_WDECL)
 #undef PQ_WDECL
+#define PQ_XDECL(NC) hipError_t launch_extcol_##NC(int var, const ManyArgs& a, hipStream_t s);
+PQ_XCLASS(PQ_XDECL)
+#undef PQ_XDECL
 
 // work-queue instances (forward and extend-row classes)
 #define PQ_QDECL(MODE, NC)                                                                      \
@@ -43,6 +49,7 @@ hipError_t launch_queue(int mode, int ncmax, int var, const QueueArgs& q, int gr
 // resident workgroups per CU of that class's queue kernel (0 on failure)
 int occupancy_queue(int mode, int ncmax, int var);
 hipError_t launch_queue_prep(const QueuePrepArgs& a, hipStream_t s);
+hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s);
 hipError_t launch_many_final(const ManyFinalArgs& a, hipStream_t s);
 hipError_t launch_dred(int stage, const DRedArgs& a, int nitems, hipStream_t s);
 hipError_t launch_grad_scatter(const GradScatterArgs& a, hipStream_t s);

@@ -66,7 +66,7 @@ static void choose_lane_digits(int nfree, const int* radix, int cap, int* chosen
         if (reach[best] >> i & 1ull) chosen[nchosen++] = i;
 }
 
-void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan& p, bool extend, int max_lane_states) {
+void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan& p, int extend, int max_lane_states) {
     p = Plan();
     int nr = 0, nc_ = 0;
     for (int i = 0; i < rows.count; ++i) nr += rows.mult[i];
@@ -86,14 +86,15 @@ void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan&
         if (nr != nc_) { p.trivial = 1; p.n = nc_; return; }
         if (nr == 0) { p.trivial = 2; return; }
     }
-    p.n = nr;
-    if (p.n > PQ_MAX_N || rows.count > kMaxDim || cols.count > kMaxDim) { p.status = PQ_ERANGE; return; }
+    p.n = extend == 2 ? nc_ : nr;
+    if (nr > PQ_MAX_N || rows.count > kMaxDim || cols.count > kMaxDim) { p.status = PQ_ERANGE; return; }
 
     uint64_t t_rows = 0, t_cols = 0;
     int f_rows = -1, f_cols = -1;
     bool ok_rows = term_count(rows, t_rows, f_rows);
-    bool ok_cols = allow_transpose ? term_count(cols, t_cols, f_cols) : false;
-    bool use_cols = allow_transpose && ok_cols && (!ok_rows || t_cols < t_rows);
+    bool ok_cols = allow_transpose || extend == 2 ? term_count(cols, t_cols, f_cols) : false;
+    bool use_cols = extend == 2 ? ok_cols : allow_transpose && ok_cols && (!ok_rows || t_cols < t_rows);
+    if (extend == 2 && !ok_cols) { p.status = PQ_ERANGE; return; }
     if (!ok_rows && !use_cols) { p.status = PQ_ERANGE; return; }
     const Side& it = use_cols ? cols : rows;
     const Side& pw = use_cols ? rows : cols;

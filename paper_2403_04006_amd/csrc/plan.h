@@ -44,10 +44,11 @@ struct Side {
 // `allow_transpose` = false keeps the rows as the iterated side.  `extend`
 // plans the row sweep of a Laplace expansion along one more row: the column
 // side then holds one photon more than the row side, the rows are always the
-// iterated side, and n is the row count (zero rows is allowed).
+// iterated side, and n is the row count (zero rows is allowed).  `extend` 2
+// iterates the column side instead, whose photons are then n.
 // `max_lane_states` (1..64) bounds the product of the lane digits' radices:
 // 64 when every lane of a wavefront owns one term, 16 when four lanes share one.
-void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan& p, bool extend = false,
+void plan_sparse(const Side& rows, const Side& cols, bool allow_transpose, Plan& p, int extend = 0,
                  int max_lane_states = 64);
 
 // Plan from dense occupation vectors of length m (validates them).
