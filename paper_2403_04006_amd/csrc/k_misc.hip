@@ -127,6 +127,16 @@ typedef int (*occ_fn)(int);
 static const launch_fn g_launch[kMaxDim] = {PQ_NC_LIST(PQ_LAUNCH_PTR)};
 static const occ_fn g_occ[kMaxDim] = {PQ_NC_LIST(PQ_OCC_PTR)};
 
+hipError_t launch_fused(bool mix, const FusedArgs& a, int grid, hipStream_t s) {
+    if (a.nc < 1 || a.r < 1 || a.r > kMaxDim || grid < 1) return hipErrorInvalidValue;
+    switch ((a.nc + 1) / 2 * 2) {
+#define PQ_FCASE(NC) case NC: return launch_fused_##NC(mix, a, grid, s);
+        PQ_FCLASS(PQ_FCASE)
+#undef PQ_FCASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_glynn(int kind, int nc, const GlynnArgs& a, int grid, hipStream_t s) {
     if (nc < 1 || nc > kMaxDim || kind < 0 || kind > 2) return hipErrorInvalidValue;
     return g_launch[nc - 1](kind, a, grid, s);

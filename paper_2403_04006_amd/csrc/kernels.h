@@ -28,6 +28,14 @@ hipError_t launch_glynn(int kind, int nc, const GlynnArgs& a, int grid, hipStrea
 // Resident 256-thread workgroups per compute unit for that kernel (0 on error).
 int occupancy_glynn(int kind, int nc);
 
+// One-launch permanents: columns padded to an even number up to kFusedMaxCols.
+constexpr int kFusedMaxCols = 32;
+#define PQ_FCLASS(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24) X(26) X(28) X(30) X(32)
+#define PQ_FDECL(NC) hipError_t launch_fused_##NC(bool mix, const FusedArgs& a, int grid, hipStream_t s);
+PQ_FCLASS(PQ_FDECL)
+#undef PQ_FDECL
+hipError_t launch_fused(bool mix, const FusedArgs& a, int grid, hipStream_t s);
+
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_table(const TableArgs& a, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);

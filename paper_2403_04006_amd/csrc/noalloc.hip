@@ -22,9 +22,12 @@ constexpr size_t kNoAllocScratchBytes = PQ_NOALLOC_SCRATCH_BYTES;
 constexpr int kNoAllocMaxDevices = 64;
 
 static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
+// the one-launch form's workgroup count, zero between launches
+static __device__ uint32_t scratch_ticket;
 
 static std::mutex g_scratch_mu;
 static char* g_scratch_dev[kNoAllocMaxDevices] = {};
+static uint32_t* g_ticket_dev[kNoAllocMaxDevices] = {};
 
 int noalloc_init(int device) {
     if (device < 0 || device >= kNoAllocMaxDevices) return PQ_EINVAL;
@@ -35,13 +38,20 @@ int noalloc_init(int device) {
         (void)hipGetLastError();
         return PQ_EDEVICE;
     }
+    void* ticket = nullptr;
+    if (hipGetSymbolAddress(&ticket, HIP_SYMBOL(scratch_ticket)) != hipSuccess || !ticket) {
+        (void)hipGetLastError();
+        return PQ_EDEVICE;
+    }
+    g_ticket_dev[device] = (uint32_t*)ticket;
     g_scratch_dev[device] = (char*)ptr;
     return PQ_OK;
 }
 
-static char* scratch_of(int device) {
+static char* scratch_of(int device, uint32_t** ticket) {
     if (device < 0 || device >= kNoAllocMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
+    *ticket = g_ticket_dev[device];
     return g_scratch_dev[device];
 }
 
@@ -66,7 +76,8 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
         if (!perm && !amp) return PQ_OK;
         return ctx->check(launch_fill((cplx*)perm, (cplx*)amp, v, st), "fill");
     }
-    char* ws = scratch_of(ctx->device);
+    uint32_t* ticket = nullptr;
+    char* ws = scratch_of(ctx->device, &ticket);
     if (!ws) return ctx->fail(PQ_EDEVICE, "pq_perm_noalloc: the static scratch of device %d was not resolved", ctx->device);
     // what fits is decided without the spread (its partials can need more
     // scratch), which is then taken where it fits too
@@ -74,6 +85,8 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     if (L.bytes > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
                          "bytes of the static buffer (use pq_perm)", L.bytes, kNoAllocScratchBytes);
+    if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocScratchBytes)
+        return run_fused(ctx, p, (double*)ws, ticket, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
     const SingleLayout spread = single_layout(ctx, p, single_waves_per_cu(ctx, p));
     if (spread.bytes <= kNoAllocScratchBytes) L = spread;
     return run_single_at(ctx, p, L, ws, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);

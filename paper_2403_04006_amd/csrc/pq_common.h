@@ -128,6 +128,28 @@ struct FinalArgs {
     cplx* amp;                   // may be null
 };
 
+// A whole permanent in one launch (k_fused_impl.h).
+struct FusedArgs {
+    const cplx* U;
+    int64_t ldu;
+    cplx* perm;                  // may be null
+    cplx* amp;                   // may be null
+    double scale;                // 2^{-(n-1)}
+    double norm;                 // 1 / sqrt(prod S! prod T!)
+    double* partials;            // [grid][4]
+    uint32_t* ticket;            // zero between launches
+    uint32_t time_states;
+    uint32_t waves;
+    int32_t r, nc;
+    int32_t transposed;          // as in PrepArgs
+    int32_t n_lane, lane_states, n_time;
+    int32_t row_mode[kMaxDim];   // iterated modes in digit order
+    int32_t col_mode[kMaxDim];
+    int8_t row_mu[kMaxDim];
+    int8_t radix[kMaxDim];       // of the lane digits, then the time digits
+    PowSteps pw;                 // of the padded columns
+};
+
 // ---------------------------------------------------------------- Gray code
 // Reflected mixed-radix Gray code, digits least significant first.  With
 // counter digits a_k of the rank, the Gray digit k is a_k when the digits

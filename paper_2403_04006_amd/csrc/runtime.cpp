@@ -183,6 +183,8 @@ void pq_ctx::release_all() {
     if (ws) hipFree(ws);
     ws = nullptr;
     ws_bytes = 0;
+    if (ticket) hipFree(ticket);
+    ticket = nullptr;
 }
 
 int pq_ctx::occupancy(int kind, int nc) {
@@ -200,7 +202,7 @@ namespace pq {
 // sums are rebuilt from the digits, about (digits x NC) multiply-adds).
 static constexpr uint64_t kMinStepsPerWave = 32;
 // and in a sweep that leaves the device part empty at that share, where a
-// wavefront more costs nothing else: 20 photons 30 -> 24 us, 2 x 11 rows 35 -> 25
+// wavefront more costs nothing else: 34 photons in 17 modes 49 -> 45 us
 static constexpr uint64_t kSpreadSteps = 8;
 
 // Sweep kernel kind of a plan (see kernels.h).
@@ -284,6 +286,87 @@ int timed_sweep(pq_ctx* ctx, int kind, int nc, const GlynnArgs& a, int grid, hip
     int rc = ctx->check(launch_glynn(kind, nc, a, grid, st), "sweep");
     if (rc) return rc;
     if (ctx->profiling) {
+        rc = ctx->check(hipEventRecord(e1, st), "profile: record");
+        if (rc) return rc;
+        ctx->ev_used.emplace_back(e0, e1);
+    }
+    return PQ_OK;
+}
+
+// Time states up to which a permanent takes one launch, and its wavefronts'
+// least share of them (two workgroups per CU at most).  Whole calls, several
+// launches -> one: 8 photons 19.2 -> 13.3 us, 16 20.9 -> 15.2, 20 24.0 -> 16.5, 22
+// 33.4 -> 25.0, 24 (2^17 states) 59.5 -> 53.0; 2 x 9 rows 23.0 -> 13.7, 2 x 11 25.2 ->
+// 16.5; but 34 photons in 17 modes (59,049 states) 45.5 -> 52, where the step
+// table of the longer sweep is the cheaper step.  Shares of 4, 8 and 16 states: 20
+// photons 19.4, 16.5, 16.3 us; 2 x 9 rows 13.7, 16.7, 21.8.
+constexpr uint64_t kFusedMaxBinary = 1 << 17;
+constexpr uint64_t kFusedMaxMixed = 1 << 15;
+constexpr uint64_t kFusedSteps = 8;
+constexpr uint64_t kFusedStepsMixed = 4;
+
+bool fused_applies(pq_ctx* ctx, const Plan& p) {
+    if (ctx->autotune || p.nc > kFusedMaxCols) return false;
+    if (p.time_states > (p.binary ? kFusedMaxBinary : kFusedMaxMixed)) return false;
+    return sweep_kind(p) != kSweepMixGeneral;
+}
+
+static uint32_t fused_waves(pq_ctx* ctx, const Plan& p) {
+    const uint64_t most = (uint64_t)ctx->num_cu * 2 * kWavesPerBlock;
+    const uint64_t least = p.binary ? kFusedSteps : kFusedStepsMixed;
+    uint64_t waves = (p.time_states + least - 1) / least;
+    if (waves > most) waves = most;
+    return (uint32_t)(waves < 1 ? 1 : waves);
+}
+
+size_t fused_bytes(pq_ctx* ctx, const Plan& p) {
+    return sizeof(double) * 4 * (size_t)((fused_waves(ctx, p) + kWavesPerBlock - 1) / kWavesPerBlock);
+}
+
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, const cplx* U, int64_t ldu, cplx* perm,
+              cplx* amp, hipStream_t st, bool timed) {
+    FusedArgs a;
+    memset(&a, 0, sizeof(a));
+    a.U = U;
+    a.ldu = ldu;
+    a.perm = perm;
+    a.amp = amp;
+    a.scale = p.scale;
+    a.norm = p.norm;
+    a.partials = partials;
+    a.ticket = ticket;
+    a.time_states = (uint32_t)p.time_states;
+    a.waves = fused_waves(ctx, p);
+    a.r = p.r;
+    a.nc = p.nc;
+    a.transposed = p.transposed;
+    a.n_lane = p.n_lane;
+    a.lane_states = p.lane_states;
+    a.n_time = p.n_time;
+    for (int i = 0; i < p.r; ++i) {
+        a.row_mode[i] = p.row_mode[i];
+        a.row_mu[i] = (int8_t)p.row_mu[i];
+        a.radix[i] = (int8_t)p.row_radix[i];
+    }
+    for (int j = 0; j < p.nc; ++j) a.col_mode[j] = p.col_mode[j];
+    // the padded column repeats the largest power
+    int kap[kFusedMaxCols];
+    const int nc = (p.nc + 1) / 2 * 2;
+    for (int j = 0; j < nc; ++j) kap[j] = p.col_kap[j < p.nc ? j : p.nc - 1];
+    make_pow_steps(kap, nc, a.pw);
+    const int grid = (int)((a.waves + kWavesPerBlock - 1) / kWavesPerBlock);
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    const bool prof = timed && ctx->profiling;
+    if (prof) {
+        e0 = ctx->take_event();
+        e1 = ctx->take_event();
+        if (!e0 || !e1) return ctx->fail(PQ_EDEVICE, "profile: hipEventCreate failed");
+        int rc = ctx->check(hipEventRecord(e0, st), "profile: record");
+        if (rc) return rc;
+    }
+    int rc = ctx->check(launch_fused(!p.binary, a, grid, st), "one-launch sweep");
+    if (rc) return rc;
+    if (prof) {
         rc = ctx->check(hipEventRecord(e1, st), "profile: record");
         if (rc) return rc;
         ctx->ev_used.emplace_back(e0, e1);
@@ -427,6 +510,11 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
 
 int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* perm, cplx* amp,
                hipStream_t st) {
+    if (fused_applies(ctx, p)) {
+        double* partials = (double*)ctx->workspace(fused_bytes(ctx, p));
+        if (!partials) return PQ_ENOMEM;
+        return run_fused(ctx, p, partials, ctx->ticket, U, ldu, perm, amp, st, true);
+    }
     int wpc = sweep_waves_per_cu(ctx, p);
     if (ctx->autotune) {
         if (const TuneRecord* t = recorded(ctx, single_sig(p))) {

@@ -46,6 +46,9 @@ struct pq_ctx {
     // device workspace, grown on demand (hipFree waits for earlier work)
     void* ws = nullptr;
     size_t ws_bytes = 0;
+    // one-launch permanents: the count of finished workgroups (device, zero
+    // between launches)
+    uint32_t* ticket = nullptr;
     // cached many-pattern plans and their device descriptors (many.cpp)
     void* many_cache = nullptr;
     // pinned host staging for descriptor uploads; upload_done marks when the
@@ -195,6 +198,13 @@ struct SingleLayout {
     size_t bytes = 0;
 };
 SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread = true);
+
+// One-launch permanents (k_fused_impl.h): whether a plan takes that form, its
+// scratch (the workgroups' sums), and the launch.
+bool fused_applies(pq_ctx* ctx, const Plan& p);
+size_t fused_bytes(pq_ctx* ctx, const Plan& p);
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, const cplx* U, int64_t ldu, cplx* perm,
+              cplx* amp, hipStream_t st, bool timed);
 
 // Full single-permanent sequence (prep, table, sweep, final) on the scratch
 // `ws` laid out by `L`; `timed` brackets the sweep with profiling events.
