@@ -39,6 +39,7 @@ __global__ __launch_bounds__(kBlock) void bprep_kernel(const BPrepArgs a) {
                 continue;
             }
             double re = 0.0, im = 0.0;
+#pragma unroll 8
             for (int i = 0; i < J.r; ++i) {
                 const int out = J.transposed ? cmode[j] : rmode[i];
                 const int in = J.transposed ? rmode[i] : cmode[j];

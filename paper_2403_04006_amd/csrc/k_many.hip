@@ -36,6 +36,7 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
     if (J.op == kOpPerm) {
         // thread t adds slots t, t + 64, ... in order, then a fixed butterfly
         cdd s{{0.0, 0.0}, {0.0, 0.0}};
+#pragma unroll 8
         for (int k = t; k < J.nchunks; k += 64) {
             const double* q = base + (size_t)k * sd;
             s = cdd_add(s, cdd{{q[0], q[1]}, {q[2], q[3]}});
@@ -50,12 +51,13 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
             if (a.perm) a.perm[a.dup_out[q]] = cplx{re, im};
             if (a.amp) a.amp[a.dup_out[q]] = cplx{re * J.norm, im * J.norm};
         }
-        if (a.adjoint && a.fuse_dred) {
+        if (a.adjoint && J.nchunks <= a.fuse_dred) {
             // derivative part of the slots: entry e adds its chunks in order
-            // (the same sums as the two reduction stages for <= 64 chunks)
+            // (the same sums as the two reduction stages)
             const int nent = J.r * J.nc;
             for (int e = t; e < nent; e += 64) {
                 double dre = 0.0, dim = 0.0;
+#pragma unroll 8
                 for (int k = 0; k < J.nchunks; ++k) {
                     dre += base[(size_t)k * sd + 4 + 2 * e];
                     dim += base[(size_t)k * sd + 4 + 2 * e + 1];
@@ -63,8 +65,7 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
                 a.dpat[a.dpat_off[p] + e] = cplx{dre * J.scale, dim * J.scale};
             }
         }
-        // (otherwise the derivative part of the slots is reduced by the two
-        // dred stages)
+        // (otherwise the derivative part of the slots is the stage-1 items')
     } else {
         // Laplace expansion: L_j from the chunk sums, then out[l] = sum_j U[l, C_j] L_j;
         // a sweep over the columns' signs has the columns on its iterated side
@@ -109,19 +110,14 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// One workgroup per distinct pattern.
-__global__ __launch_bounds__(64) void many_final_kernel(const ManyFinalArgs a) {
-    __shared__ cplx L[kMaxExtendCols];
-    const int p = blockIdx.x;
-    if (p >= a.npat) return;
-    final_pattern(a, p, (int)threadIdx.x, L);
-}
-
-__global__ __launch_bounds__(64) void dred1_kernel(const DRedArgs a) {
-    const DRedItem it = a.items[blockIdx.x];
+// Stage-1 item of the derivative reduction (see DRedItem).  Bound by the
+// latency of its strided reads: with 16 of them in flight, and beside the
+// patterns' values instead of after them, one 23-photon pattern's reductions
+// (18 MB of slots) take 14 us in two launches, 48 in three before.
+__device__ __forceinline__ void reduce_slots(const ManyFinalArgs& a, const DRedItem& it, int t) {
     const BJob& J = a.jobs[it.pat];
     const int nent = J.r * J.nc;
-    const int e = it.eb * 64 + (int)threadIdx.x;
+    const int e = it.eb * 64 + t;
     if (e >= nent) return;
     const int cls = a.pat_class[it.pat];
     const int sd = a.class_sd[cls];
@@ -129,20 +125,31 @@ __global__ __launch_bounds__(64) void dred1_kernel(const DRedArgs a) {
     const int k0 = it.cb * 64;
     const int k1 = J.nchunks < k0 + 64 ? J.nchunks : k0 + 64;
     double re = 0.0, im = 0.0;
+#pragma unroll 16
     for (int k = k0; k < k1; ++k) {
         re += base[(size_t)k * sd];
         im += base[(size_t)k * sd + 1];
     }
-    a.part[it.part_off + (int64_t)it.cb * nent + e] = cplx{re, im};
+    if (it.ncb == 1) a.dpat[a.dpat_off[it.pat] + e] = cplx{re * J.scale, im * J.scale};
+    else a.red_part[it.part_off + (int64_t)it.cb * nent + e] = cplx{re, im};
 }
 
-__global__ __launch_bounds__(64) void dred2_kernel(const DRedArgs a) {
+// One workgroup per distinct pattern, then one per stage-1 item.
+__global__ __launch_bounds__(64) void many_final_kernel(const ManyFinalArgs a) {
+    __shared__ cplx L[kMaxExtendCols];
+    const int p = blockIdx.x;
+    if (p < a.npat) final_pattern(a, p, (int)threadIdx.x, L);
+    else if (p - a.npat < a.nred) reduce_slots(a, a.red[p - a.npat], (int)threadIdx.x);
+}
+
+__global__ __launch_bounds__(64) void dred_kernel(const DRedArgs a) {
     const DRedItem it = a.items[blockIdx.x];
     const BJob& J = a.jobs[it.pat];
     const int nent = J.r * J.nc;
     const int e = it.eb * 64 + (int)threadIdx.x;
     if (e >= nent) return;
     double re = 0.0, im = 0.0;
+#pragma unroll 8
     for (int cb = 0; cb < it.ncb; ++cb) {
         const cplx v = a.part[it.part_off + (int64_t)cb * nent + e];
         re += v.re;
@@ -151,10 +158,9 @@ __global__ __launch_bounds__(64) void dred2_kernel(const DRedArgs a) {
     a.dpat[a.dpat_off[it.pat] + e] = cplx{re * J.scale, im * J.scale};
 }
 
-hipError_t launch_dred(int stage, const DRedArgs& a, int nitems, hipStream_t s) {
+hipError_t launch_dred(const DRedArgs& a, int nitems, hipStream_t s) {
     if (nitems <= 0) return hipSuccess;
-    if (stage == 1) hipLaunchKernelGGL(dred1_kernel, dim3(nitems), dim3(64), 0, s, a);
-    else hipLaunchKernelGGL(dred2_kernel, dim3(nitems), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(dred_kernel, dim3(nitems), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
@@ -175,7 +181,8 @@ hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_many_final(const ManyFinalArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(many_final_kernel, dim3(a.npat > 0 ? a.npat : 1), dim3(64), 0, s, a);
+    const int n = a.npat + a.nred;
+    hipLaunchKernelGGL(many_final_kernel, dim3(n > 0 ? n : 1), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

@@ -50,15 +50,23 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
                   kTuneCandidates[0].chunks_per_wave == ChunkPolicy().chunks_per_wave &&
                   kTuneCandidates[0].min_chunk == ChunkPolicy().min_chunk,
               "the first candidate is the default policy");
-// Cached plans: four whatever their size, more while their device blocks
-// stay within kMaxManyBytes together, kMaxManyEntries at most (a training loop
-// holds a forward and a reverse plan for each of its pattern sets).
 // From this many extend-row jobs on, their final step reads U transposed (one
 // launch more; 19,000 jobs on 400 modes: 230 us of final step before).
 constexpr int kTransposeMinJobs = 512;
+// Cached plans: four whatever their size, more while their device blocks
+// stay within kMaxManyBytes together, kMaxManyEntries at most (a training loop
+// holds a forward and a reverse plan for each of its pattern sets; 4096 patterns
+// of 8 photons take 5 MB).  A block of its own costs a large new list more than
+// one given back just before: gradients of new 23-photon patterns (19 MB each)
+// 430 us a call with 16 of them kept, 250 with four.
 constexpr int kMinManyEntries = 4;
 constexpr int kMaxManyEntries = 16;
-constexpr size_t kMaxManyBytes = (size_t)1 << 30;
+constexpr size_t kMaxManyBytes = (size_t)64 << 20;
+// Chunks of a pattern up to which its own workgroup of the final kernel adds
+// the derivative slots; more are separate workgroups' (one per 64 slots and 64
+// entries).  16 photons, one pattern: 40 us at 64, 29 at 8; 64 patterns of 14:
+// 39 and 36; at 2 the many short lists have twice the workgroups for nothing.
+constexpr int kFusedReduction = 8;
 struct ManyClass;
 int walk_occupancy(pq_ctx* ctx, const ManyClass& C);
 
@@ -84,7 +92,6 @@ struct ManyEntry {
     size_t bytes = 0;            // device block
     int mode = 0;                // kModeFwd (forward and extend jobs) or kModeAdj
     int npat = 0, ntab = 0;      // npat: distinct patterns (identical ones are swept once)
-    bool fuse_dred = false;      // adjoint: the final kernel reduces the derivative slots
     int max_chunks = 0;          // most chunks of any pattern (1: nothing for a work queue to balance)
     int queue_pref = -1;         // the autotuner's schedule for pq_perm_batched (1 queue, 0 static, -1 none)
     size_t mat_elems = 0, partial_doubles = 0, dpat_elems = 0;
@@ -475,29 +482,21 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
 
     for (size_t k = 0; k < pats.size(); ++k)
         if (pat_class[k] >= 0) E.max_chunks = std::max(E.max_chunks, (int)hj[k].nchunks);
-    // adjoint: the final kernel adds the derivative slots itself when no
-    // pattern has more than 64 chunks (one stage-1 block each: the same sums)
-    if (adj) {
-        int maxch = 0;
-        for (size_t k = 0; k < pats.size(); ++k)
-            if (pat_class[k] >= 0) maxch = std::max(maxch, (int)hj[k].nchunks);
-        E.fuse_dred = maxch <= 64;
-    }
     // adjoint: reduction items of the derivative slots (see DRedItem)
     std::vector<DRedItem> red1, red2;
     size_t red_part = 0;
-    if (adj && !E.fuse_dred) {
+    if (adj) {
         for (size_t k = 0; k < pats.size(); ++k) {
-            if (pat_class[k] < 0) continue;
+            if (pat_class[k] < 0 || (int)hj[k].nchunks <= kFusedReduction) continue;
             const BJob& b = hj[k];
             const int nent = b.r * b.nc;
             if (nent == 0) continue;
             const int neb = (nent + 63) / 64, ncb = (b.nchunks + 63) / 64;
             for (int eb = 0; eb < neb; ++eb) {
                 for (int cb = 0; cb < ncb; ++cb) red1.push_back(DRedItem{(int32_t)k, eb, cb, ncb, (int64_t)red_part});
-                red2.push_back(DRedItem{(int32_t)k, eb, 0, ncb, (int64_t)red_part});
+                if (ncb > 1) red2.push_back(DRedItem{(int32_t)k, eb, 0, ncb, (int64_t)red_part});
             }
-            red_part += (size_t)ncb * nent;
+            if (ncb > 1) red_part += (size_t)ncb * nent;
         }
     }
     E.nred1 = (int)red1.size();
@@ -705,12 +704,15 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     fa.dup_out = E.d_dup_out;
     fa.npat = E.npat;
     fa.adjoint = E.mode == kModeAdj ? 1 : 0;
-    fa.fuse_dred = E.fuse_dred ? 1 : 0;
+    fa.fuse_dred = kFusedReduction;
     fa.perm = perm;
     fa.amp = amp;
     fa.dpat = E.d_dpat;
     fa.gperm = gperm;
     fa.gsum = E.d_gsum;
+    fa.red = E.d_red1;
+    fa.nred = E.nred1;
+    fa.red_part = E.d_red_part;
     const int nclass = (int)E.classes.size();
     bool any_queue = false;
     for (const ManyClass& C : E.classes) any_queue = any_queue || (queue && class_queues(ctx, C));
@@ -769,19 +771,11 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     if (E.mode == kModeAdj) {
         DRedArgs ra;
         ra.jobs = E.d_jobs;
-        ra.pat_slot = E.d_pat_slot;
-        ra.pat_class = E.d_pat_class;
-        ra.class_off = E.d_class_off;
-        ra.class_sd = E.d_class_sd;
-        ra.partials = E.d_partials;
         ra.dpat_off = E.d_dpat_off;
         ra.part = E.d_red_part;
         ra.dpat = E.d_dpat;
-        ra.items = E.d_red1;
-        rc = ctx->check(launch_dred(1, ra, E.nred1, st), "derivative reduction");
-        if (rc) return rc;
         ra.items = E.d_red2;
-        rc = ctx->check(launch_dred(2, ra, E.nred2, st), "derivative reduction");
+        rc = ctx->check(launch_dred(ra, E.nred2, st), "derivative reduction");
         if (rc) return rc;
         GradScatterArgs ga;
         ga.offsets = E.d_sc_off;

@@ -55,6 +55,25 @@ struct ManyArgs {
     double* partials;       // slot storage of this class
 };
 
+// Reduction of the reverse sweeps' derivative slots in two fixed-order
+// stages: stage 1 (in the final kernel) adds up to 64 consecutive slots of a
+// pattern for 64 consecutive entries, stage 2 adds a pattern's stage-1 partials
+// and scales; a pattern of one stage-1 row needs no second stage.
+// Item (pat, eb, cb): entries [64 eb, 64 eb + 64), slots [64 cb, 64 cb + 64);
+// stage-2 items have cb = 0 and read ncb partial rows.
+struct DRedItem {
+    int32_t pat, eb, cb, ncb;
+    int64_t part_off;       // complex offset of the pattern's [ncb][r * nc] partials
+};
+
+struct DRedArgs {
+    const DRedItem* items;
+    const BJob* jobs;
+    const int64_t* dpat_off;
+    const cplx* part;
+    cplx* dpat;
+};
+
 // Per-pattern reduction of the chunk slots.
 struct ManyFinalArgs {
     const cplx* U;
@@ -78,12 +97,15 @@ struct ManyFinalArgs {
     const int64_t* dup_out;
     int32_t npat;              // distinct patterns
     int32_t adjoint;
-    int32_t fuse_dred;         // adjoint: add the derivative slots here (every pattern has <= 64 chunks)
+    int32_t fuse_dred;         // adjoint: most chunks of a pattern whose slots its own workgroup adds
     cplx* perm;                // may be null (forward values)
     cplx* amp;                 // may be null
     cplx* dpat;                // adjoint: per pattern r x nc complex d perm / d B (scaled)
     const cplx* gperm;         // adjoint: the caller's per-copy cotangents
     cplx* gsum;                // adjoint: per distinct pattern, the sum of its copies' cotangents
+    const DRedItem* red;       // [nred]: stage-1 items of the other patterns
+    int32_t nred;
+    cplx* red_part;
 };
 
 // U transposed for the extend-row jobs' final step: its lanes are consecutive
@@ -111,29 +133,6 @@ struct QueueArgs {
 struct QueuePrepArgs {
     unsigned* zero;
     int32_t nzero;
-};
-
-// Reduction of the reverse sweeps' derivative slots in two fixed-order
-// stages: stage 1 adds up to 64 consecutive slots of a pattern for 64
-// consecutive entries, stage 2 adds a pattern's stage-1 partials and scales.
-// Item (pat, eb, cb): entries [64 eb, 64 eb + 64), slots [64 cb, 64 cb + 64);
-// stage-2 items have cb = 0 and read ncb partial rows.
-struct DRedItem {
-    int32_t pat, eb, cb, ncb;
-    int64_t part_off;       // complex offset of the pattern's [ncb][r * nc] partials
-};
-
-struct DRedArgs {
-    const DRedItem* items;
-    const BJob* jobs;
-    const int32_t* pat_slot;
-    const int32_t* pat_class;
-    const int64_t* class_off;
-    const int32_t* class_sd;
-    const double* partials;
-    const int64_t* dpat_off;
-    cplx* part;
-    cplx* dpat;
 };
 
 // Scatter of the per-pattern derivatives into dU (conjugate-Wirtinger VJP).

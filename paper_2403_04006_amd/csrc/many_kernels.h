@@ -51,7 +51,7 @@ int occupancy_queue(int mode, int ncmax, int var);
 hipError_t launch_queue_prep(const QueuePrepArgs& a, hipStream_t s);
 hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s);
 hipError_t launch_many_final(const ManyFinalArgs& a, hipStream_t s);
-hipError_t launch_dred(int stage, const DRedArgs& a, int nitems, hipStream_t s);
+hipError_t launch_dred(const DRedArgs& a, int nitems, hipStream_t s);
 hipError_t launch_grad_scatter(const GradScatterArgs& a, hipStream_t s);
 
 }  // namespace pq
