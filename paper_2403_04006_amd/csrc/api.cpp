@@ -56,18 +56,7 @@ int pq_create(pq_ctx** out, int hip_device) {
         c->cancel_word = (int32_t*)h;
         c->cancel_word_dev = (int32_t*)d;
         __atomic_store_n(c->cancel_word, 0, __ATOMIC_SEQ_CST);
-        void* t = nullptr;
-        if (hipMalloc(&t, 256) != hipSuccess) {
-            c->release_all();
-            delete c;
-            return PQ_ENOMEM;
-        }
-        c->ticket = (uint32_t*)t;
-        if (hipMemset(t, 0, 256) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-            c->release_all();
-            delete c;
-            return PQ_EDEVICE;
-        }
+        c->tickets = take_tickets(hip_device);
     }
     if (const char* e = getenv("PQ_FAULT_INJECT")) {
         if (!strcmp(e, "alloc")) c->fault = PQ_FAULT_ALLOC;

@@ -46,6 +46,91 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// The pair sweep's table (layout at PairArgs): one thread per pair of columns and
+// digit row; row 0 also takes the pair's sums and constants.
+__global__ __launch_bounds__(64) void pair_prep_kernel(const PairPrepArgs a) {
+    const int P = a.pairs, W = 2 * P;
+    const int e = blockIdx.x * 64 + (int)threadIdx.x;
+    const int i = e / P, p = e - i * P;
+    const int n_rows = a.n_lane + 3 + a.n_outer;
+    if (i >= n_rows) return;
+    auto at = [&](int row, int col) {
+        if (col >= a.nc) return cplx{0.0, 0.0};
+        const int out = a.transposed ? a.col_mode[col] : a.row_mode[row];
+        const int in = a.transposed ? a.row_mode[row] : a.col_mode[col];
+        return a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
+    };
+    cplx* lrow = a.tab + W;
+    cplx* prod = lrow + kMaxLaneDigits * W;
+    cplx* dev = prod + 4 * P;
+    cplx* steps = dev + 8 * P;
+    // sign patterns of the three lowest digits, up to a common sign
+    const double sign[4][3] = {{1, 1, 1}, {1, -1, -1}, {-1, 1, -1}, {-1, -1, 1}};
+    cplx ak[4], bk[4];
+    cplx la[3], lb[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        la[q] = at(a.n_lane + q, 2 * p);
+        lb[q] = at(a.n_lane + q, 2 * p + 1);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        ak[k] = bk[k] = cplx{0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            cfma_to(ak[k], sign[k][q], la[q]);
+            cfma_to(bk[k], sign[k][q], lb[q]);
+        }
+    }
+    if (i < a.n_lane) {
+        const cplx x = at(i, 2 * p), y = at(i, 2 * p + 1);
+        lrow[i * W + 2 * p] = cplx{-2.0 * x.re, -2.0 * x.im};
+        lrow[i * W + 2 * p + 1] = cplx{-2.0 * y.re, -2.0 * y.im};
+    } else if (i >= a.n_lane + 3) {
+        const cplx x = at(i, 2 * p), y = at(i, 2 * p + 1);
+        cplx* s = steps + ((size_t)(i - a.n_lane - 3) * 2 * P + p) * 6;
+#pragma unroll
+        for (int sel = 0; sel < 2; ++sel) {
+            const double f = sel ? 2.0 : -2.0;
+            const cplx sx{f * x.re, f * x.im}, sy{f * y.re, f * y.im};
+            cplx* o = s + (size_t)sel * P * 6;
+            o[0] = sx;
+            o[1] = sy;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const cplx u = cmul(sx, bk[k]), v = cmul(sy, ak[k]);
+                o[2 + k] = cplx{u.re + v.re, u.im + v.im};
+            }
+        }
+    }
+    if (i == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            prod[4 * p + k] = cmul(ak[k], bk[k]);
+            dev[8 * p + 2 * k] = ak[k];
+            dev[8 * p + 2 * k + 1] = bk[k];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int col = 2 * p + h;
+            cplx s{col < a.nc ? 0.0 : 1.0, 0.0};
+#pragma unroll 8
+            for (int row = 0; row < a.r; ++row) {
+                // the middle of a low digit is one unit of its row below digit zero
+                const bool low = row >= a.n_lane && row < a.n_lane + 3;
+                cfma_to(s, (double)(a.row_mu[row] - (low ? 1 : 0)), at(row, col));
+            }
+            a.tab[col] = s;
+        }
+    }
+}
+
+hipError_t launch_pair_prep(const PairPrepArgs& a, hipStream_t s) {
+    const int n = a.pairs * (a.n_lane + 3 + a.n_outer);
+    hipLaunchKernelGGL(pair_prep_kernel, dim3((n + 63) / 64), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
 // Per-step table of the inner digits.  Forward traversal: position q is the
 // Gray state of rank q.  Reflected traversal: position p is the state of rank
 // M-1-p (the inner code run backwards).  Entry p holds the row offset of the
@@ -72,6 +157,7 @@ hipError_t launch_table(const TableArgs& a, hipStream_t s) {
 __global__ __launch_bounds__(kBlock) void final_kernel(const FinalArgs a) {
     __shared__ double sh[kBlock][4];
     cdd s{{0.0, 0.0}, {0.0, 0.0}};
+#pragma unroll 8
     for (int k = threadIdx.x; k < a.count; k += kBlock) {
         const double* p = a.partials + 4 * (size_t)k;
         s = cdd_add(s, cdd{{p[0], p[1]}, {p[2], p[3]}});
@@ -134,6 +220,25 @@ hipError_t launch_fused(bool mix, const FusedArgs& a, int grid, hipStream_t s) {
         PQ_FCLASS(PQ_FCASE)
 #undef PQ_FCASE
         default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_pair(int nc, const PairArgs& a, hipStream_t s) {
+    if (a.groups < 1 || a.n_outer < 1 || a.blocks != 1ull << a.n_outer) return hipErrorInvalidValue;
+    switch ((nc + 1) / 2) {
+#define PQ_PCASE(P) case P: return launch_pair_##P(a, s);
+        PQ_PCLASS(PQ_PCASE)
+#undef PQ_PCASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+int occupancy_pair(int nc) {
+    switch ((nc + 1) / 2) {
+#define PQ_PCASE(P) case P: return occupancy_pair_##P();
+        PQ_PCLASS(PQ_PCASE)
+#undef PQ_PCASE
+        default: return 0;
     }
 }
 

@@ -16,6 +16,7 @@ namespace pq {
 constexpr int kSweepMix = 0;         // mixed digits or powers (product_grouped)
 constexpr int kSweepBin = 1;         // binary digits, unit powers
 constexpr int kSweepMixGeneral = 2;  // powers whose steps product_grouped does not cover
+constexpr int kSweepPair = 3;        // binary digits, unit powers, by pairs of columns (k_pair_impl.h)
 
 #define PQ_DECL(NC)                                                              \
     hipError_t launch_glynn_##NC(int kind, const GlynnArgs& a, int grid, hipStream_t s); \
@@ -35,6 +36,17 @@ constexpr int kFusedMaxCols = 32;
 PQ_FCLASS(PQ_FDECL)
 #undef PQ_FDECL
 hipError_t launch_fused(bool mix, const FusedArgs& a, int grid, hipStream_t s);
+
+// Long binary sweeps by pairs of columns (padded to an even number).
+constexpr int kPairMinCols = 25, kPairMaxCols = 32;
+#define PQ_PCLASS(X) X(13) X(14) X(15) X(16)
+#define PQ_PDECL(P) hipError_t launch_pair_##P(const PairArgs& a, hipStream_t s); int occupancy_pair_##P();
+PQ_PCLASS(PQ_PDECL)
+#undef PQ_PDECL
+hipError_t launch_pair_prep(const PairPrepArgs& a, hipStream_t s);
+hipError_t launch_pair(int nc, const PairArgs& a, hipStream_t s);
+// Resident workgroups (of two wavefronts) per compute unit (0 on error).
+int occupancy_pair(int nc);
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
 hipError_t launch_table(const TableArgs& a, hipStream_t s);

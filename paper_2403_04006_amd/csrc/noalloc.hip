@@ -9,7 +9,9 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
+#include <vector>
 
 #include "../../include/pq.h"
 #include "kernels.h"
@@ -18,16 +20,21 @@
 
 namespace pq {
 
+// what is accepted, and the buffer, which also holds the pair sweep's sums
 constexpr size_t kNoAllocScratchBytes = PQ_NOALLOC_SCRATCH_BYTES;
+constexpr size_t kNoAllocBufferBytes = 640 * 1024;
 constexpr int kNoAllocMaxDevices = 64;
 
-static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
-// the one-launch form's workgroup count, zero between launches
-static __device__ uint32_t scratch_ticket;
+static __device__ __align__(256) char scratch[kNoAllocBufferBytes];
+// the one-launch form's workgroup counts, zero from the start and between
+// launches: the first for this file, the others lent to one ctx each
+constexpr int kTicketSets = 1024;
+static __device__ uint32_t ticket_sets[kTicketSets][kTickets];
 
 static std::mutex g_scratch_mu;
+static std::vector<bool> g_sets_taken[kNoAllocMaxDevices];
 static char* g_scratch_dev[kNoAllocMaxDevices] = {};
-static uint32_t* g_ticket_dev[kNoAllocMaxDevices] = {};
+static uint32_t* g_tickets_dev[kNoAllocMaxDevices] = {};
 
 int noalloc_init(int device) {
     if (device < 0 || device >= kNoAllocMaxDevices) return PQ_EINVAL;
@@ -38,20 +45,40 @@ int noalloc_init(int device) {
         (void)hipGetLastError();
         return PQ_EDEVICE;
     }
-    void* ticket = nullptr;
-    if (hipGetSymbolAddress(&ticket, HIP_SYMBOL(scratch_ticket)) != hipSuccess || !ticket) {
+    void* tickets = nullptr;
+    if (hipGetSymbolAddress(&tickets, HIP_SYMBOL(ticket_sets)) != hipSuccess || !tickets) {
         (void)hipGetLastError();
         return PQ_EDEVICE;
     }
-    g_ticket_dev[device] = (uint32_t*)ticket;
+    g_tickets_dev[device] = (uint32_t*)tickets;
     g_scratch_dev[device] = (char*)ptr;
     return PQ_OK;
 }
 
-static char* scratch_of(int device, uint32_t** ticket) {
+uint32_t* take_tickets(int device) {
     if (device < 0 || device >= kNoAllocMaxDevices) return nullptr;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
-    *ticket = g_ticket_dev[device];
+    if (!g_tickets_dev[device]) return nullptr;
+    std::vector<bool>& taken = g_sets_taken[device];
+    taken.resize(kTicketSets, false);
+    for (int k = 1; k < kTicketSets; ++k)
+        if (!taken[k]) {
+            taken[k] = true;
+            return g_tickets_dev[device] + (size_t)k * kTickets;
+        }
+    return nullptr;
+}
+
+void give_tickets(int device, uint32_t* tickets) {
+    if (!tickets) return;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    g_sets_taken[device][(size_t)(tickets - g_tickets_dev[device]) / kTickets] = false;
+}
+
+static char* scratch_of(int device, uint32_t** tickets) {
+    if (device < 0 || device >= kNoAllocMaxDevices) return nullptr;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    *tickets = g_tickets_dev[device];
     return g_scratch_dev[device];
 }
 
@@ -76,18 +103,21 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
         if (!perm && !amp) return PQ_OK;
         return ctx->check(launch_fill((cplx*)perm, (cplx*)amp, v, st), "fill");
     }
-    uint32_t* ticket = nullptr;
-    char* ws = scratch_of(ctx->device, &ticket);
+    uint32_t* tickets = nullptr;
+    char* ws = scratch_of(ctx->device, &tickets);
     if (!ws) return ctx->fail(PQ_EDEVICE, "pq_perm_noalloc: the static scratch of device %d was not resolved", ctx->device);
-    // what fits is decided without the spread (its partials can need more
-    // scratch), which is then taken where it fits too
-    SingleLayout L = single_layout(ctx, p, single_waves_per_cu(ctx, p), false);
+    // what fits is decided by the sweep of single columns without the spread (its
+    // partials can need more scratch); other forms are taken where they fit too
+    const int kind = sweep_kind(p), plain = kind == kSweepPair ? kSweepBin : kind;
+    const int wpc = single_waves_per_cu(ctx, p);
+    const int plain_wpc = std::max(1, wpc / resident_waves(ctx, p, kind)) * resident_waves(ctx, p, plain);
+    SingleLayout L = single_layout(ctx, p, plain, plain == kind ? wpc : plain_wpc, false);
     if (L.bytes > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
                          "bytes of the static buffer (use pq_perm)", L.bytes, kNoAllocScratchBytes);
-    if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocScratchBytes)
-        return run_fused(ctx, p, (double*)ws, ticket, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
-    const SingleLayout spread = single_layout(ctx, p, single_waves_per_cu(ctx, p));
-    if (spread.bytes <= kNoAllocScratchBytes) L = spread;
+    if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
+        return run_fused(ctx, p, (double*)ws, tickets, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
+    const SingleLayout spread = single_layout(ctx, p, kind, wpc);
+    if (spread.bytes <= kNoAllocBufferBytes) L = spread;
     return run_single_at(ctx, p, L, ws, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
 }

@@ -92,6 +92,40 @@ struct GlynnArgs {
     PowSteps pw;          // their structure for product_grouped
 };
 
+// Pair sweep (k_pair_impl.h).  Its table, in complex values for P pairs, W = 2 P
+// columns (sums 1 and rows 0 in a padded one):
+//   [W]                 column sums, lane and higher time digits at zero, the
+//                       three lowest time digits at their middle
+//   [kMaxLaneDigits][W] -2B of the lane digits
+//   [P][4]              a_k b_k
+//   [P][4][2]           a_k, b_k
+//   [n_outer][2][P][6]  steps of the higher time digits (up, down): moves of the
+//                       pair's sums, then of O_0 .. O_3
+struct PairArgs {
+    const cplx* tab;
+    double* partials;            // [groups][4]
+    uint64_t blocks;             // blocks of eight time states
+    uint32_t groups;             // workgroups (the blocks are split evenly among them)
+    int32_t n_lane, lane_states;
+    int32_t n_outer;             // time digits above the three lowest (1 at least)
+};
+
+PQ_HD size_t pair_table_size(int pairs, int n_outer) {
+    return (size_t)pairs * (size_t)(2 + 2 * kMaxLaneDigits + 4 + 8 + 12 * n_outer);
+}
+
+struct PairPrepArgs {
+    const cplx* U;
+    int64_t ldu;
+    cplx* tab;
+    int32_t r, nc, pairs;
+    int32_t transposed;          // as in PrepArgs
+    int32_t n_lane, n_outer;     // rows: lane digits, three time digits, n_outer time digits, constant rows
+    int32_t row_mode[kMaxDim];   // iterated modes in digit order
+    int32_t row_mu[kMaxDim];
+    int32_t col_mode[kMaxDim];
+};
+
 // Prep kernel arguments: gather the compact matrix from U and build the
 // +-2B rows and the base column sums.
 struct PrepArgs {
@@ -129,6 +163,7 @@ struct FinalArgs {
 };
 
 // A whole permanent in one launch (k_fused_impl.h).
+constexpr int kTickets = 4;
 struct FusedArgs {
     const cplx* U;
     int64_t ldu;
@@ -137,7 +172,8 @@ struct FusedArgs {
     double scale;                // 2^{-(n-1)}
     double norm;                 // 1 / sqrt(prod S! prod T!)
     double* partials;            // [grid][4]
-    uint32_t* ticket;            // zero between launches
+    uint32_t* tickets;           // [kTickets], zero between launches
+    uint32_t turn;               // the one this launch counts in
     uint32_t time_states;
     uint32_t waves;
     int32_t r, nc;

@@ -5,6 +5,8 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "../../include/pq.h"
 #include "kernels.h"
 
@@ -183,14 +185,14 @@ void pq_ctx::release_all() {
     if (ws) hipFree(ws);
     ws = nullptr;
     ws_bytes = 0;
-    if (ticket) hipFree(ticket);
-    ticket = nullptr;
+    pq::give_tickets(device, tickets);
+    tickets = nullptr;
 }
 
 int pq_ctx::occupancy(int kind, int nc) {
     int& o = occ[kind][nc];
     if (o == 0) {
-        o = pq::occupancy_glynn(kind, nc);
+        o = kind == pq::kSweepPair ? pq::occupancy_pair(nc) : pq::occupancy_glynn(kind, nc);
         if (o < 1) o = 1;
     }
     return o;
@@ -205,22 +207,48 @@ static constexpr uint64_t kMinStepsPerWave = 32;
 // wavefront more costs nothing else: 34 photons in 17 modes 49 -> 45 us
 static constexpr uint64_t kSpreadSteps = 8;
 
-// Sweep kernel kind of a plan (see kernels.h).
+// The pair sweep from 2^18 time states on: 25 photons 108 -> 88 us, 26 187 -> 153
+// (24 photons in one launch 53, by pairs 51, 23 35 and 38).  Beyond 32 columns two
+// wavefronts' registers do not hold the pairs.
+static constexpr int kPairTimeDigits = 18;
+// Its workgroups: one round of the resident ones, and one for every
+// kPairBlocks blocks of eight states (at two rounds of wavefronts; the tuner's
+// one and four rounds scale it) where that is more, since equal shares leave the
+// fastest of the eight XCDs idle for 6 % of the time: 30 photons at 1024
+// workgroups 2.41 ms, 2048 2.38, 8192 2.28, 16384 2.25; but 28 photons 545, 545,
+// 562 and 621 us, where the start-up (two blocks' work) shows.
+static constexpr uint64_t kPairBlocks = 128;
+static constexpr uint64_t kPairMaxGroups = 16384;
+
 int sweep_kind(const Plan& p) {
-    if (p.binary) return kSweepBin;
+    if (p.binary)
+        return p.nc >= kPairMinCols && p.nc <= kPairMaxCols && p.n_time >= kPairTimeDigits ? kSweepPair : kSweepBin;
     PowSteps ps;
     make_pow_steps(p.col_kap, p.nc, ps);
     return ps.general ? kSweepMixGeneral : kSweepMix;
 }
 
-int sweep_waves_per_cu(pq_ctx* ctx, const Plan& p, int rounds) {
-    return ctx->occupancy(sweep_kind(p), p.nc) * kWavesPerBlock * rounds;
+int resident_waves(pq_ctx* ctx, const Plan& p, int kind) {
+    return ctx->occupancy(kind, p.nc) * (kind == kSweepPair ? 2 : kWavesPerBlock);
 }
 
-Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread) {
+int sweep_waves_per_cu(pq_ctx* ctx, const Plan& p, int rounds) {
+    return resident_waves(ctx, p, sweep_kind(p)) * rounds;
+}
+
+Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread) {
     Geometry g;
     const uint64_t full = (uint64_t)(waves_per_cu > 0 ? waves_per_cu : 1) * (uint64_t)ctx->num_cu;
-    const uint64_t round = (uint64_t)ctx->occupancy(sweep_kind(p), p.nc) * kWavesPerBlock * (uint64_t)ctx->num_cu;
+    if (kind == kSweepPair) {
+        const uint64_t round = (uint64_t)resident_waves(ctx, p, kind) * (uint64_t)ctx->num_cu / 2;
+        const uint64_t rounds = std::max(full / 2 / std::max(round, (uint64_t)1), (uint64_t)1);
+        const uint64_t blocks = p.time_states >> 3;
+        const uint64_t groups = std::min(std::max(round, blocks * rounds / (2 * kPairBlocks)), kPairMaxGroups);
+        g.grid = (int)std::max(std::min(groups, blocks), (uint64_t)1);
+        g.waves = 2 * (uint32_t)g.grid;
+        return g;
+    }
+    const uint64_t round = (uint64_t)resident_waves(ctx, p, kind) * (uint64_t)ctx->num_cu;
     uint64_t waves = (p.time_states + kMinStepsPerWave - 1) / kMinStepsPerWave;
     if (waves > full) waves = full;
     if (!spread) {
@@ -274,18 +302,21 @@ int single_waves_per_cu(pq_ctx* ctx, const Plan& p) {
     return sweep_waves_per_cu(ctx, p);
 }
 
-int timed_sweep(pq_ctx* ctx, int kind, int nc, const GlynnArgs& a, int grid, hipStream_t st) {
+// `launch()`, bracketed by timing events when `timed` and profiling is on.
+template <class F>
+static int timed_sweep(pq_ctx* ctx, bool timed, hipStream_t st, F launch) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (ctx->profiling) {
+    timed = timed && ctx->profiling;
+    if (timed) {
         e0 = ctx->take_event();
         e1 = ctx->take_event();
         if (!e0 || !e1) return ctx->fail(PQ_EDEVICE, "profile: hipEventCreate failed");
         int rc = ctx->check(hipEventRecord(e0, st), "profile: record");
         if (rc) return rc;
     }
-    int rc = ctx->check(launch_glynn(kind, nc, a, grid, st), "sweep");
+    int rc = ctx->check(launch(), "sweep");
     if (rc) return rc;
-    if (ctx->profiling) {
+    if (timed) {
         rc = ctx->check(hipEventRecord(e1, st), "profile: record");
         if (rc) return rc;
         ctx->ev_used.emplace_back(e0, e1);
@@ -323,7 +354,7 @@ size_t fused_bytes(pq_ctx* ctx, const Plan& p) {
     return sizeof(double) * 4 * (size_t)((fused_waves(ctx, p) + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, const cplx* U, int64_t ldu, cplx* perm,
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, const cplx* U, int64_t ldu, cplx* perm,
               cplx* amp, hipStream_t st, bool timed) {
     FusedArgs a;
     memset(&a, 0, sizeof(a));
@@ -334,7 +365,8 @@ int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, co
     a.scale = p.scale;
     a.norm = p.norm;
     a.partials = partials;
-    a.ticket = ticket;
+    a.tickets = tickets;
+    a.turn = ctx->ticket_turn++ % kTickets;
     a.time_states = (uint32_t)p.time_states;
     a.waves = fused_waves(ctx, p);
     a.r = p.r;
@@ -355,31 +387,22 @@ int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, co
     for (int j = 0; j < nc; ++j) kap[j] = p.col_kap[j < p.nc ? j : p.nc - 1];
     make_pow_steps(kap, nc, a.pw);
     const int grid = (int)((a.waves + kWavesPerBlock - 1) / kWavesPerBlock);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    const bool prof = timed && ctx->profiling;
-    if (prof) {
-        e0 = ctx->take_event();
-        e1 = ctx->take_event();
-        if (!e0 || !e1) return ctx->fail(PQ_EDEVICE, "profile: hipEventCreate failed");
-        int rc = ctx->check(hipEventRecord(e0, st), "profile: record");
-        if (rc) return rc;
-    }
-    int rc = ctx->check(launch_fused(!p.binary, a, grid, st), "one-launch sweep");
-    if (rc) return rc;
-    if (prof) {
-        rc = ctx->check(hipEventRecord(e1, st), "profile: record");
-        if (rc) return rc;
-        ctx->ev_used.emplace_back(e0, e1);
-    }
-    return PQ_OK;
+    return timed_sweep(ctx, timed, st, [&] { return launch_fused(!p.binary, a, grid, st); });
 }
 
-SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread) {
+SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread) {
     SingleLayout L;
-    L.geo = sweep_geometry(ctx, p, waves_per_cu, spread);
+    L.geo = sweep_geometry(ctx, p, kind, waves_per_cu, spread);
+    L.kind = kind;
     const int r = p.r, nc = p.nc;
     const size_t ntab = p.binary ? 0 : (size_t)p.m_inner;
     Carve cv;
+    if (kind == kSweepPair) {
+        L.oB = cv.take(sizeof(cplx) * pair_table_size((nc + 1) / 2, p.n_time - 3));
+        L.oP = cv.take(sizeof(double) * 4 * (size_t)L.geo.grid);
+        L.bytes = cv.off;
+        return L;
+    }
     L.oB = cv.take(sizeof(cplx) * r * nc);
     L.oR = cv.take(sizeof(cplx) * r * 2 * nc);
     L.oBase = cv.take(sizeof(cplx) * nc);
@@ -390,8 +413,55 @@ SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool sp
     return L;
 }
 
+static int run_final(pq_ctx* ctx, const Plan& p, const double* partials, int count, cplx* perm, cplx* amp,
+                     hipStream_t st) {
+    FinalArgs fa;
+    fa.partials = partials;
+    fa.count = count;
+    fa.scale = p.scale;
+    fa.norm = p.norm;
+    fa.perm = perm;
+    fa.amp = amp;
+    return ctx->check(launch_final(fa, st), "final");
+}
+
+// The pair sweep's launches: table, sweep, final sum.
+static int run_pair(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, const cplx* U, int64_t ldu, cplx* perm,
+                    cplx* amp, hipStream_t st, bool timed) {
+    PairPrepArgs pa;
+    memset(&pa, 0, sizeof(pa));
+    pa.U = U;
+    pa.ldu = ldu;
+    pa.tab = (cplx*)(ws + L.oB);
+    pa.r = p.r;
+    pa.nc = p.nc;
+    pa.pairs = (p.nc + 1) / 2;
+    pa.transposed = p.transposed;
+    pa.n_lane = p.n_lane;
+    pa.n_outer = p.n_time - 3;
+    for (int i = 0; i < p.r; ++i) {
+        pa.row_mode[i] = p.row_mode[i];
+        pa.row_mu[i] = p.row_mu[i];
+    }
+    for (int j = 0; j < p.nc; ++j) pa.col_mode[j] = p.col_mode[j];
+    int rc = ctx->check(launch_pair_prep(pa, st), "pair table");
+    if (rc) return rc;
+    PairArgs a;
+    a.tab = pa.tab;
+    a.partials = (double*)(ws + L.oP);
+    a.blocks = p.time_states >> 3;
+    a.groups = (uint32_t)L.geo.grid;
+    a.n_lane = p.n_lane;
+    a.lane_states = p.lane_states;
+    a.n_outer = pa.n_outer;
+    rc = timed_sweep(ctx, timed, st, [&] { return launch_pair(p.nc, a, st); });
+    if (rc) return rc;
+    return run_final(ctx, p, a.partials, L.geo.grid, perm, amp, st);
+}
+
 int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, const cplx* U, int64_t ldu,
                   cplx* perm, cplx* amp, hipStream_t st, bool timed) {
+    if (L.kind == kSweepPair) return run_pair(ctx, p, L, ws, U, ldu, perm, amp, st, timed);
     const int r = p.r, nc = p.nc;
     PrepArgs pa;
     memset(&pa, 0, sizeof(pa));
@@ -440,18 +510,9 @@ int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, c
         rc = ctx->check(launch_table(ta, st), "table");
         if (rc) return rc;
     }
-    if (timed) rc = timed_sweep(ctx, sweep_kind(p), nc, ga, L.geo.grid, st);
-    else rc = ctx->check(launch_glynn(sweep_kind(p), nc, ga, L.geo.grid, st), "sweep");
+    rc = timed_sweep(ctx, timed, st, [&] { return launch_glynn(L.kind, nc, ga, L.geo.grid, st); });
     if (rc) return rc;
-
-    FinalArgs fa;
-    fa.partials = ga.partials;
-    fa.count = L.geo.grid;
-    fa.scale = p.scale;
-    fa.norm = p.norm;
-    fa.perm = perm;
-    fa.amp = amp;
-    return ctx->check(launch_final(fa, st), "final");
+    return run_final(ctx, p, ga.partials, L.geo.grid, perm, amp, st);
 }
 
 // Time the whole launch sequence of a plan under 2, 1 and 4 rounds of the
@@ -471,7 +532,7 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
     double best = -1.0;
     for (int rounds : {kSweepRounds, 1, 4}) {
         const int w = sweep_waves_per_cu(ctx, p, rounds);
-        const SingleLayout L = single_layout(ctx, p, w);
+        const SingleLayout L = single_layout(ctx, p, sweep_kind(p), w);
         char* ws = (char*)ctx->workspace(L.bytes);
         if (!ws) {
             rc = PQ_ENOMEM;
@@ -510,10 +571,10 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
 
 int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* perm, cplx* amp,
                hipStream_t st) {
-    if (fused_applies(ctx, p)) {
+    if (ctx->tickets && fused_applies(ctx, p)) {
         double* partials = (double*)ctx->workspace(fused_bytes(ctx, p));
         if (!partials) return PQ_ENOMEM;
-        return run_fused(ctx, p, partials, ctx->ticket, U, ldu, perm, amp, st, true);
+        return run_fused(ctx, p, partials, ctx->tickets, U, ldu, perm, amp, st, true);
     }
     int wpc = sweep_waves_per_cu(ctx, p);
     if (ctx->autotune) {
@@ -525,7 +586,7 @@ int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* per
             return rc;
         }
     }
-    const SingleLayout L = single_layout(ctx, p, wpc);
+    const SingleLayout L = single_layout(ctx, p, sweep_kind(p), wpc);
     char* ws = (char*)ctx->workspace(L.bytes);
     if (!ws) return PQ_ENOMEM;
     return run_single_at(ctx, p, L, ws, U, ldu, perm, amp, st, true);

@@ -46,9 +46,10 @@ struct pq_ctx {
     // device workspace, grown on demand (hipFree waits for earlier work)
     void* ws = nullptr;
     size_t ws_bytes = 0;
-    // one-launch permanents: the count of finished workgroups (device, zero
-    // between launches)
-    uint32_t* ticket = nullptr;
+    // one-launch permanents: counts of finished workgroups (lent, see
+    // take_tickets; without them permanents take the longer way)
+    uint32_t* tickets = nullptr;
+    uint32_t ticket_turn = 0;
     // cached many-pattern plans and their device descriptors (many.cpp)
     void* many_cache = nullptr;
     // pinned host staging for descriptor uploads; upload_done marks when the
@@ -57,7 +58,7 @@ struct pq_ctx {
     size_t stage_bytes = 0;
     hipEvent_t upload_done = nullptr;
     // resident workgroups per CU per (binary, nc); 0 = not yet queried
-    int occ[3][pq::kMaxDim + 1] = {};
+    int occ[4][pq::kMaxDim + 1] = {};
 
     // autotuning (pq_autotune_enable): chunk policies of pq_perm_many by
     // job-list shape signature and pq_perm's launch shapes by plan shape
@@ -176,9 +177,13 @@ struct Geometry {
 // the CUs that finish their first ones early, which evens out unequal CU and
 // XCD speeds that a single round leaves on the critical path.
 constexpr int kSweepRounds = 2;
+// Sweep kernel kind of a plan (see kernels.h).
+int sweep_kind(const Plan& p);
+// resident wavefronts per CU of that kernel
+int resident_waves(pq_ctx* ctx, const Plan& p, int kind);
 // rounds x the resident wavefronts per CU of the plan's sweep kernel
 int sweep_waves_per_cu(pq_ctx* ctx, const Plan& p, int rounds = kSweepRounds);
-Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread = true);
+Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread);
 // Shape signature of a single permanent's launch (kernel kind, sums, digits
 // and powers: n and the multiplicity class), for the autotuner's records.
 uint64_t single_sig(const Plan& p);
@@ -186,24 +191,22 @@ uint64_t single_sig(const Plan& p);
 // the plan's shape if there is one; otherwise the default.
 int single_waves_per_cu(pq_ctx* ctx, const Plan& p);
 
-// Launch a sweep, bracketed by timing events when profiling is on.
-int timed_sweep(pq_ctx* ctx, int kind, int nc, const GlynnArgs& a, int grid, hipStream_t st);
-
-// Device scratch of one permanent's launch sequence: compact matrix, +-2B
-// rows, base sums, the two step tables (mixed radices only) and the
-// workgroup partials, at 256-byte aligned offsets.
+// Device scratch of one permanent's launch sequence: compact matrix (or the
+// pair sweep's table), +-2B rows, base sums, the two step tables (mixed radices
+// only) and the workgroup partials, at 256-byte aligned offsets.
 struct SingleLayout {
     Geometry geo;
+    int kind = 0;
     size_t oB = 0, oR = 0, oBase = 0, oTf = 0, oTb = 0, oP = 0;
     size_t bytes = 0;
 };
-SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int waves_per_cu, bool spread = true);
+SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread = true);
 
 // One-launch permanents (k_fused_impl.h): whether a plan takes that form, its
 // scratch (the workgroups' sums), and the launch.
 bool fused_applies(pq_ctx* ctx, const Plan& p);
 size_t fused_bytes(pq_ctx* ctx, const Plan& p);
-int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* ticket, const cplx* U, int64_t ldu, cplx* perm,
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, const cplx* U, int64_t ldu, cplx* perm,
               cplx* amp, hipStream_t st, bool timed);
 
 // Full single-permanent sequence (prep, table, sweep, final) on the scratch
@@ -221,5 +224,10 @@ int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* per
 // Allocation-free entry point's set-up: resolve the device address of its
 // static scratch on the current device (once per device).  PQ_OK or an error.
 int noalloc_init(int device);
+
+// A set of kTickets device words that are zero between launches, for one ctx;
+// null when noalloc_init failed on this device or none is left.
+uint32_t* take_tickets(int device);
+void give_tickets(int device, uint32_t* tickets);
 
 }  // namespace pq
