@@ -54,18 +54,24 @@ __device__ __forceinline__ double shfl_xor_d(double v, int mask) {
     return __shfl_xor(v, mask, 64);
 }
 
-// Butterfly over the 64 lanes in a fixed order; lane 0 holds the result.
+// Sum over the 64 lanes in a fixed order, for lane 0.  After the first level the
+// lower half of the lanes goes on with the real parts, the upper with the
+// imaginary ones: half the work of reducing both in every lane, and the same
+// pairs added.
 __device__ __forceinline__ cdd wave_reduce(cdd v) {
+    const bool upper = (threadIdx.x & 32) != 0;
+    dd mine = upper ? v.im : v.re, other = upper ? v.re : v.im;
+    other.hi = shfl_xor_d(other.hi, 32);
+    other.lo = shfl_xor_d(other.lo, 32);
+    mine = dd_add(mine, other);
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        cdd o;
-        o.re.hi = shfl_xor_d(v.re.hi, m);
-        o.re.lo = shfl_xor_d(v.re.lo, m);
-        o.im.hi = shfl_xor_d(v.im.hi, m);
-        o.im.lo = shfl_xor_d(v.im.lo, m);
-        v = cdd_add(v, o);
+    for (int m = 16; m >= 1; m >>= 1) {
+        dd o;
+        o.hi = shfl_xor_d(mine.hi, m);
+        o.lo = shfl_xor_d(mine.lo, m);
+        mine = dd_add(mine, o);
     }
-    return v;
+    return cdd{mine, dd{shfl_xor_d(mine.hi, 32), shfl_xor_d(mine.lo, 32)}};
 }
 
 // Reduce one value per thread of a 256-thread workgroup and write the
