@@ -1,4 +1,4 @@
-// Small kernels around the forward sweep: gather of the compact matrix, the
+// Small kernels around the forward sweep: gather of the compact matrix with the
 // inner digits' step tables, the final double-double reduction, and a
 // constant fill for the trivial cases.
 #include <hip/hip_runtime.h>
@@ -10,29 +10,71 @@ namespace pq {
 
 // B[i][j] = U[out][in] for iterated row i and power column j; rows2 holds
 // -2B_i (a digit increment lowers delta_i by 2) and +2B_i; base_j = sum_i mu_i B_ij
-// (column sums with every digit at zero, delta_i = mu_i).
-__global__ __launch_bounds__(kBlock) void prep_kernel(const PrepArgs a) {
-    const int total = a.r * a.nc;
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-        const int i = e / a.nc, j = e % a.nc;
+// (column sums with every digit at zero, delta_i = mu_i).  For mixed digits
+// also the per-step table of the inner digits and the lanes' sums and weights,
+// by workgroups of their own.
+// Table, forward traversal: position q is the Gray state of rank q.  Reflected
+// traversal: position p is the state of rank M-1-p (the inner code run
+// backwards).  Entry p holds the row offset of the step from position p-1 to p
+// (digit up -> -2B row, down -> +2B row) and the signed binomial weight of state p.
+__global__ __launch_bounds__(kBlock) void prep_kernel(const PrepArgs a, const int nprep, const int ntab) {
+    auto at = [&](int i, int j) {
         const int out = a.transposed ? a.col_mode[j] : a.row_mode[i];
         const int in = a.transposed ? a.row_mode[i] : a.col_mode[j];
-        const cplx v = a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
+        return a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
+    };
+    if ((int)blockIdx.x >= nprep + ntab) {
+        const int e = ((int)blockIdx.x - nprep - ntab) * kBlock + (int)threadIdx.x;
+        const int j = e >> 6, lane = e & 63;
+        if (j > a.nc) return;
+        // digits of the lane: delta_i = mu_i - 2 d_i
+        int d[kMaxLaneDigits];
+        double w = lane < a.lane_states ? 1.0 : 0.0;
+        int rest = lane;
+#pragma unroll
+        for (int i = 0; i < kMaxLaneDigits; ++i) {
+            const int rho = i < a.n_lane ? a.lane_radix[i] : 1;
+            d[i] = rest % rho;
+            rest /= rho;
+            if (i < a.n_lane) w *= digit_weight(rho, d[i]);
+        }
+        if (j == a.nc) {
+            a.lane_w[lane] = w;
+            return;
+        }
+        cplx s{0.0, 0.0};
+#pragma unroll 8
+        for (int i = 0; i < a.r; ++i) cfma_to(s, (double)a.row_mu[i], at(i, j));
+#pragma unroll
+        for (int i = 0; i < kMaxLaneDigits; ++i)
+            if (i < a.n_lane) cfma_to(s, -2.0 * (double)d[i], at(i, j));
+        a.lane_sums[e] = s;
+        return;
+    }
+    if ((int)blockIdx.x >= nprep) {
+        const int q = ((int)blockIdx.x - nprep) * kBlock + (int)threadIdx.x;
+        if (q >= a.m_inner) return;
+        const GrayStep e = gray_step(a.n_inner, [&](int k) { return a.radix[k]; }, a.m_inner, q);
+        const int32_t of = (int32_t)((2 * e.fwd + (e.fwd_up ? 0 : 1)) * a.nc);
+        const int32_t ob = (int32_t)((2 * e.bwd + (e.bwd_up ? 0 : 1)) * a.nc);
+        a.tab_fwd[q] = StepEntry{q > 0 ? of : 0, 0, e.w};
+        a.tab_bwd[a.m_inner - 1 - q] = StepEntry{q < a.m_inner - 1 ? ob : 0, 0, e.w};
+        return;
+    }
+    const int total = a.r * a.nc;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += nprep * blockDim.x) {
+        const int i = e / a.nc, j = e % a.nc;
+        const cplx v = at(i, j);
         a.B[(size_t)i * a.nc + j] = v;
         a.rows2[((size_t)i * 2 + 0) * a.nc + j] = cplx{-2.0 * v.re, -2.0 * v.im};
         a.rows2[((size_t)i * 2 + 1) * a.nc + j] = cplx{2.0 * v.re, 2.0 * v.im};
     }
-    if (blockIdx.x == 0) {
+    if (blockIdx.x == 0 && a.m_inner == 0) {
         for (int j = threadIdx.x; j < a.nc; j += blockDim.x) {
-            double re = 0.0, im = 0.0;
-            for (int i = 0; i < a.r; ++i) {
-                const int out = a.transposed ? a.col_mode[j] : a.row_mode[i];
-                const int in = a.transposed ? a.row_mode[i] : a.col_mode[j];
-                const cplx v = a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
-                re = __builtin_fma((double)a.row_mu[i], v.re, re);
-                im = __builtin_fma((double)a.row_mu[i], v.im, im);
-            }
-            a.base[j] = cplx{re, im};
+            cplx s{0.0, 0.0};
+#pragma unroll 8
+            for (int i = 0; i < a.r; ++i) cfma_to(s, (double)a.row_mu[i], at(i, j));
+            a.base[j] = s;
         }
     }
 }
@@ -42,7 +84,9 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
     int grid = (total + kBlock - 1) / kBlock;
     if (grid < 1) grid = 1;
     if (grid > 64) grid = 64;
-    hipLaunchKernelGGL(prep_kernel, dim3(grid), dim3(kBlock), 0, s, a);
+    const int ntab = (a.m_inner + kBlock - 1) / kBlock;
+    const int nlane = a.m_inner > 0 ? (64 * (a.nc + 1) + kBlock - 1) / kBlock : 0;
+    hipLaunchKernelGGL(prep_kernel, dim3(grid + ntab + nlane), dim3(kBlock), 0, s, a, grid, ntab);
     return hipGetLastError();
 }
 
@@ -128,27 +172,6 @@ __global__ __launch_bounds__(64) void pair_prep_kernel(const PairPrepArgs a) {
 hipError_t launch_pair_prep(const PairPrepArgs& a, hipStream_t s) {
     const int n = a.pairs * (a.n_lane + 3 + a.n_outer);
     hipLaunchKernelGGL(pair_prep_kernel, dim3((n + 63) / 64), dim3(64), 0, s, a);
-    return hipGetLastError();
-}
-
-// Per-step table of the inner digits.  Forward traversal: position q is the
-// Gray state of rank q.  Reflected traversal: position p is the state of rank
-// M-1-p (the inner code run backwards).  Entry p holds the row offset of the
-// step from position p-1 to p (digit up -> -2B row, down -> +2B row) and the
-// signed binomial weight of state p.
-__global__ __launch_bounds__(kBlock) void table_kernel(const TableArgs a) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.m_inner) return;
-    const GrayStep e = gray_step(a.n_inner, [&](int k) { return a.radix[k]; }, a.m_inner, q);
-    const int32_t of = (int32_t)((2 * e.fwd + (e.fwd_up ? 0 : 1)) * a.nc);
-    const int32_t ob = (int32_t)((2 * e.bwd + (e.bwd_up ? 0 : 1)) * a.nc);
-    a.tab_fwd[q] = StepEntry{q > 0 ? of : 0, 0, e.w};
-    a.tab_bwd[a.m_inner - 1 - q] = StepEntry{q < a.m_inner - 1 ? ob : 0, 0, e.w};
-}
-
-hipError_t launch_table(const TableArgs& a, hipStream_t s) {
-    const int grid = (a.m_inner + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(table_kernel, dim3(grid), dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 

@@ -49,7 +49,6 @@ hipError_t launch_pair(int nc, const PairArgs& a, hipStream_t s);
 int occupancy_pair(int nc);
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
-hipError_t launch_table(const TableArgs& a, hipStream_t s);
 hipError_t launch_final(const FinalArgs& a, hipStream_t s);
 // Write `value` to perm[0] and amp[0] (either may be null).
 hipError_t launch_fill(cplx* perm, cplx* amp, cplx value, hipStream_t s);

@@ -112,9 +112,9 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     const int wpc = single_waves_per_cu(ctx, p);
     const int plain_wpc = std::max(1, wpc / resident_waves(ctx, p, kind)) * resident_waves(ctx, p, plain);
     SingleLayout L = single_layout(ctx, p, plain, plain == kind ? wpc : plain_wpc, false);
-    if (L.bytes > kNoAllocScratchBytes)
+    if (L.accept > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
-                         "bytes of the static buffer (use pq_perm)", L.bytes, kNoAllocScratchBytes);
+                         "bytes of the static buffer (use pq_perm)", L.accept, kNoAllocScratchBytes);
     if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
         return run_fused(ctx, p, (double*)ws, tickets, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
     const SingleLayout spread = single_layout(ctx, p, kind, wpc);

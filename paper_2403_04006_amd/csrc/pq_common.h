@@ -90,6 +90,11 @@ struct GlynnArgs {
     int32_t time_radix[kMaxDim];
     int32_t kap[kMaxDim]; // column powers (ascending)
     PowSteps pw;          // their structure for product_grouped
+    // mixed digits: column sums and weight of every lane's digits with the time
+    // digits at zero, and the inverses of the time radices (digit_inverse)
+    const cplx* lane_sums;    // [NC][64]
+    const double* lane_w;     // [64]
+    uint64_t time_inv[kMaxDim];
 };
 
 // Pair sweep (k_pair_impl.h).  Its table, in complex values for P pairs, W = 2 P
@@ -139,15 +144,16 @@ struct PrepArgs {
     int32_t row_mode[kMaxDim];   // iterated modes in digit order
     int32_t row_mu[kMaxDim];
     int32_t col_mode[kMaxDim];
-};
-
-// Table kernel arguments: the inner digits' Gray sequence.
-struct TableArgs {
+    // mixed digits: the inner digits' Gray sequence, and the lanes' sums and
+    // weights (GlynnArgs); m_inner 0 otherwise
     StepEntry* tab_fwd;
     StepEntry* tab_bwd;
+    cplx* lane_sums;
+    double* lane_w;
     int32_t n_inner;
     int32_t m_inner;
-    int32_t nc;                  // row length of the +-2B table
+    int32_t n_lane, lane_states;
+    int32_t lane_radix[kMaxLaneDigits];
     int32_t radix[16];
 };
 
@@ -266,6 +272,29 @@ PQ_HD int gray_digits_desc(int d, Radix radix, uint64_t rank, int parity_in, F&&
         f(k, g);
     }
     return par;
+}
+
+// Quotients by a radix rho of 2..49 through its inverse, exact below 2^58 (the
+// error of the inverse, less than rho / 2^64, stays below 1 / rho).
+inline uint64_t digit_inverse(uint32_t rho) { return ~(uint64_t)0 / rho + 1; }
+
+// The same digits from digit 0 up: a digit runs downward where the quotient by
+// the radices up to it is odd (every step moves one digit by one, so a digit
+// sum's parity is its rank's).  On scalar registers alone, where
+// gray_digits_desc takes some 25 vector instructions a digit.
+template <class Radix, class Inv, class F>
+PQ_HD void gray_digits_asc(int d, Radix radix, Inv inv, uint64_t rank, F&& f) {
+    for (int k = 0; k < d; ++k) {
+        const uint32_t rk = (uint32_t)radix(k);
+#if defined(__HIP_DEVICE_COMPILE__)
+        const uint64_t q = __umul64hi(rank, inv(k));
+#else
+        const uint64_t q = (uint64_t)(((unsigned __int128)rank * inv(k)) >> 64);
+#endif
+        const int a = (int)((uint32_t)rank - (uint32_t)q * rk);
+        f(k, (q & 1) ? (int)rk - 1 - a : a);
+        rank = q;
+    }
 }
 
 // C(a, b) for small non-negative integers, exact in double (a <= 48).

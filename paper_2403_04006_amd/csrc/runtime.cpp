@@ -204,8 +204,9 @@ namespace pq {
 // sums are rebuilt from the digits, about (digits x NC) multiply-adds).
 static constexpr uint64_t kMinStepsPerWave = 32;
 // and in a sweep that leaves the device part empty at that share, where a
-// wavefront more costs nothing else: 34 photons in 17 modes 49 -> 45 us
-static constexpr uint64_t kSpreadSteps = 8;
+// wavefront more costs nothing else: 34 photons in 17 modes 36 us at 16, 34 at 8
+// and 4; 48 photons in 6 modes 27.8, 20.0 and 16.9
+static constexpr uint64_t kSpreadSteps = 4;
 
 // The pair sweep from 2^18 time states on: 25 photons 108 -> 88 us, 26 187 -> 153
 // (24 photons in one launch 53, by pairs 51, 23 35 and 38).  Beyond 32 columns two
@@ -327,12 +328,13 @@ static int timed_sweep(pq_ctx* ctx, bool timed, hipStream_t st, F launch) {
 // Time states up to which a permanent takes one launch, and its wavefronts'
 // least share of them (two workgroups per CU at most).  Whole calls, several
 // launches -> one: 8 photons 19.2 -> 13.3 us, 16 20.9 -> 15.2, 20 24.0 -> 16.5, 22
-// 33.4 -> 25.0, 24 (2^17 states) 59.5 -> 53.0; 2 x 9 rows 23.0 -> 13.7, 2 x 11 25.2 ->
-// 16.5; but 34 photons in 17 modes (59,049 states) 45.5 -> 52, where the step
-// table of the longer sweep is the cheaper step.  Shares of 4, 8 and 16 states: 20
+// 33.4 -> 25.0, 24 (2^17 states) 59.5 -> 53.0; 2 x 9 rows 19.7 -> 13.2, 2 x 11 19.9 ->
+// 15.9, 2 x 12 (6,561 states) 20.0 -> 20.4; but 27 photons in 17 modes (13,824) 20.6
+// -> 23.8, 2 x 13 (19,683) 21.6 -> 27.6, where the step table of the longer sweep
+// is the cheaper step.  Shares of 4, 8 and 16 states: 20
 // photons 19.4, 16.5, 16.3 us; 2 x 9 rows 13.7, 16.7, 21.8.
 constexpr uint64_t kFusedMaxBinary = 1 << 17;
-constexpr uint64_t kFusedMaxMixed = 1 << 15;
+constexpr uint64_t kFusedMaxMixed = 1 << 13;
 constexpr uint64_t kFusedSteps = 8;
 constexpr uint64_t kFusedStepsMixed = 4;
 
@@ -409,6 +411,12 @@ SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_c
     L.oTf = cv.take(sizeof(StepEntry) * ntab);
     L.oTb = cv.take(sizeof(StepEntry) * ntab);
     L.oP = cv.take(sizeof(double) * 4 * (size_t)L.geo.grid);
+    // (what pq_perm_noalloc accepts was settled without the lanes' sums)
+    L.accept = cv.off;
+    if (!p.binary) {
+        L.oL = cv.take(sizeof(cplx) * 64 * (size_t)nc);
+        L.oLw = cv.take(sizeof(double) * 64);
+    }
     L.bytes = cv.off;
     return L;
 }
@@ -475,6 +483,18 @@ int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, c
     pa.transposed = p.transposed;
     for (int i = 0; i < r; ++i) { pa.row_mode[i] = p.row_mode[i]; pa.row_mu[i] = p.row_mu[i]; }
     for (int j = 0; j < nc; ++j) pa.col_mode[j] = p.col_mode[j];
+    if (!p.binary) {
+        pa.tab_fwd = (StepEntry*)(ws + L.oTf);
+        pa.tab_bwd = (StepEntry*)(ws + L.oTb);
+        pa.lane_sums = (cplx*)(ws + L.oL);
+        pa.lane_w = (double*)(ws + L.oLw);
+        pa.n_inner = p.n_inner;
+        pa.m_inner = p.m_inner;
+        pa.n_lane = p.n_lane;
+        pa.lane_states = p.lane_states;
+        for (int k = 0; k < p.n_lane; ++k) pa.lane_radix[k] = p.lane_radix[k];
+        for (int k = 0; k < p.n_inner; ++k) pa.radix[k] = p.time_radix[k];
+    }
     int rc = ctx->check(launch_prep(pa, st), "prep");
     if (rc) return rc;
 
@@ -494,22 +514,15 @@ int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, c
     ga.n_inner = p.n_inner;
     ga.m_inner = p.m_inner;
     for (int k = 0; k < p.n_lane; ++k) ga.lane_radix[k] = p.lane_radix[k];
-    for (int k = 0; k < p.n_time; ++k) ga.time_radix[k] = p.time_radix[k];
+    for (int k = 0; k < p.n_time; ++k) {
+        ga.time_radix[k] = p.time_radix[k];
+        ga.time_inv[k] = digit_inverse((uint32_t)p.time_radix[k]);
+    }
+    ga.lane_sums = pa.lane_sums;
+    ga.lane_w = pa.lane_w;
     for (int j = 0; j < nc; ++j) ga.kap[j] = p.col_kap[j];
     make_pow_steps(ga.kap, nc, ga.pw);
 
-    if (!p.binary) {
-        TableArgs ta;
-        memset(&ta, 0, sizeof(ta));
-        ta.tab_fwd = (StepEntry*)(ws + L.oTf);
-        ta.tab_bwd = (StepEntry*)(ws + L.oTb);
-        ta.n_inner = p.n_inner;
-        ta.m_inner = p.m_inner;
-        ta.nc = nc;
-        for (int k = 0; k < p.n_inner; ++k) ta.radix[k] = p.time_radix[k];
-        rc = ctx->check(launch_table(ta, st), "table");
-        if (rc) return rc;
-    }
     rc = timed_sweep(ctx, timed, st, [&] { return launch_glynn(L.kind, nc, ga, L.geo.grid, st); });
     if (rc) return rc;
     return run_final(ctx, p, ga.partials, L.geo.grid, perm, amp, st);

@@ -193,12 +193,14 @@ int single_waves_per_cu(pq_ctx* ctx, const Plan& p);
 
 // Device scratch of one permanent's launch sequence: compact matrix (or the
 // pair sweep's table), +-2B rows, base sums, the two step tables (mixed radices
-// only) and the workgroup partials, at 256-byte aligned offsets.
+// only), the workgroup partials and the lanes' sums and weights (mixed radices
+// only), at 256-byte aligned offsets.
 struct SingleLayout {
     Geometry geo;
     int kind = 0;
-    size_t oB = 0, oR = 0, oBase = 0, oTf = 0, oTb = 0, oP = 0;
+    size_t oB = 0, oR = 0, oBase = 0, oTf = 0, oTb = 0, oP = 0, oL = 0, oLw = 0;
     size_t bytes = 0;
+    size_t accept = 0;   // without the lanes' sums: what pq_perm_noalloc measures
 };
 SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread = true);
 
