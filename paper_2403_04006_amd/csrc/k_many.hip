@@ -229,38 +229,28 @@ hipError_t launch_queue_prep(const QueuePrepArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-typedef hipError_t (*qlaunch_fn)(int, const QueueArgs&, int, hipStream_t);
-typedef hipError_t (*qocc_fn)(int, int*);
-#define PQ_QPTR_L(MODE, NC) &launch_queue_##MODE##_##NC,
-#define PQ_QPTR_O(MODE, NC) &occupancy_queue_##MODE##_##NC,
-static const qlaunch_fn g_q_fwd[] = {PQ_MCLASS_FWD(PQ_QPTR_L)};
-static const qlaunch_fn g_q_ext[] = {PQ_MCLASS_EXT(PQ_QPTR_L)};
-static const qocc_fn g_qo_fwd[] = {PQ_MCLASS_FWD(PQ_QPTR_O)};
-static const qocc_fn g_qo_ext[] = {PQ_MCLASS_EXT(PQ_QPTR_O)};
-
 hipError_t launch_queue(int mode, int ncmax, int var, const QueueArgs& q, int grid, hipStream_t s) {
-    const int k = ncmax / 4 - 1;
-    if (ncmax % 4 || k < 0) return hipErrorInvalidValue;
-    if (mode == kModeFwd && k < (int)(sizeof(g_q_fwd) / sizeof(g_q_fwd[0]))) return g_q_fwd[k](var, q, grid, s);
-    if (mode == kModeExt && k < (int)(sizeof(g_q_ext) / sizeof(g_q_ext[0]))) return g_q_ext[k](var, q, grid, s);
-    return hipErrorInvalidValue;
+    switch (mode * 64 + ncmax) {
+#define PQ_QCASE(MODE, NC) case MODE * 64 + NC: return launch_queue_##MODE##_##NC(var, q, grid, s);
+        PQ_MCLASS_FWD(PQ_QCASE)
+        PQ_MCLASS_EXT(PQ_QCASE)
+#undef PQ_QCASE
+        default: return hipErrorInvalidValue;
+    }
 }
 
 int occupancy_queue(int mode, int ncmax, int var) {
-    const int k = ncmax / 4 - 1;
-    if (ncmax % 4 || k < 0) return 0;
     int blocks = 0;
     hipError_t e = hipErrorInvalidValue;
-    if (mode == kModeFwd && k < (int)(sizeof(g_qo_fwd) / sizeof(g_qo_fwd[0]))) e = g_qo_fwd[k](var, &blocks);
-    if (mode == kModeExt && k < (int)(sizeof(g_qo_ext) / sizeof(g_qo_ext[0]))) e = g_qo_ext[k](var, &blocks);
+    switch (mode * 64 + ncmax) {
+#define PQ_QCASE(MODE, NC) case MODE * 64 + NC: e = occupancy_queue_##MODE##_##NC(var, &blocks); break;
+        PQ_MCLASS_FWD(PQ_QCASE)
+        PQ_MCLASS_EXT(PQ_QCASE)
+#undef PQ_QCASE
+        default: break;
+    }
     return e == hipSuccess ? blocks : 0;
 }
-
-typedef hipError_t (*mlaunch_fn)(int, const ManyArgs&, hipStream_t);
-#define PQ_MPTR(MODE, NC) &launch_many_##MODE##_##NC,
-static const mlaunch_fn g_m_fwd[] = {PQ_MCLASS_FWD(PQ_MPTR)};
-static const mlaunch_fn g_m_ext[] = {PQ_MCLASS_EXT(PQ_MPTR)};
-static const mlaunch_fn g_m_adj[] = {PQ_MCLASS_ADJ(PQ_MPTR)};
 
 hipError_t launch_many(int mode, int ncmax, int var, const ManyArgs& a, hipStream_t s) {
     if (mode == kModeExtCol) {
@@ -271,20 +261,22 @@ hipError_t launch_many(int mode, int ncmax, int var, const ManyArgs& a, hipStrea
             default: return hipErrorInvalidValue;
         }
     }
-    const int k = ncmax / 4 - 1;
-    if (ncmax % 4 || k < 0) return hipErrorInvalidValue;
-    if (mode == 0 && k < (int)(sizeof(g_m_fwd) / sizeof(g_m_fwd[0]))) return g_m_fwd[k](var, a, s);
-    if (mode == 1 && k < (int)(sizeof(g_m_ext) / sizeof(g_m_ext[0]))) return g_m_ext[k](var, a, s);
-    if (mode == 2 && k < (int)(sizeof(g_m_adj) / sizeof(g_m_adj[0]))) return g_m_adj[k](var, a, s);
     if (mode == kModeAdjWalk) {
         switch (ncmax) {
 #define PQ_WCASE(NC) case NC: return launch_adjw_##NC(var, a, s);
             PQ_WCLASS(PQ_WCASE)
 #undef PQ_WCASE
-            default: break;
+            default: return hipErrorInvalidValue;
         }
     }
-    return hipErrorInvalidValue;
+    switch (mode * 64 + ncmax) {
+#define PQ_MCASE(MODE, NC) case MODE * 64 + NC: return launch_many_##MODE##_##NC(var, a, s);
+        PQ_MCLASS_FWD(PQ_MCASE)
+        PQ_MCLASS_EXT(PQ_MCASE)
+        PQ_MCLASS_ADJ(PQ_MCASE)
+#undef PQ_MCASE
+        default: return hipErrorInvalidValue;
+    }
 }
 
 int occupancy_walk(int ncmax, int variant) {

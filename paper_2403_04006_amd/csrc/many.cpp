@@ -50,6 +50,10 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
                   kTuneCandidates[0].chunks_per_wave == ChunkPolicy().chunks_per_wave &&
                   kTuneCandidates[0].min_chunk == ChunkPolicy().min_chunk,
               "the first candidate is the default policy");
+// From this many time states on, a forward job of 13..22 columns is padded to an
+// even number of them instead of a multiple of four: two columns less are a
+// tenth of its work, where a class more is one more launch and its uneven end.
+constexpr uint64_t kEvenClassStates = 1 << 18;
 // From this many extend-row jobs on, their final step reads U transposed (one
 // launch more; 19,000 jobs on 400 modes: 230 us of final step before).
 constexpr int kTransposeMinJobs = 512;
@@ -292,6 +296,8 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
             continue;
         }
         int ncmax = ((p.nc + 3) / 4) * 4;
+        // a long sweep takes the even class that holds it
+        if (!ext && !adj && p.time_states >= kEvenClassStates && p.nc > 12 && p.nc <= 22) ncmax = ((p.nc + 1) / 2) * 2;
         if (ext && ncmax > kMaxExtendCols) return ctx->fail(PQ_ERANGE, "pattern %zu: more than %d columns", k, kMaxExtendCols);
         bool extcol = false;
         if (ext) {

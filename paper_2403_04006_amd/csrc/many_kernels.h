@@ -6,8 +6,8 @@
 
 namespace pq {
 
-#define PQ_MCLASS_FWD(X) X(0, 4) X(0, 8) X(0, 12) X(0, 16) X(0, 20) X(0, 24) X(0, 28) X(0, 32) \
-    X(0, 36) X(0, 40) X(0, 44) X(0, 48)
+#define PQ_MCLASS_FWD(X) X(0, 4) X(0, 8) X(0, 12) X(0, 14) X(0, 16) X(0, 18) X(0, 20) X(0, 22) X(0, 24) \
+    X(0, 28) X(0, 32) X(0, 36) X(0, 40) X(0, 44) X(0, 48)
 #define PQ_MCLASS_EXT(X) X(1, 4) X(1, 8) X(1, 12) X(1, 16) X(1, 20) X(1, 24)
 #define PQ_MCLASS_ADJ(X) X(2, 4) X(2, 8) X(2, 12) X(2, 16) X(2, 20) X(2, 24)
 // reverse-sweep walk classes (binary digits, unit powers), padded column counts
