@@ -48,6 +48,9 @@ constexpr int kHafMaxLane = 7;     // lane digits (six of radix >= 2 and a radix
 constexpr int kHafMaxN = 64;       // vertices (photons)
 constexpr int kHafInner = 2048;    // inner (table-driven) Gray block
 constexpr uint64_t kHafMinChunk = 256;   // time states per wavefront, at least, in a sweep that fills the device
+// with loops, whose steps cost more: 18 doubled modes 1185 us at 256 (one round),
+// 1135 at 128, 64 and 32 (three and four); without them 349, 359, 399 and 399
+constexpr uint64_t kHafMinChunkLoops = 64;
 // In one that does not, a share of fewer states still pays for its wavefront's
 // set-up (loop-free and loop steps).  Twice as many or twice as few were slower or
 // level: 10, 12 and 14 doubled modes at 4, 8, 16 and 64 states took 18, 27, 48 /
@@ -56,7 +59,7 @@ constexpr uint64_t kHafMinChunk = 256;   // time states per wavefront, at least,
 constexpr uint64_t kHafSpread = 8;
 constexpr uint64_t kHafSpreadLoops = 4;
 // A hafnian sweep splits its steps evenly over this many rounds of the
-// resident wavefronts (each at least kHafMinChunk states): later rounds go to
+// resident wavefronts (each at least the share above): later rounds go to
 // the CUs that finish first.  On 2 x 20 modes 1, 2, 4, 8 and 16 rounds took
 // 2.87, 2.78, 2.72, 2.77 and 2.82 ms (the loop hafnian 10.5, 9.7, 9.2, 9.1
 // and 9.1 ms).
