@@ -91,19 +91,36 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
 }
 
 // The pair sweep's table (layout at PairArgs): one thread per pair of columns and
-// digit row; row 0 also takes the pair's sums and constants.
-__global__ __launch_bounds__(64) void pair_prep_kernel(const PairPrepArgs a) {
+// digit row (row 0 also takes the pair's constants), then one wavefront per
+// column for the column sums, each lane a row.
+__global__ __launch_bounds__(64) void pair_prep_kernel(const PairPrepArgs a, const int main_blocks) {
     const int P = a.pairs, W = 2 * P;
     const int e = blockIdx.x * 64 + (int)threadIdx.x;
     const int i = e / P, p = e - i * P;
     const int n_rows = a.n_lane + 3 + a.n_outer;
-    if (i >= n_rows) return;
     auto at = [&](int row, int col) {
         if (col >= a.nc) return cplx{0.0, 0.0};
         const int out = a.transposed ? a.col_mode[col] : a.row_mode[row];
         const int in = a.transposed ? a.row_mode[row] : a.col_mode[col];
         return a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
     };
+    if ((int)blockIdx.x >= main_blocks) {
+        const int col = (int)blockIdx.x - main_blocks, row = (int)threadIdx.x;
+        cplx s{0.0, 0.0};
+        if (row < a.r) {
+            // the middle of a low digit is one unit of its row below digit zero
+            const bool low = row >= a.n_lane && row < a.n_lane + 3;
+            cfma_to(s, (double)(a.row_mu[row] - (low ? 1 : 0)), at(row, col));
+        }
+#pragma unroll
+        for (int h = 32; h >= 1; h >>= 1) {
+            s.re += shfl_xor_d(s.re, h);
+            s.im += shfl_xor_d(s.im, h);
+        }
+        if (row == 0) a.tab[col] = col < a.nc ? s : cplx{1.0, 0.0};
+        return;
+    }
+    if (i >= n_rows) return;
     cplx* lrow = a.tab + W;
     cplx* prod = lrow + kMaxLaneDigits * W;
     cplx* dev = prod + 4 * P;
@@ -154,24 +171,13 @@ __global__ __launch_bounds__(64) void pair_prep_kernel(const PairPrepArgs a) {
             dev[8 * p + 2 * k] = ak[k];
             dev[8 * p + 2 * k + 1] = bk[k];
         }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int col = 2 * p + h;
-            cplx s{col < a.nc ? 0.0 : 1.0, 0.0};
-#pragma unroll 8
-            for (int row = 0; row < a.r; ++row) {
-                // the middle of a low digit is one unit of its row below digit zero
-                const bool low = row >= a.n_lane && row < a.n_lane + 3;
-                cfma_to(s, (double)(a.row_mu[row] - (low ? 1 : 0)), at(row, col));
-            }
-            a.tab[col] = s;
-        }
     }
 }
 
 hipError_t launch_pair_prep(const PairPrepArgs& a, hipStream_t s) {
-    const int n = a.pairs * (a.n_lane + 3 + a.n_outer);
-    hipLaunchKernelGGL(pair_prep_kernel, dim3((n + 63) / 64), dim3(64), 0, s, a);
+    if (a.r > 64) return hipErrorInvalidValue;
+    const int blocks = (a.pairs * (a.n_lane + 3 + a.n_outer) + 63) / 64;
+    hipLaunchKernelGGL(pair_prep_kernel, dim3(blocks + 2 * a.pairs), dim3(64), 0, s, a, blocks);
     return hipGetLastError();
 }
 

@@ -23,7 +23,7 @@
 //
 // Bound by FP64 issue at the clock that the card's power allows under it: 30
 // photons 1052 FP64 instructions a block of eight terms and lane (1,480 one by
-// one), 2.89 -> 2.29 ms; 28 photons 698 -> 543 us; 32 photons 13.0 -> 9.6 ms.
+// one), 2.86 -> 2.26 ms; 28 photons 698 -> 540 us; 32 photons 13.0 -> 9.7 ms.
 // Exchanging through a ring of four blocks with counters instead of a barrier
 // was no faster (2.33 ms at 30).
 #pragma once

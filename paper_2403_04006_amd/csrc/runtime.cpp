@@ -208,8 +208,7 @@ static constexpr uint64_t kMinStepsPerWave = 32;
 // and 4; 48 photons in 6 modes 27.8, 20.0 and 16.9
 static constexpr uint64_t kSpreadSteps = 4;
 
-// The pair sweep from 2^18 time states on: 25 photons 108 -> 88 us, 26 187 -> 153
-// (24 photons in one launch 53, by pairs 51, 23 35 and 38).  Beyond 32 columns two
+// The pair sweep from 2^18 time states on: 25 photons 108 -> 80 us, 26 187 -> 144.  Beyond 32 columns two
 // wavefronts' registers do not hold the pairs.
 static constexpr int kPairTimeDigits = 18;
 // Its workgroups: one round of the resident ones, and one for every
