@@ -113,11 +113,11 @@ def flops_per_term(n: int) -> int:
 
 
 def executed_flops_per_term(n: int) -> float:
-    """FP64 flops a term that the sweep kernel executes.  From 25 to 32 columns
+    """FP64 flops a term that the sweep kernel executes.  From 23 to 32 columns
     the pair sweep takes eight terms at a time over p pairs of columns: 36 adds
     and one complex multiply a pair, p - 2 multiplies and one multiply-add a
     term, 6 to accumulate; otherwise the one-by-one walk's count."""
-    if not 25 <= n <= 32:
+    if not 23 <= n <= 32:
         return float(flops_per_term(n))
     p = (n + 1) // 2
     return (p * 42 + 8 * (6 * (p - 2) + 8) + 6) / 8
@@ -649,7 +649,7 @@ def main() -> int:
             "unit": "TFLOP/s",
             "frac": achieved_tflops / FP64_VECTOR_PEAK_TFLOPS,
             "traffic": sweep_traffic_bytes(n),
-            "kernel": f"pair_kernel<{(n + 3) // 4}, {(n + 1) // 4}>" if 25 <= n <= 32 else f"glynn_bin<{n}>",
+            "kernel": f"pair_kernel<{(n + 3) // 4}, {(n + 1) // 4}>" if 23 <= n <= 32 else f"glynn_bin<{n}>",
             "flops_per_launch": executed_flops,
             # of the walk that takes one term at a time
             "one_by_one_flops": algo_flops,

@@ -38,8 +38,8 @@ PQ_FCLASS(PQ_FDECL)
 hipError_t launch_fused(bool mix, const FusedArgs& a, int grid, hipStream_t s);
 
 // Long binary sweeps by pairs of columns (padded to an even number).
-constexpr int kPairMinCols = 25, kPairMaxCols = 32;
-#define PQ_PCLASS(X) X(13) X(14) X(15) X(16)
+constexpr int kPairMinCols = 23, kPairMaxCols = 32;
+#define PQ_PCLASS(X) X(12) X(13) X(14) X(15) X(16)
 #define PQ_PDECL(P) hipError_t launch_pair_##P(const PairArgs& a, hipStream_t s); int occupancy_pair_##P();
 PQ_PCLASS(PQ_PDECL)
 #undef PQ_PDECL

@@ -28,9 +28,9 @@ def value(eng, U, S, T):
     return complex(perm.item()), complex(amp.item())
 
 
-@pytest.mark.parametrize("n", [24, 25, 26])
+@pytest.mark.parametrize("n", [22, 23, 24, 25, 26])
 def test_against_oracle(eng, n):
-    # 24: the last below the range; 25, 26: 13 pairs with and without padding
+    # 22: the last below the range; 23 to 26: 12 and 13 pairs with and without padding
     A = workloads.collision_free_block(n, 40 + n)
     U = torch.from_numpy(A).cuda()
     got, amp = value(eng, U, [1] * n, [1] * n)
