@@ -143,11 +143,12 @@ int pq_perm(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  * forbid allocation.  Same arguments, planning, errors and results as
  * pq_perm (the same kernels in the same launch geometry: the default, or
  * the autotuner's recorded decision for the shape), but the launch
- * sequence's scratch (compact matrix, +-2B rows, step tables, workgroup
- * partials) is a static device array of PQ_NOALLOC_SCRATCH_BYTES per GPU,
- * resolved by pq_create; the call itself allocates nothing (no hipMalloc,
- * hipFree or allocating library routine) and records no profiling events.
- *   - A permanent whose launch needs more scratch than that returns
+ * sequence's scratch is a static device array per GPU, resolved by
+ * pq_create; the call itself allocates nothing (no hipMalloc, hipFree or
+ * allocating library routine) and records no profiling events.
+ *   - A permanent whose sweep by single columns would need more than
+ *     PQ_NOALLOC_SCRATCH_BYTES (compact matrix, +-2B rows, step tables,
+ *     workgroup partials) returns
  *     PQ_ERANGE (outputs untouched); pq_perm handles it.  Under the default
  *     launch shape every binary (collision-free) permanent up to n = 48
  *     fits; large mixed-radix ones with 4096-state step tables and 40

@@ -150,9 +150,9 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const FusedArgs a) {
     for (int x = 1; x < kWavesPerBlock; ++x) s = cdd_add(s, cdd{{sred[x][0], sred[x][1]}, {sred[x][2], sred[x][3]}});
     if (gridDim.x > 1) {
         // every workgroup's sum, then its ticket; the last one sees them all.
-        // It leaves every counter at zero; consecutive calls take turns through
-        // them, so that what calls racing against the rules leave in one does
-        // not reach beyond the next call.
+        // Consecutive calls take turns through the counters, and the last
+        // workgroup clears its own and the one two turns on: even two calls
+        // racing against the rules leave nothing behind for later ones.
         if (tid == 0) {
             double* o = a.partials + 4 * (size_t)blockIdx.x;
             __hip_atomic_store(o, s.re.hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const FusedArgs a) {
         __syncthreads();
         s = cdd{{sred[0][0], sred[0][1]}, {sred[0][2], sred[0][3]}};
         for (int x = 1; x < kWavesPerBlock; ++x) s = cdd_add(s, cdd{{sred[x][0], sred[x][1]}, {sred[x][2], sred[x][3]}});
-        if (tid < kTickets) __hip_atomic_store(a.tickets + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid < 2) __hip_atomic_store(a.tickets + (a.turn + 2 * tid) % kTickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (tid == 0) {
         const double re = (s.re.hi + s.re.lo) * a.scale;

@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -32,6 +33,8 @@ constexpr int kTicketSets = 1024;
 static __device__ uint32_t ticket_sets[kTicketSets][kTickets];
 
 static std::mutex g_scratch_mu;
+// turns through the first set, over every ctx
+static std::atomic<uint32_t> g_noalloc_turn{0};
 static std::vector<bool> g_sets_taken[kNoAllocMaxDevices];
 static char* g_scratch_dev[kNoAllocMaxDevices] = {};
 static uint32_t* g_tickets_dev[kNoAllocMaxDevices] = {};
@@ -115,8 +118,8 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     if (L.accept > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
                          "bytes of the static buffer (use pq_perm)", L.accept, kNoAllocScratchBytes);
-    if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
-        return run_fused(ctx, p, (double*)ws, tickets, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
+    if (ctx->tickets && fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
+        return run_fused(ctx, p, (double*)ws, tickets, g_noalloc_turn.fetch_add(1), (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
     const SingleLayout spread = single_layout(ctx, p, kind, wpc);
     if (spread.bytes <= kNoAllocBufferBytes) L = spread;
     return run_single_at(ctx, p, L, ws, (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);

@@ -358,7 +358,7 @@ size_t fused_bytes(pq_ctx* ctx, const Plan& p) {
     return sizeof(double) * 4 * (size_t)((fused_waves(ctx, p) + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, const cplx* U, int64_t ldu, cplx* perm,
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, uint32_t turn, const cplx* U, int64_t ldu, cplx* perm,
               cplx* amp, hipStream_t st, bool timed) {
     FusedArgs a;
     memset(&a, 0, sizeof(a));
@@ -370,7 +370,7 @@ int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, c
     a.norm = p.norm;
     a.partials = partials;
     a.tickets = tickets;
-    a.turn = ctx->ticket_turn++ % kTickets;
+    a.turn = turn % kTickets;
     a.time_states = (uint32_t)p.time_states;
     a.waves = fused_waves(ctx, p);
     a.r = p.r;
@@ -589,7 +589,7 @@ int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* per
     if (ctx->tickets && fused_applies(ctx, p)) {
         double* partials = (double*)ctx->workspace(fused_bytes(ctx, p));
         if (!partials) return PQ_ENOMEM;
-        return run_fused(ctx, p, partials, ctx->tickets, U, ldu, perm, amp, st, true);
+        return run_fused(ctx, p, partials, ctx->tickets, ctx->ticket_turn++, U, ldu, perm, amp, st, true);
     }
     int wpc = sweep_waves_per_cu(ctx, p);
     if (ctx->autotune) {

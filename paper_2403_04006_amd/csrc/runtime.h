@@ -208,7 +208,7 @@ SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_c
 // scratch (the workgroups' sums), and the launch.
 bool fused_applies(pq_ctx* ctx, const Plan& p);
 size_t fused_bytes(pq_ctx* ctx, const Plan& p);
-int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, const cplx* U, int64_t ldu, cplx* perm,
+int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, uint32_t turn, const cplx* U, int64_t ldu, cplx* perm,
               cplx* amp, hipStream_t st, bool timed);
 
 // Full single-permanent sequence (prep, table, sweep, final) on the scratch
