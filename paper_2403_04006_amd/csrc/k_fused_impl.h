@@ -12,9 +12,10 @@
 // 1; so the weight follows from the product over the digits above, which lane k
 // keeps for digit k.
 //
-// Bound by latency: the launch, one round of loads of U, a start-up of r rows'
-// additions (as long as seven steps at 20 rows) and the ticket.  20 photons take
-// 16.5 us a call, of which the host's part is 12 (24 us with three launches).
+// Bound by the host's part of a call up to 20 photons (16 us at 40 modes; 24 with
+// three launches), beyond by latency: the launch, one round of loads of U, a
+// start-up of r rows' additions (as long as seven steps at 20 rows) and the
+// ticket.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -37,13 +38,13 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const FusedArgs a) {
     const int tid = (int)threadIdx.x, lane = tid & 63;
     for (int e = tid; e < a.r * W; e += kBlock) {
         const int i = e / W, j = e - i * W;
-        cplx v{0.0, 0.0};
-        if (j < a.nc) {
-            const int out = a.transposed ? a.col_mode[j] : a.row_mode[i];
-            const int in = a.transposed ? a.row_mode[i] : a.col_mode[j];
-            v = a.U[(size_t)out * (size_t)a.ldu + (size_t)in];
-        }
-        rows[e] = v;
+        // (the padding by selects on the values: on the address, it would go
+        // through scratch memory)
+        const int out = a.transposed ? a.col_mode[j] : a.row_mode[i];
+        const int in = a.transposed ? a.row_mode[i] : a.col_mode[j];
+        const bool on = j < a.nc;
+        const cplx u = a.U[on ? (size_t)out * (size_t)a.ldu + (size_t)in : 0];
+        rows[e] = cplx{on ? u.re : 0.0, on ? u.im : 0.0};
     }
     __syncthreads();
     const uint32_t wave = wave_id_uniform();
