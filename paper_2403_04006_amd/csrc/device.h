@@ -27,6 +27,14 @@ __device__ __forceinline__ void cfma_to(cplx& acc, double w, const cplx& b) {
     acc.im = __builtin_fma(w, b.im, acc.im);
 }
 
+// acc += a * b (complex, four fused multiply-adds)
+__device__ __forceinline__ void cmadd(cplx& acc, const cplx& a, const cplx& b) {
+    acc.re = __builtin_fma(a.re, b.re, acc.re);
+    acc.re = __builtin_fma(-a.im, b.im, acc.re);
+    acc.im = __builtin_fma(a.re, b.im, acc.im);
+    acc.im = __builtin_fma(a.im, b.re, acc.im);
+}
+
 // ---------------------------------------------------------- double-double
 struct dd { double hi, lo; };
 

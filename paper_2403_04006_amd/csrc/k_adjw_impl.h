@@ -71,14 +71,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// acc += a * b (complex, four fused multiply-adds)
-__device__ __forceinline__ void cmul_add_to(cplx& acc, const cplx& a, const cplx& b) {
-    acc.re = __builtin_fma(a.re, b.re, acc.re);
-    acc.re = __builtin_fma(-a.im, b.im, acc.re);
-    acc.im = __builtin_fma(a.re, b.im, acc.im);
-    acc.im = __builtin_fma(a.im, b.re, acc.im);
-}
-
 template <int B>
 __device__ __forceinline__ void walk_term(const cplx (&c)[B], double w, cplx (&P)[B], cplx& acc) {
     cplx pre[B];
@@ -94,11 +86,11 @@ __device__ __forceinline__ void walk_term(const cplx (&c)[B], double w, cplx (&P
     // the term's sign rides on the suffix, so P_j += pre_j * s is one fused
     // complex multiply-add per column
     const cplx wZ2{w * Z2.re, w * Z2.im};
-    cmul_add_to(acc, Z, wZ2);
+    cmadd(acc, Z, wZ2);
     cplx s = cmul(Y1, wZ2);
 #pragma unroll
     for (int j = B - 1; j >= 1; --j) {
-        cmul_add_to(P[j], pre[j], s);
+        cmadd(P[j], pre[j], s);
         s = cmul(s, c[j]);
     }
     cadd_to(P[0], s);
@@ -152,11 +144,11 @@ __device__ __forceinline__ void walk_term_s(const cplx (&c)[B], cplx (&P)[B], cp
     const cplx Z = cmul(Y, Y1);
     const cplx Z2 = quad_xchg<kQuadXor2, SWZ>(Z);
     const cplx Z2s = NEG ? cplx{-Z2.re, -Z2.im} : Z2;
-    cmul_add_to(acc, Z, Z2s);
+    cmadd(acc, Z, Z2s);
     cplx s = cmul(Y1, Z2s);
 #pragma unroll
     for (int j = B - 1; j >= 1; --j) {
-        cmul_add_to(P[j], pre[j], s);
+        cmadd(P[j], pre[j], s);
         s = cmul(s, c[j]);
     }
     cadd_to(P[0], s);

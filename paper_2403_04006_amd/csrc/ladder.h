@@ -49,11 +49,4 @@ __device__ __forceinline__ int ladder_mode(const uint32_t* row, int P, uint32_t 
     return q;
 }
 
-__device__ __forceinline__ void cmadd(cplx& v, const cplx& a, const cplx& b) {
-    v.re = __builtin_fma(a.re, b.re, v.re);
-    v.re = __builtin_fma(-a.im, b.im, v.re);
-    v.im = __builtin_fma(a.re, b.im, v.im);
-    v.im = __builtin_fma(a.im, b.re, v.im);
-}
-
 }  // namespace pq

@@ -209,9 +209,9 @@ static constexpr uint64_t kMinStepsPerWave = 32;
 static constexpr uint64_t kSpreadSteps = 4;
 
 // The pair sweep from 2^16 time states on, in three launches against one of the
-// one-by-one walk: 22 photons (2^15) 23.3 and 23.0 us a call, 23 30.4 and 33.8, 24 44.4 and 51.2; and against its three: 25
-// photons 79.8 and 108, 26 144 and 187.  Beyond 32 columns two wavefronts'
-// registers do not hold the pairs.
+// one-by-one walk: 22 photons (2^15) 23.3 and 23.0 us a call, 23 30.4 and 33.8,
+// 24 44.4 and 51.2; and against its three: 25 photons 79.8 and 108, 26 144 and
+// 187.  Beyond 32 columns two wavefronts' registers do not hold the pairs.
 static constexpr int kPairTimeDigits = 16;
 // Its workgroups: one round of the resident ones, and one for every
 // kPairBlocks blocks of eight states (at two rounds of wavefronts; the tuner's
@@ -329,10 +329,10 @@ static int timed_sweep(pq_ctx* ctx, bool timed, hipStream_t st, F launch) {
 // Time states up to which a permanent takes one launch, and its wavefronts'
 // least share of them (two workgroups per CU at most).  Whole calls, several
 // launches -> one: 8 photons 19.2 -> 13.3 us, 16 20.9 -> 15.2, 20 24.0 -> 16.5, 22
-// 33.4 -> 23.0 (23 and more go by pairs, kPairTimeDigits); 2 x 9 rows 19.7 -> 13.2, 2 x 11 19.9 ->
-// 15.9, 2 x 12 (6,561 states) 20.0 -> 19.7; but 27 photons in 17 modes (13,824) 20.6
-// -> 23.8, 2 x 13 (19,683) 21.6 -> 27.6, where the step table of the longer sweep
-// is the cheaper step.  Shares of 4, 8 and 16 states: 20
+// 33.4 -> 23.0 (23 and more go by pairs, kPairTimeDigits); 2 x 9 rows 19.7 -> 13.2,
+// 2 x 11 19.9 -> 15.9, 2 x 12 (6,561 states) 20.0 -> 19.7; but 27 photons in 17
+// modes (13,824) 20.6 -> 23.8, 2 x 13 (19,683) 21.6 -> 27.6, where the step table
+// of the longer sweep is the cheaper step.  Shares of 4, 8 and 16 states: 20
 // photons 19.4, 16.5, 16.3 us; 2 x 9 rows 13.7, 16.7, 21.8.
 constexpr uint64_t kFusedMaxBinary = 1 << 15;
 constexpr uint64_t kFusedMaxMixed = 1 << 13;
