@@ -79,6 +79,7 @@ constexpr int kAllLadderSmall = 2048;              // values of a level kept in 
 constexpr int kAllLadderFirst = 4096;              // values of the last level that the small kernel takes
 constexpr int kAllLadderCols = 512;                // modes x levels of the small kernel
 constexpr int kAllLadderBlock = 1024;              // threads of the small levels' workgroup
+static_assert(kAllMaxPhotons <= kRankMaxPhotons, "the rank table holds every level");
 
 struct AllLadderArgs {
     const cplx* U;

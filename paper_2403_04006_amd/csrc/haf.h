@@ -239,6 +239,7 @@ hipError_t launch_haf_many_final(const HafManyFinalArgs& a, hipStream_t s);
 constexpr int kHafLadderModes = 32;
 constexpr int kHafLadderSmall = 2048;        // vectors of a level that the small kernel takes
 constexpr int kHafLadderBlock = 1024;        // threads of the small levels' workgroup
+static_assert(kHafMaxN <= kRankMaxPhotons, "the rank table holds every level");
 constexpr uint64_t kHafLadderBytes = 1ull << 30;   // all levels' values
 
 struct HafLadderArgs {

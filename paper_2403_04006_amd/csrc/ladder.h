@@ -11,9 +11,7 @@
 
 namespace pq {
 
-// The rank table of the ladder: G[r][q] = C(r + q - 1, r) for 1 <= q < m (the
-// vectors of r photons in the last q modes), 0 at q = 0 and no rank at all
-// from q = m on; rows of P, the power of two from m on.
+// The rank table (RankLane): 0 at q = 0 and no rank at all from q = m on.
 constexpr uint32_t kNoRank = 0xffffffffu;
 
 __host__ __device__ inline int ladder_stride(int m) {
@@ -22,19 +20,15 @@ __host__ __device__ inline int ladder_stride(int m) {
     return p;
 }
 
-// G for at most n photons by one wavefront, without divisions or memory
-// reads: lane r makes F(q, r) = C(q + r, r) at step q + r from its own
-// F(q - 1, r) and its neighbour's F(q, r - 1).
+// G for at most n photons (kRankMaxPhotons at most) by one wavefront, without
+// divisions or memory reads.
 __device__ __forceinline__ void ladder_table(int m, int n, int P, int lane, uint32_t* G) {
     for (int e = lane; e < (n + 1) * P; e += 64) G[e] = (e & (P - 1)) == 0 ? 0u : kNoRank;
-    uint32_t v = 0;
-    for (int s = 0; s < m - 1 + n; ++s) {
-        const uint32_t left = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
-        const int q = s - lane;
-        if (lane <= n && q >= 0 && q < m - 1) {
-            v = lane == 0 || q == 0 ? 1u : v + left;
-            G[lane * P + q + 1] = v;
-        }
+    RankLane x{0, 0};
+    const int steps = rank_table_steps(m, n);
+    for (int s = 0; s < steps; ++s) {
+        const uint32_t left = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x.v, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
+        rank_table_step(x, lane, left, s, m, n, P, G);
     }
 }
 

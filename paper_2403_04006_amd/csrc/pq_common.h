@@ -348,6 +348,30 @@ PQ_HD GrayStep gray_step(int n, Radix radix, int M, int q) {
     return e;
 }
 
+// Rank table of photon vectors (ladder.h): G[r][q] = C(r + q - 1, r), the ways
+// to put r photons into the last q modes, for 1 <= q < m; rows of P, the power
+// of two from m on.  The 64 lanes of a wavefront make rows 0..63 together:
+// lane r has F(q, r) = C(q + r, r) = F(q - 1, r) + F(q, r - 1) at step q + r,
+// `left` being its neighbour's value of the step before (0 in lane 0).  The last
+// lane's value is also what row 64 adds at the same q.
+constexpr int kRankMaxPhotons = 64;
+struct RankLane {
+    uint32_t v, next;   // F(q, lane); in the last lane also F(q, 64)
+};
+
+PQ_HD int rank_table_steps(int m, int n) { return m - 1 + (n < kRankMaxPhotons ? n : kRankMaxPhotons - 1); }
+
+PQ_HD void rank_table_step(RankLane& x, int lane, uint32_t left, int s, int m, int n, int P, uint32_t* G) {
+    const int q = s - lane;
+    if (lane > n || q < 0 || q >= m - 1) return;
+    x.v = lane == 0 || q == 0 ? 1u : x.v + left;
+    G[lane * P + q + 1] = x.v;
+    if (lane == kRankMaxPhotons - 1 && n == kRankMaxPhotons) {
+        x.next = q == 0 ? 1u : x.next + x.v;
+        G[kRankMaxPhotons * P + q + 1] = x.next;
+    }
+}
+
 // Even split of [0, total) over `parts`: [start, start + count) of part w.
 PQ_HD void split_range(uint64_t total, uint32_t parts, uint32_t w, uint64_t& start, uint64_t& count) {
     uint64_t q = total / parts, rem = total % parts;
