@@ -94,8 +94,11 @@ void pq_destroy(pq_ctx* ctx);
 /*
  * Cancellation.  pq_cancel(ctx, 1) sets a flag in pinned, device-mapped host
  * memory owned by ctx.  Work-queue launches of this ctx (pq_perm_batched)
- * poll it before every chunk they pop and stop popping once it is set: jobs
- * whose chunks were not all swept keep whatever their output buffers held.
+ * poll it as they pop chunks and stop popping once it is set; of EXTEND_ROW
+ * jobs swept over the signs of their columns (every column of multiplicity 1)
+ * every 64th chunk behind a class's first ones reads it as it starts, and the
+ * chunks that start after it are left out once it is set.  The outputs of jobs whose chunks were not all swept are then
+ * not valid.
  * Kernels of other entry points run to completion.  While the flag is set,
  * every entry point that enqueues GPU work returns PQ_ECANCELLED without
  * enqueuing anything; pq_cancel(ctx, 0) clears it.  Safe to call from another
@@ -214,6 +217,10 @@ typedef struct {
  *     sequence (every pop is an atomic on one counter, and thousands of tiny
  *     chunks popped at once cost more than their sweeps).  pq_queue_mode
  *     overrides this.
+ *   - EXTEND_ROW classes swept over the signs of their columns take one
+ *     workgroup per chunk in the same launch sequence as well, longest first:
+ *     their chunks are short, and the dispatcher hands them out at less cost
+ *     than pops.
  *   - Chunk sizes follow the autotuner when it is enabled (off by default: a
  *     first call then times 13 chunk policies under the queue, about 26 runs
  *     of the batch, and the kept policy under the static schedule as well;
@@ -221,7 +228,8 @@ typedef struct {
  *     (pq_autotune_enable, PQ_AUTOTUNE_CACHE) apply.  Untuned plans run the
  *     queue.
  *   - The work queue reads the ctx's cancellation word every 16 pops per
- *     wavefront (pq_cancel).
+ *     wavefront (pq_cancel), a class of column signs in every 64th chunk
+ *     behind the first 16 per CU.
  *   perm  device, complex, large enough for every job's outputs.
  *   amp   device, may be NULL; written for PQ_OP_PERM jobs only.
  * Output ranges of different jobs must not overlap (PQ_EINVAL otherwise).
@@ -233,8 +241,10 @@ int pq_perm_batched(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
 /*
  * pq_queue_mode -- which column classes pq_perm_batched runs as work queues:
  * PQ_QUEUE_AUTO (default: the rule above, and a tuned plan's recorded
- * schedule), PQ_QUEUE_ALWAYS (every class of a multi-chunk plan), or
- * PQ_QUEUE_NEVER (the static schedule throughout).  Results are the same bits
+ * schedule), PQ_QUEUE_ALWAYS (every class of a multi-chunk plan; classes swept
+ * over column signs keep one workgroup per chunk and read the cancellation word
+ * from their first chunk on), or PQ_QUEUE_NEVER (the static schedule throughout, which
+ * pq_cancel does not stop).  Results are the same bits
  * in every mode.  PQ_QUEUE=auto|always|never in the environment sets it at
  * pq_create.  NULL ctx or another value: PQ_EINVAL.
  */

@@ -248,4 +248,11 @@ __device__ __forceinline__ double sweep_chunk(const JobT& J, const cplx* __restr
     return wl;
 }
 
+// Whether the host has asked to stop (the ctx's cancellation word).
+__device__ __forceinline__ bool cancel_requested(const int32_t* word, int lane) {
+    int c = 0;
+    if (lane == 0) c = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return __builtin_amdgcn_readfirstlane(c) != 0;
+}
+
 }  // namespace pq

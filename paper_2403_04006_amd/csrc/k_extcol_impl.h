@@ -68,6 +68,18 @@ __global__ __launch_bounds__(64, NC <= 12 ? 4 : (NC <= 20 ? 3 : 2)) void extcol_
     const int lane = threadIdx.x & 63;
     const int ci = (int)blockIdx.x;
     if (ci >= a.nchunks) return;
+    if (a.cancel && ci >= a.poll_from) {
+        if (ci % kExtColPollEvery == 0) {
+            if (cancel_requested(a.cancel, lane)) {
+                if (lane == 0) __hip_atomic_store(a.stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+        } else {
+            unsigned stop = 0;
+            if (lane == 0) stop = __hip_atomic_load(a.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_readfirstlane((int)stop)) return;
+        }
+    }
     typedef const __attribute__((address_space(4))) MChunk kchunk;
     kchunk& ch = *(kchunk*)(a.chunks + ci);
     // the descriptor and the rows are written by earlier work only: through the

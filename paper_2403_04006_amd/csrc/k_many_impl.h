@@ -216,12 +216,8 @@ __global__ __launch_bounds__(64) void queue_kernel(const QueueArgs q) {
     const ManyArgs& a = q.m;
     const int lane = threadIdx.x & 63;
     for (int it = 0; it < a.nchunks; ++it) {
-        if (q.cancel && (it & 15) == 0) {
-            // cancellation requested by the host: stop popping
-            int c = 0;
-            if (lane == 0) c = __hip_atomic_load(q.cancel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            if (__builtin_amdgcn_readfirstlane(c)) break;
-        }
+        // cancellation requested by the host: stop popping
+        if (q.cancel && (it & 15) == 0 && cancel_requested(q.cancel, lane)) break;
         unsigned ci = 0;
         if (lane == 0) ci = atomicAdd(q.counter, 1u);
         ci = (unsigned)__builtin_amdgcn_readfirstlane((int)ci);

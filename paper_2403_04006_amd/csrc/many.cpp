@@ -659,7 +659,8 @@ int queue_grid(pq_ctx* ctx, const ManyClass& C) {
     return (int)std::max(1L, std::min((long)C.nchunks, resident));
 }
 
-// Whether a class runs as a work queue in pq_perm_batched: only a class with
+// Whether a class runs as a work queue in pq_perm_batched (kModeExtCol never
+// does, kExtColPollFrom): only a class with
 // more chunks than resident wavefronts has anything to balance, and only
 // chunks of some length amortise a pop.  Every pop is an atomic on one
 // counter, and on this multi-XCD part those serialise: thousands of one-state
@@ -672,6 +673,13 @@ bool class_queues(pq_ctx* ctx, const ManyClass& C) {
     if (ctx->queue_mode == PQ_QUEUE_ALWAYS) return true;
     if (C.states < kQueueMinMeanStates * (uint64_t)C.nchunks) return false;
     return C.nchunks > queue_grid(ctx, C);
+}
+
+// Chunks of a column-sign class that start without reading the cancellation
+// word, and whether any does under pq_perm_batched.
+int poll_from(pq_ctx* ctx) { return ctx->queue_mode == PQ_QUEUE_ALWAYS ? 0 : ctx->num_cu * kExtColPollFrom; }
+bool class_polls(pq_ctx* ctx, const ManyClass& C) {
+    return C.mode == kModeExtCol && ctx->queue_mode != PQ_QUEUE_NEVER && C.nchunks > poll_from(ctx);
 }
 
 // Launch sequence of a plan.  queue (forward plans only): the classes that
@@ -728,7 +736,7 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     fa.red_part = E.d_red_part;
     const int nclass = (int)E.classes.size();
     bool any_queue = false;
-    for (const ManyClass& C : E.classes) any_queue = any_queue || (queue && class_queues(ctx, C));
+    for (const ManyClass& C : E.classes) any_queue = any_queue || (queue && (class_queues(ctx, C) || class_polls(ctx, C)));
     if (any_queue) {
         QueuePrepArgs qp;
         qp.zero = E.d_qzero;
@@ -759,6 +767,10 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
         a.idx = E.d_idx;
         a.tabs = E.d_tabs;
         a.partials = E.d_partials + C.slot_off;
+        const bool polled = queue && class_polls(ctx, C);
+        a.cancel = polled ? ctx->cancel_word_dev : nullptr;
+        a.stop = E.d_qzero + ci;
+        a.poll_from = poll_from(ctx);
         if (queue && class_queues(ctx, C)) {
             QueueArgs q;
             q.m = a;

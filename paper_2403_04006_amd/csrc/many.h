@@ -29,6 +29,18 @@ constexpr int kModeAdjWalk = 3;   // reverse sweep of wide collision-free patter
 constexpr int kModeExtCol = 4;    // EXTEND_ROW jobs over the signs of unit columns (k_extcol_impl.h)
 constexpr int kExtColDigits = 8;  // most time digits that move inside one of its chunks
 constexpr int kExtColMaxPowers = 20;   // most (padded) rows of theirs when some row repeats
+// Under pq_perm_batched its chunks are handed out by the dispatcher as in the
+// static schedule, longest first, which evens out the CUs as a queue would: popped
+// from one counter, 1000 runs of 20 photons in 400 modes take 5.7 ms instead of
+// 4.5 and 100 runs 1.68 instead of 0.88 (a chunk is a quarter of a row chunk's
+// work).  What a queue has besides is the host's request to stop: of the chunks
+// behind the first kExtColPollFrom per CU, which start at once, every
+// kExtColPollEvery-th reads the host's word and passes it on through a word in
+// device memory, which the others read (with every chunk reading over the host
+// link 400 jobs of 24 columns took 19.2 ms instead of 17.7, and as long when
+// cancelled).
+constexpr int kExtColPollFrom = 16;
+constexpr int kExtColPollEvery = 64;
 constexpr int kWalkMinCols = 16;  // padded column range of the walk classes
 constexpr int kWalkMaxCols = 32;
 constexpr int kWalkLaneStates = 16;   // lane-digit states per wavefront (four lanes per term)
@@ -53,6 +65,12 @@ struct ManyArgs {
     const int32_t* idx;
     const StepEntry* tabs;
     double* partials;       // slot storage of this class
+    // kModeExtCol under pq_perm_batched: the host's word (pq_cancel), the class's
+    // word in device memory that is set from it, and the first chunk that reads
+    // them; null: none does
+    const int32_t* cancel;
+    unsigned* stop;
+    int32_t poll_from;
 };
 
 // Reduction of the reverse sweeps' derivative slots in two fixed-order
