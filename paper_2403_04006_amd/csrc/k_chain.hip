@@ -274,17 +274,24 @@ __global__ __launch_bounds__(64 << LW, LW == 2 ? 3 : 2) void chain_kernel(const 
             double before = __shfl_up(upto, 1, 64);
             if (lane == 0) before = 0.0;
             const double target = a.uniforms[(size_t)s * n + (k - 1)] * total;
-            const unsigned long long hit = __ballot(upto > target);
-            if (hit == 0) {
+            // a lane of zero weights is passed over: the scan's order of additions
+            // differs by lane, so its sum can exceed the target by rounding alone;
+            // where that leaves none, the last mode of any weight is taken, and
+            // the last mode of all where the target is not below the total
+            const unsigned long long some = __ballot(mine > 0.0), hit = some & __ballot(upto > target);
+            const int who = hit ? __builtin_ctzll(hit) : (some && target < total ? 63 - __builtin_clzll(some) : -1);
+            if (who < 0) {
                 if (lane == 0) sPick = m - 1;
-            } else if (lane == __builtin_ctzll(hit)) {
-                int pick = -1;
+            } else if (lane == who) {
+                int pick = m - 1;
                 for (int l = l0; l < l1; ++l) {
                     before += sW[l];
-                    if (sW[l] > 0.0) pick = l;   // where rounding leaves the run's sum at the target: its last mode
-                    if (before > target) break;
+                    if (sW[l] > 0.0) {
+                        pick = l;   // where rounding leaves the run's sum at the target: its last mode
+                        if (before > target) break;
+                    }
                 }
-                sPick = pick >= 0 ? pick : m - 1;
+                sPick = pick;
             }
             if (lane == 0) a.out[(size_t)s * n + (k - 1)] = sPick;
         }
