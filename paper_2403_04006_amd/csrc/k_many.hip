@@ -89,7 +89,7 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int32_t* cmode = a.idx + J.idx_off + (J.ext_cols ? 0 : 2 * J.r);
+        const int32_t* cmode = a.idx + J.idx_off + (a.UT ? 2 * J.r + J.nc : J.ext_cols ? 0 : 2 * J.r);
         for (int l = t; l < J.m_out; l += 64) {
             const cplx* Ul = a.U + (size_t)l * (size_t)a.ldu;
             double re = 0.0, im = 0.0;
@@ -167,16 +167,16 @@ hipError_t launch_dred(const DRedArgs& a, int nitems, hipStream_t s) {
 __global__ __launch_bounds__(256) void transpose_kernel(const TransposeArgs a) {
     __shared__ cplx tile[16][17];
     const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
-    const int r = blockIdx.y * 16 + y, c = blockIdx.x * 16 + x;
-    if (r < a.m && c < a.m) tile[y][x] = a.U[(size_t)r * (size_t)a.ldu + c];
+    const int r = blockIdx.x * 16 + y, c = blockIdx.y * 16 + x;
+    if (r < a.m && c < a.n) tile[y][x] = a.U[(size_t)r * (size_t)a.ldu + (size_t)a.col[c]];
     __syncthreads();
-    const int tr = blockIdx.x * 16 + y, tc = blockIdx.y * 16 + x;
-    if (tr < a.m && tc < a.m) a.UT[(size_t)tr * (size_t)a.m + tc] = tile[x][y];
+    const int tr = blockIdx.y * 16 + y, tc = blockIdx.x * 16 + x;
+    if (tr < a.n && tc < a.m) a.UT[(size_t)tr * (size_t)a.m + tc] = tile[x][y];
 }
 
 hipError_t launch_transpose(const TransposeArgs& a, hipStream_t s) {
-    const unsigned n = (unsigned)((a.m + 15) / 16);
-    hipLaunchKernelGGL(transpose_kernel, dim3(n, n), dim3(256), 0, s, a);
+    if (a.m < 1 || a.n < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(transpose_kernel, dim3((unsigned)((a.m + 15) / 16), (unsigned)((a.n + 15) / 16)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -54,9 +54,11 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
 // even number of them instead of a multiple of four: two columns less are a
 // tenth of its work, where a class more is one more launch and its uneven end.
 constexpr uint64_t kEvenClassStates = 1 << 18;
-// From this many extend-row jobs on, their final step reads U transposed (one
-// launch more; 19,000 jobs on 400 modes: 230 us of final step before).
+// From this many extend-row jobs on, their final step reads the columns of U that
+// they use, transposed (one launch more; 19,000 jobs on 400 modes: 230 us of final
+// step before), as long as these take at most so many bytes of the plan's block.
 constexpr int kTransposeMinJobs = 512;
+constexpr size_t kTransposeMaxBytes = (size_t)32 << 20;
 // Cached plans: four whatever their size, more while their device blocks
 // stay within kMaxManyBytes together, kMaxManyEntries at most (a training loop
 // holds a forward and a reverse plan for each of its pattern sets; 4096 patterns
@@ -99,7 +101,9 @@ struct ManyEntry {
     int max_chunks = 0;          // most chunks of any pattern (1: nothing for a work queue to balance)
     int queue_pref = -1;         // the autotuner's schedule for pq_perm_batched (1 queue, 0 static, -1 none)
     size_t mat_elems = 0, partial_doubles = 0, dpat_elems = 0;
-    cplx* d_ut = nullptr;        // U transposed (kTransposeMinJobs)
+    cplx* d_ut = nullptr;        // columns of U, transposed (kTransposeMinJobs)
+    int32_t* d_ut_col = nullptr; // which
+    int nut = 0;
     std::vector<ManyClass> classes;
     ChunkPolicy policy;
     // device
@@ -277,6 +281,10 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     std::map<std::vector<int32_t>, int> sigs;
     std::map<std::tuple<int, int, int>, std::vector<int>> by_class;
     size_t mat_elems = 0, dpat_elems = 0;
+    // columns of U that extend-row jobs use, and their places among them
+    std::vector<int32_t> ut_col, ut_at;
+    if (!adj && pats.size() >= (size_t)kTransposeMinJobs) ut_at.assign((size_t)m, -1);
+    int next = 0;
     Side rows, cols;
     for (size_t k = 0; k < pats.size(); ++k) {
         const PatRef& ps = pats[k];
@@ -379,6 +387,17 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         for (int i = 0; i < p.r; ++i) hidx.push_back(p.row_mode[i]);
         for (int i = 0; i < p.r; ++i) hidx.push_back(p.row_mu[i]);
         for (int j = 0; j < p.nc; ++j) hidx.push_back(p.col_mode[j]);
+        if (ext) {
+            ++next;
+            for (int j = 0; !ut_at.empty() && j < ps.nc; ++j) {
+                const int c = extcol ? p.row_mode[j] : p.col_mode[j];
+                if (ut_at[(size_t)c] < 0) {
+                    ut_at[(size_t)c] = (int32_t)ut_col.size();
+                    ut_col.push_back(c);
+                }
+                hidx.push_back(ut_at[(size_t)c]);
+            }
+        }
         if (adj) {
             dpat_off[k] = (int64_t)dpat_elems;
             dpat_elems += (size_t)p.r * p.nc;
@@ -551,6 +570,10 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         }
     }
 
+    const size_t ut_bytes = sizeof(cplx) * ut_col.size() * (size_t)m;
+    const bool ut = next >= kTransposeMinJobs && ut_bytes <= kTransposeMaxBytes;
+    if (!ut) ut_col.clear();
+
     // one device block: uploaded descriptors first, kernel-written arrays after
     Carve cv;
     auto sz = [](size_t n) { return std::max<size_t>(1, n); };
@@ -571,6 +594,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     const size_t oDuo = cv.take(sizeof(int32_t) * sz(dup_off.size()));
     const size_t oDup = cv.take(sizeof(int32_t) * sz(dup_pat.size()));
     const size_t oDut = cv.take(sizeof(int64_t) * sz(dup_out.size()));
+    const size_t oUc = cv.take(sizeof(int32_t) * sz(ut_col.size()));
     const size_t upload_bytes = cv.off;
     const size_t oMat = cv.take(sizeof(cplx) * sz(mat_elems));
     const size_t oTab = cv.take(sizeof(StepEntry) * 2 * kMaxInner * sz(sigs.size()));
@@ -578,9 +602,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     const size_t oDp = cv.take(sizeof(cplx) * sz(dpat_elems));
     const size_t oRp = cv.take(sizeof(cplx) * sz(red_part));
     const size_t oGs = cv.take(sizeof(cplx) * sz(adj ? pats.size() : 0));
-    int next = 0;
-    for (const BJob& b : hj) next += b.m_out > 0;
-    const size_t oUt = cv.take(sizeof(cplx) * sz(next >= kTransposeMinJobs ? (size_t)m * (size_t)m : 0));
+    const size_t oUt = cv.take(ut ? ut_bytes : 1);
     const size_t oQz = cv.take(sizeof(unsigned) * sz(adj ? 0 : E.classes.size()));
     if (int rc = ctx->device_alloc((void**)&E.dmem, cv.off, "many")) return rc;
     E.bytes = cv.off;
@@ -604,7 +626,9 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     E.d_dup_out = (int64_t*)(E.dmem + oDut);
     E.d_gsum = (cplx*)(E.dmem + oGs);
     E.d_qzero = (unsigned*)(E.dmem + oQz);
-    E.d_ut = next >= kTransposeMinJobs ? (cplx*)(E.dmem + oUt) : nullptr;
+    E.d_ut = ut ? (cplx*)(E.dmem + oUt) : nullptr;
+    E.d_ut_col = (int32_t*)(E.dmem + oUc);
+    E.nut = (int)ut_col.size();
     E.d_mat = (cplx*)(E.dmem + oMat);
     E.d_tabs = (StepEntry*)(E.dmem + oTab);
     E.d_partials = (double*)(E.dmem + oPart);
@@ -630,6 +654,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     put(oDuo, dup_off.data(), sizeof(int32_t) * dup_off.size());
     put(oDup, dup_pat.data(), sizeof(int32_t) * dup_pat.size());
     put(oDut, dup_out.data(), sizeof(int64_t) * dup_out.size());
+    put(oUc, ut_col.data(), sizeof(int32_t) * ut_col.size());
     return ctx->upload(E.dmem, stage, upload_bytes, st);
 }
 
@@ -702,7 +727,7 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
         if (rc) return rc;
     }
     if (E.d_ut) {
-        TransposeArgs ta{U, ldu, m, E.d_ut};
+        TransposeArgs ta{U, ldu, m, E.nut, E.d_ut_col, E.d_ut};
         rc = ctx->check(launch_transpose(ta, st), "many transpose");
         if (rc) return rc;
     }

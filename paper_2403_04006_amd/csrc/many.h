@@ -98,7 +98,8 @@ struct DRedArgs {
 struct ManyFinalArgs {
     const cplx* U;
     int64_t ldu;
-    const cplx* UT;            // U transposed, [m][m], or null (extend-row jobs)
+    const cplx* UT;            // columns of U, transposed, or null; their rows in it follow an
+                               // extend-row job's modes in idx
     int32_t m;
     const int32_t* idx;
     const int64_t* dpat_off;   // [npat]: complex offset of the pattern's D block
@@ -128,14 +129,15 @@ struct ManyFinalArgs {
     cplx* red_part;
 };
 
-// U transposed for the extend-row jobs' final step: its lanes are consecutive
-// output modes, whose entries of one column are a row of the transpose (in U
-// itself every lane reads another line).
+// Columns of U, transposed, for the extend-row jobs' final step: its lanes are
+// consecutive output modes, whose entries of one column are a row of the transpose
+// (in U itself every lane reads another line).
 struct TransposeArgs {
     const cplx* U;
     int64_t ldu;
-    int32_t m;
-    cplx* UT;
+    int32_t m, n;
+    const int32_t* col;     // [n]
+    cplx* UT;               // [n][m]
 };
 
 // Persistent work queue over one class's chunks (forward and extend-row
