@@ -380,8 +380,8 @@ int pq_perm_grad(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  * By default the values are built photon by photon,
  *   perm_k(T) = sum_i t_i U[i][j_k] perm_{k-1}(T - e_i),
  * in workspace for the two levels below the outputs (16 bytes per vector of
- * n - 1 and of n - 2 photons in m modes), as long as that is at most 1 GiB.
- * Two forms compute the signed sum instead (pq_all_outputs_gemm picks them):
+ * n - 1 and of n - 2 photons in m modes), as long as that is at most 1 GiB and
+ * can be allocated.  Two forms compute the signed sum instead (pq_all_outputs_gemm picks them):
  *   - the sweep: a term's m column sums c_i = sum_j delta_j U[i][j] give
  *     w prod_i c_i^{t_i} for all T at once; one thread per output T, terms
  *     staged through LDS;
@@ -527,7 +527,8 @@ int pq_lhaf_pack(pq_ctx* ctx, int mode);
  * probabilities of many output patterns of one Gaussian state), in one
  * submission.  Where the vectors of at most max N photons in the occupied
  * modes (at most 32) are cheaper to tabulate than the patterns are to sweep,
- * their values are built level by level in workspace (at most 1 GiB),
+ * their values are built level by level in workspace (at most 1 GiB, and only
+ * if that can be allocated),
  *   h(r) = gamma_i h(r - e_i) + sum_k (r - e_i)_k A_ik h(r - e_i - e_k),
  * and each pattern's value is read from the table.  Otherwise every pattern
  * is planned on the host, its Gray range is cut into chunks (four per

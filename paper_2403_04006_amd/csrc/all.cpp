@@ -201,18 +201,18 @@ int all_cache(pq_ctx* ctx, AllCache** out) {
 }
 
 // The ladder form (see all.h).  done = false when its lower levels do not fit
-// kAllLadderBytes: nothing was launched then.
+// kAllLadderBytes or the memory at hand: nothing was launched then.
 int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int32_t* S, double norm_s,
                uint64_t outputs, cplx* perm, cplx* amp, hipStream_t st, bool& done) {
     done = false;
     const uint64_t c1 = compositions(m, n - 1, (uint64_t)kAllMaxOutputs);
     const uint64_t c2 = n > 1 ? compositions(m, n - 2, (uint64_t)kAllMaxOutputs) : 1;
     if ((c1 + c2) * sizeof(cplx) > kAllLadderBytes) return PQ_OK;
-    done = true;
     Carve cv;
     const size_t oBuf[2] = {cv.take(sizeof(cplx) * (size_t)c1), cv.take(sizeof(cplx) * (size_t)c2)};
-    char* ws = (char*)ctx->workspace(cv.off);
-    if (!ws) return PQ_ENOMEM;
+    char* ws = (char*)ctx->try_workspace(cv.off);
+    if (!ws) return PQ_OK;
+    done = true;
     AllLevelArgs la;
     memset(&la, 0, sizeof(la));
     AllLadderArgs& a = la.a;

@@ -292,14 +292,18 @@ bool plan_ladder(const int32_t* reps, int d, int npat, bool loops, HafLadderArgs
     return ladder_ns < sweep_ns;
 }
 
+// done = false when the table does not fit the memory at hand: nothing was
+// launched then.
 int run_haf_ladder(pq_ctx* ctx, HafLadderArgs& a, const cplx* A, int64_t lda, int d, const cplx* gamma,
-                   const int32_t* reps, cplx* out, hipStream_t st) {
+                   const int32_t* reps, cplx* out, hipStream_t st, bool& done) {
+    done = false;
     Carve cv;
     const size_t oR = cv.take((size_t)a.npat * (size_t)a.d);
     const size_t upload = cv.off;
     const size_t oH = cv.take(sizeof(cplx) * (size_t)a.off[a.N + 1]);
-    char* ws = (char*)ctx->workspace(cv.off);
-    if (!ws) return PQ_ENOMEM;
+    char* ws = (char*)ctx->try_workspace(cv.off);
+    if (!ws) return PQ_OK;
+    done = true;
     uint8_t* stage = (uint8_t*)ctx->staging(upload);
     if (!stage) return PQ_ENOMEM;
     uint8_t* __restrict w = stage + oR;
@@ -478,8 +482,10 @@ int pq_lhaf_many(pq_ctx* ctx, const pq_c128* A, int64_t lda, int32_t d, const pq
         HafLadderArgs la;
         if (A && lda >= d && plan_ladder(reps, d, npat, loops, la)) {
             DeviceGuard guard(ctx->device);
-            return run_haf_ladder(ctx, la, (const cplx*)A, lda, d, (const cplx*)gamma, reps, (cplx*)out,
-                                  (hipStream_t)stream);
+            bool done = false;
+            const int rc = run_haf_ladder(ctx, la, (const cplx*)A, lda, d, (const cplx*)gamma, reps, (cplx*)out,
+                                          (hipStream_t)stream, done);
+            if (rc || done) return rc;
         }
     }
     std::vector<HafDesc> descs((size_t)npat);

@@ -87,6 +87,9 @@ void pq_ctx::tune_cache_store(const pq::TuneRecord& rec, const char* kind) {
     fclose(f);
 }
 
+// hipFree waits for earlier work that uses the old block
+static constexpr size_t kMinWorkspace = (size_t)1 << 20;
+
 void* pq_ctx::workspace(size_t bytes) {
     if (bytes <= ws_bytes && ws) return ws;
     if (ws) {
@@ -94,8 +97,22 @@ void* pq_ctx::workspace(size_t bytes) {
         ws = nullptr;
         ws_bytes = 0;
     }
-    size_t want = bytes < ((size_t)1 << 20) ? ((size_t)1 << 20) : bytes;
+    const size_t want = std::max(bytes, kMinWorkspace);
     if (device_alloc(&ws, want, "workspace")) return nullptr;
+    ws_bytes = want;
+    return ws;
+}
+
+void* pq_ctx::try_workspace(size_t bytes) {
+    if (bytes <= ws_bytes && ws) return ws;
+    const size_t want = std::max(bytes, kMinWorkspace);
+    void* more = nullptr;
+    if (device_alloc(&more, want, "workspace")) {
+        clear_error();
+        return nullptr;
+    }
+    if (ws) hipFree(ws);
+    ws = more;
     ws_bytes = want;
     return ws;
 }

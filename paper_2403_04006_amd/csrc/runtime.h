@@ -126,6 +126,9 @@ struct pq_ctx {
     int check(hipError_t e, const char* what);
     // workspace of at least `bytes`; nullptr on failure (status set)
     void* workspace(size_t bytes);
+    // the same for a form that another one can stand in for: nullptr, the
+    // workspace kept as it is and no error, where there is no memory for it
+    void* try_workspace(size_t bytes);
     // pinned staging of at least `bytes`, free to overwrite (waits for the
     // previous upload out of it); nullptr on failure
     void* staging(size_t bytes);
