@@ -270,8 +270,11 @@ int pq_perm_many(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  * A plan aims at num_cu * waves_per_cu * chunks_per_wave chunks per class,
  * none shorter than min_chunk Gray time states; the default policy is
  * (64, 8, 256): fine chunks for long uneven jobs (a short tail), and short
- * jobs kept whole.  It applies to pq_perm_batched as well, so the two calls
- * give the same bits on the same job list.
+ * jobs kept whole.  A class too short to fill the device in such chunks is cut
+ * into shorter ones whatever the policy; EXTEND_ROW classes swept over the signs
+ * of their columns take powers of two from 32 to 256 states.  It applies to
+ * pq_perm_batched as well, so the two calls give the same bits on the same job
+ * list.
  *
  * pq_autotune_enable -- on (nonzero): the first pq_perm_many call on a job
  * list whose shape (m, and for every job kind and padded column count the

@@ -432,21 +432,22 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
                          : C.mode == kModeExt ? 4 * C.ncmax
                          : C.mode == kModeExtCol ? 4 * rmax : 4 + 2 * rmax * C.ncmax;
         uint64_t chunk = 0;
-        if (C.mode == kModeFwd || C.mode == kModeExt) {
+        if (C.mode == kModeFwd || C.mode == kModeExt || C.mode == kModeExtCol) {
             const uint64_t target = (uint64_t)ctx->num_cu * (uint64_t)pol.waves_per_cu * (uint64_t)pol.chunks_per_wave;
             chunk = (total + target - 1) / target;
             if (chunk < (uint64_t)pol.min_chunk) chunk = (uint64_t)pol.min_chunk;
             // a class that would leave the device part empty in such chunks is
-            // spread over it in shorter ones
+            // spread over it in shorter ones, whatever the policy
             const uint64_t spread = (uint64_t)ctx->num_cu * kSpreadWaves;
-            if (total < chunk * spread) {
+            if (C.mode == kModeExtCol) {
+                // the power of two that the policy's chunk holds
+                int q = kExtColDigits;
+                while (q > kExtColMinDigits && ((chunk >> q) == 0 || (total >> q) < spread)) --q;
+                chunk = (uint64_t)1 << q;
+            } else if (total < chunk * spread) {
                 chunk = std::min(chunk, (total + spread - 1) / spread);
                 chunk = std::max(chunk, C.mode == kModeFwd ? kSpreadChunk : kSpreadExtChunk);
             }
-        } else if (C.mode == kModeExtCol) {
-            int q = kExtColDigits;
-            while (q > kExtColMinDigits && (total >> q) < (uint64_t)ctx->num_cu * kSpreadWaves) --q;
-            chunk = (uint64_t)1 << q;
         } else if (C.mode == kModeAdjWalk) {
             // whole rounds of the resident wavefronts (every walk costs the
             // same), in whole 8-state blocks: one round, or up to four while
@@ -892,12 +893,15 @@ int run_many_graph(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_
     return ctx->check(hipGraphLaunch(rec->exec, st), "graph launch");
 }
 
-// Shape signature of a job list: for every (op, padded column count) class,
-// the number of patterns and of Gray terms in half-octave buckets, and m.
+// Shape signature of a job list: for every (op, padded column count) class (jobs
+// swept over column signs apart, whose chunks cost other times), the number of
+// patterns and of Gray terms in half-octave buckets, and m.
 // Job lists with the same work per class (say, other sampling runs of the
 // same size, whose output collisions differ) share a tuned policy.
 uint64_t shape_sig(int32_t m, const std::vector<PatRef>& pats) {
-    std::map<std::pair<int, int>, std::pair<double, double>> cls;   // (op, ncmax) -> (patterns, terms)
+    // (op, ncmax) -> (patterns, terms); column signs under an op of their own
+    constexpr int kSignsOp = 16;
+    std::map<std::pair<int, int>, std::pair<double, double>> cls;
     Side rows, cols;
     for (const PatRef& ps : pats) {
         const bool ext = ps.op == kOpExtend;
@@ -906,7 +910,9 @@ uint64_t shape_sig(int32_t m, const std::vector<PatRef>& pats) {
         Plan p;
         plan_sparse(rows, cols, !ext, p, ext);
         if (p.status || p.trivial) continue;
-        auto& c = cls[std::make_pair(ps.op, ((p.nc + 3) / 4) * 4)];
+        Plan pc;
+        const int op = ext && ext_over_columns(rows, cols, p, pc) ? kSignsOp : ps.op;
+        auto& c = cls[std::make_pair(op, ((p.nc + 3) / 4) * 4)];
         c.first += 1.0;
         c.second += (double)p.time_states * (double)p.lane_states;
     }
