@@ -132,8 +132,11 @@ const char* pq_last_error(const pq_ctx* ctx);
  *   perm   device, 1 complex, may be NULL: perm(U_{T,S}).
  *   amp    device, 1 complex, may be NULL: perm / sqrt(prod S! prod T!).
  * U must not be NULL when m > 0; S and T must not be NULL.
- * The sweep splits its Gray range evenly over two rounds of the resident
- * wavefronts (each at least 32 time states); with autotuning on
+ * Short sums (up to 2^15 time states of collision-free patterns, 2^13 others)
+ * take one launch.  Longer sweeps split their Gray range evenly over up to two
+ * rounds of the resident wavefronts (each at least 32 time states, or at least 4
+ * where that would leave the device part empty), collision-free ones of 23 to 32
+ * photons over workgroups of two wavefronts.  With autotuning on
  * (pq_autotune_enable) the launch shape follows the autotuner instead.
  */
 int pq_perm(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
@@ -290,15 +293,17 @@ int pq_perm_many(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
  *   The same switch tunes pq_perm's launch shape: the first call on a plan
  * shape (kernel kind, column count, digit radices and column powers: n and
  * the multiplicity class) with no recorded decision runs the whole launch
- * sequence under 2, 1 and 4 rounds of the resident wavefronts (the default
- * first, best of two runs each, timed with HIP events around the sequence:
- * 6 runs, and the stream is synchronized), keeps the fastest, records it,
- * and then runs once more with it.  Later calls of that shape reuse the
+ * sequence under 2, 1 and 4 rounds of the resident wavefronts, or in one launch
+ * and under 1 and 4 rounds where the plan is short enough for one launch (the
+ * default first, best of two runs each, timed with HIP events around the
+ * sequence: 6 runs, and the stream is synchronized), keeps the fastest, records
+ * it, and then runs once more with it.  Later calls of that shape reuse the
  * record; pq_perm_noalloc follows a recorded decision but never times.
  * PQ_AUTOTUNE_CACHE persists these decisions too (kind "perm").
  *
  * pq_autotune_last -- the last decision: policy = {waves_per_cu,
- * chunks_per_wave, min_chunk} (for pq_perm: {wavefronts per CU, 1, 32}),
+ * chunks_per_wave, min_chunk} (for pq_perm: {wavefronts per CU, 1, 32}, 0
+ * wavefronts for one launch),
  * the kept plan's or shape's time and the default's (ms), and the number of
  * candidates timed (0: the decision came from the record).  All zero before
  * any tuning.  NULL arguments: PQ_EINVAL.

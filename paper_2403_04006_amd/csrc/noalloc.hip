@@ -118,7 +118,7 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     if (L.accept > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
                          "bytes of the static buffer (use pq_perm)", L.accept, kNoAllocScratchBytes);
-    if (ctx->tickets && fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
+    if (fused_applies(ctx, p) && fused_bytes(ctx, p) <= kNoAllocBufferBytes)
         return run_fused(ctx, p, (double*)ws, tickets, g_noalloc_turn.fetch_add(1), (const cplx*)U, ldu, (cplx*)perm, (cplx*)amp, st, false);
     const SingleLayout spread = single_layout(ctx, p, kind, wpc);
     if (spread.bytes <= kNoAllocBufferBytes) L = spread;

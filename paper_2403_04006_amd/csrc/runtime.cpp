@@ -288,6 +288,24 @@ Geometry sweep_geometry(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, 
     return g;
 }
 
+// Time states up to which a permanent takes one launch, and its wavefronts'
+// least share of them (two workgroups per CU at most).  Whole calls, several
+// launches -> one: 8 photons 19.2 -> 13.3 us, 16 20.9 -> 15.2, 20 24.0 -> 16.5, 22
+// 33.4 -> 23.0 (23 and more go by pairs, kPairTimeDigits); 2 x 9 rows 19.7 -> 13.2,
+// 2 x 11 19.9 -> 15.9, 2 x 12 (6,561 states) 20.0 -> 19.7; but 27 photons in 17
+// modes (13,824) 20.6 -> 23.8, 2 x 13 (19,683) 21.6 -> 27.6, where the step table
+// of the longer sweep is the cheaper step.  Shares of 4, 8 and 16 states: 20
+// photons 19.4, 16.5, 16.3 us; 2 x 9 rows 13.7, 16.7, 21.8.
+constexpr uint64_t kFusedMaxBinary = 1 << 15;
+constexpr uint64_t kFusedMaxMixed = 1 << 13;
+constexpr uint64_t kFusedSteps = 8;
+constexpr uint64_t kFusedStepsMixed = 4;
+
+static bool fused_shape(const Plan& p) {
+    return p.nc <= kFusedMaxCols && p.time_states <= (p.binary ? kFusedMaxBinary : kFusedMaxMixed) &&
+           sweep_kind(p) != kSweepMixGeneral;
+}
+
 uint64_t single_sig(const Plan& p) {
     // seeded apart from the job-list shape signatures, which share the
     // records and the cache file
@@ -297,7 +315,8 @@ uint64_t single_sig(const Plan& p) {
         h *= 1099511628211ull;
         h ^= h >> 29;
     };
-    mix((uint64_t)sweep_kind(p));
+    // (shapes that the one-launch form may take apart from records made without it)
+    mix((uint64_t)sweep_kind(p) + (fused_shape(p) ? 16 : 0));
     mix((uint64_t)p.r);
     mix((uint64_t)p.nc);
     mix((uint64_t)p.n_lane);
@@ -317,7 +336,8 @@ static const TuneRecord* recorded(pq_ctx* ctx, uint64_t sig) {
 
 int single_waves_per_cu(pq_ctx* ctx, const Plan& p) {
     if (ctx->autotune)
-        if (const TuneRecord* t = recorded(ctx, single_sig(p))) return t->policy.waves_per_cu;
+        if (const TuneRecord* t = recorded(ctx, single_sig(p)))
+            if (t->policy.waves_per_cu > 0) return t->policy.waves_per_cu;
     return sweep_waves_per_cu(ctx, p);
 }
 
@@ -343,23 +363,11 @@ static int timed_sweep(pq_ctx* ctx, bool timed, hipStream_t st, F launch) {
     return PQ_OK;
 }
 
-// Time states up to which a permanent takes one launch, and its wavefronts'
-// least share of them (two workgroups per CU at most).  Whole calls, several
-// launches -> one: 8 photons 19.2 -> 13.3 us, 16 20.9 -> 15.2, 20 24.0 -> 16.5, 22
-// 33.4 -> 23.0 (23 and more go by pairs, kPairTimeDigits); 2 x 9 rows 19.7 -> 13.2,
-// 2 x 11 19.9 -> 15.9, 2 x 12 (6,561 states) 20.0 -> 19.7; but 27 photons in 17
-// modes (13,824) 20.6 -> 23.8, 2 x 13 (19,683) 21.6 -> 27.6, where the step table
-// of the longer sweep is the cheaper step.  Shares of 4, 8 and 16 states: 20
-// photons 19.4, 16.5, 16.3 us; 2 x 9 rows 13.7, 16.7, 21.8.
-constexpr uint64_t kFusedMaxBinary = 1 << 15;
-constexpr uint64_t kFusedMaxMixed = 1 << 13;
-constexpr uint64_t kFusedSteps = 8;
-constexpr uint64_t kFusedStepsMixed = 4;
-
+// A recorded launch shape of 0 wavefronts per CU is the one-launch form.
 bool fused_applies(pq_ctx* ctx, const Plan& p) {
-    if (ctx->autotune || p.nc > kFusedMaxCols) return false;
-    if (p.time_states > (p.binary ? kFusedMaxBinary : kFusedMaxMixed)) return false;
-    return sweep_kind(p) != kSweepMixGeneral;
+    if (!ctx->tickets || !fused_shape(p)) return false;
+    const TuneRecord* t = ctx->autotune ? recorded(ctx, single_sig(p)) : nullptr;
+    return !t || t->policy.waves_per_cu <= 0;
 }
 
 static uint32_t fused_waves(pq_ctx* ctx, const Plan& p) {
@@ -547,11 +555,13 @@ int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, c
 }
 
 // Time the whole launch sequence of a plan under 2, 1 and 4 rounds of the
-// resident wavefronts (the default first; best of two runs each), record the
-// fastest for the plan's shape, and return its wavefronts per CU.  The runs
-// write perm and amp; the caller's run afterwards writes them again.
+// resident wavefronts (the default first; best of two runs each), and record the
+// fastest for the plan's shape.  Where the one-launch form applies, that is the
+// default and comes first instead of the 2 rounds (so few states make the same
+// launch of any).  The runs write perm and amp; the caller's run afterwards writes
+// them again.
 static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* perm, cplx* amp,
-                       hipStream_t st, int& wpc) {
+                       hipStream_t st) {
     TuneRecord rec;
     rec.sig = single_sig(p);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -561,10 +571,13 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
     }
     int rc = PQ_OK;
     double best = -1.0;
+    const bool fused = ctx->tickets && fused_shape(p);
     for (int rounds : {kSweepRounds, 1, 4}) {
-        const int w = sweep_waves_per_cu(ctx, p, rounds);
-        const SingleLayout L = single_layout(ctx, p, sweep_kind(p), w);
-        char* ws = (char*)ctx->workspace(L.bytes);
+        const bool one = fused && rec.candidates == 0;
+        const int w = one ? 0 : sweep_waves_per_cu(ctx, p, rounds);
+        SingleLayout L;
+        if (!one) L = single_layout(ctx, p, sweep_kind(p), w);
+        char* ws = (char*)ctx->workspace(one ? fused_bytes(ctx, p) : L.bytes);
         if (!ws) {
             rc = PQ_ENOMEM;
             break;
@@ -572,7 +585,8 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
         double ms = -1.0;
         for (int rep = 0; rep < 2 && !rc; ++rep) {
             rc = ctx->check(hipEventRecord(e0, st), "tune: record");
-            if (!rc) rc = run_single_at(ctx, p, L, ws, U, ldu, perm, amp, st, false);
+            if (!rc) rc = one ? run_fused(ctx, p, (double*)ws, ctx->tickets, ctx->ticket_turn++, U, ldu, perm, amp, st, false)
+                              : run_single_at(ctx, p, L, ws, U, ldu, perm, amp, st, false);
             if (!rc) rc = ctx->check(hipEventRecord(e1, st), "tune: record");
             if (!rc) rc = ctx->check(hipEventSynchronize(e1), "tune: synchronize");
             float f = 0.0f;
@@ -596,28 +610,25 @@ static int tune_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, c
     ctx->tuned.push_back(rec);
     ctx->last_tune = rec;
     ctx->tune_cache_store(rec, "perm");
-    wpc = rec.policy.waves_per_cu;
     return PQ_OK;
 }
 
 int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* perm, cplx* amp,
                hipStream_t st) {
-    if (ctx->tickets && fused_applies(ctx, p)) {
-        double* partials = (double*)ctx->workspace(fused_bytes(ctx, p));
-        if (!partials) return PQ_ENOMEM;
-        return run_fused(ctx, p, partials, ctx->tickets, ctx->ticket_turn++, U, ldu, perm, amp, st, true);
-    }
-    int wpc = sweep_waves_per_cu(ctx, p);
     if (ctx->autotune) {
         if (const TuneRecord* t = recorded(ctx, single_sig(p))) {
             ctx->last_tune = *t;
             ctx->last_tune.candidates = 0;
-            wpc = t->policy.waves_per_cu;
-        } else if (int rc = tune_single(ctx, p, U, ldu, perm, amp, st, wpc)) {
+        } else if (int rc = tune_single(ctx, p, U, ldu, perm, amp, st)) {
             return rc;
         }
     }
-    const SingleLayout L = single_layout(ctx, p, sweep_kind(p), wpc);
+    if (fused_applies(ctx, p)) {
+        double* partials = (double*)ctx->workspace(fused_bytes(ctx, p));
+        if (!partials) return PQ_ENOMEM;
+        return run_fused(ctx, p, partials, ctx->tickets, ctx->ticket_turn++, U, ldu, perm, amp, st, true);
+    }
+    const SingleLayout L = single_layout(ctx, p, sweep_kind(p), single_waves_per_cu(ctx, p));
     char* ws = (char*)ctx->workspace(L.bytes);
     if (!ws) return PQ_ENOMEM;
     return run_single_at(ctx, p, L, ws, U, ldu, perm, amp, st, true);

@@ -173,9 +173,9 @@ struct Geometry {
     uint32_t waves = 1; // active wavefronts
 };
 // The sweep splits its time-state range evenly over num_cu * waves_per_cu
-// wavefronts (each at least 32 states).  With `spread`, whole rounds of the
-// resident wavefronts, and one round, each at least 8 states, where that share
-// does not fill one.  The default is two rounds of the
+// wavefronts (each at least kMinStepsPerWave states).  With `spread`, whole rounds
+// of the resident wavefronts, and one round, each at least kSpreadSteps states,
+// where that share does not fill one.  The default is two rounds of the
 // resident wavefronts: the dispatcher hands the second round's workgroups to
 // the CUs that finish their first ones early, which evens out unequal CU and
 // XCD speeds that a single round leaves on the critical path.
@@ -207,8 +207,8 @@ struct SingleLayout {
 };
 SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread = true);
 
-// One-launch permanents (k_fused_impl.h): whether a plan takes that form, its
-// scratch (the workgroups' sums), and the launch.
+// One-launch permanents (k_fused_impl.h): whether a plan takes that form (its
+// shape fits, and no other decision is recorded for it), its scratch (the workgroups' sums), and the launch.
 bool fused_applies(pq_ctx* ctx, const Plan& p);
 size_t fused_bytes(pq_ctx* ctx, const Plan& p);
 int run_fused(pq_ctx* ctx, const Plan& p, double* partials, uint32_t* tickets, uint32_t turn, const cplx* U, int64_t ldu, cplx* perm,
@@ -221,8 +221,7 @@ int run_single_at(pq_ctx* ctx, const Plan& p, const SingleLayout& L, char* ws, c
 
 // The same on the ctx workspace (grown on demand).  With autotuning on, a
 // plan shape without a recorded decision first times the whole sequence
-// under 2, 1 and 4 rounds of the resident wavefronts (best of two runs each)
-// and records the fastest.
+// under its candidate shapes (tune_single) and records the fastest.
 int run_single(pq_ctx* ctx, const Plan& p, const cplx* U, int64_t ldu, cplx* perm, cplx* amp,
                hipStream_t st);
 

@@ -1,5 +1,6 @@
 """Recorded autotuning decisions on the forms of the later kernels: a recorded
-policy sets the chunks of EXTEND_ROW jobs swept over column signs."""
+policy sets the chunks of EXTEND_ROW jobs swept over column signs, and short
+permanents have the one-launch form among their candidates."""
 import json
 
 import numpy as np
@@ -59,3 +60,43 @@ def test_a_recorded_policy_sets_the_chunks_of_column_signs(pq, tmp_path, monkeyp
     assert not np.array_equal(a, b) and not np.array_equal(b, c)
     scale = np.abs(a).max()
     assert np.abs(a - b).max() <= 1e-12 * scale and np.abs(a - c).max() <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("S,T", [
+    ([1] * 20, [1] * 20),                              # binary digits
+    ([2] * 9, [2] * 9),                                # mixed radices
+])
+def test_short_permanents_tune_the_one_launch_form(pq, tmp_path, monkeypatch, S, T):
+    # a record of 0 wavefronts is the default's one launch, bit for bit; another one the longer sequence
+    m = len(S)
+    U = torch.from_numpy(workloads.haar(m, 4)).cuda()
+    plain = pq.Engine(0)
+    want = complex(plain.perm(U, S, T)[0].item())
+    plain.close()
+    path = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("PQ_AUTOTUNE_CACHE", str(path))
+    monkeypatch.setenv("PQ_AUTOTUNE", "1")
+    first = pq.Engine(0)
+    tuned = complex(first.perm(U, S, T)[0].item())
+    info = first.autotune_last()
+    first.close()
+    assert info["candidates"] == 3 and info["best_ms"] <= info["default_ms"]
+    assert abs(tuned - want) <= 1e-12 * abs(want)
+    if info["waves_per_cu"] == 0:
+        assert tuned == want
+    got = {}
+    for waves in (0, 4):
+        rewrite(path, (waves, 1, 32))
+        eng = pq.Engine(0)
+        got[waves] = complex(eng.perm(U, S, T)[0].item())
+        assert eng.autotune_last()["candidates"] == 0 and eng.autotune_last()["waves_per_cu"] == waves
+        # the allocation-free call follows the record
+        out = torch.empty(1, dtype=torch.complex128, device="cuda")
+        occ = [(pq._lib.ctypes.c_int32 * m)(*v) for v in (S, T)]
+        torch.cuda.synchronize()
+        assert eng._lib.pq_perm_noalloc(eng._ctx, U.data_ptr(), U.stride(0), m, occ[0], occ[1], out.data_ptr(), None,
+                                        torch.cuda.current_stream().cuda_stream) == 0
+        assert complex(out.item()) == got[waves]
+        eng.close()
+    assert got[0] == want
+    assert got[4] != want and abs(got[4] - want) <= 1e-12 * abs(want)
