@@ -27,7 +27,7 @@ struct BJob {
     int32_t tab;          // table index (mixed digits), -1 when binary
     int32_t m_out;        // EXTEND: number of output modes
     int32_t ext_cols;     // EXTEND: 1 when the sweep runs over the columns' signs (kModeExtCol)
-    int64_t mat_off;      // complex offset of B [r][ncmax] | rows2 [r][2][ncmax] | base [ncmax]
+    int64_t mat_off;      // complex offset of B [r][ncmax] (ext_cols: scales [r]) | rows2 [r][2][ncmax] | base [ncmax]
     int64_t idx_off;      // int32 offset of row_mode[r], row_mu[r], col_mode[nc] (extend-row jobs of a long
                           // list: and the columns' rows in ManyFinalArgs::UT)
     int64_t out_offset;
@@ -55,6 +55,8 @@ struct BPrepArgs {
     int64_t ldu;
     const BJob* jobs;
     int32_t njobs;
+    const int32_t* list;    // [nlist]: the jobs not swept over column signs, where some are
+    int32_t nlist;
     const int32_t* idx;
     cplx* mat;
 };

@@ -73,6 +73,8 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
         // lane (g, j) adds slots g, g + G, ... of column j in order; the G groups
         // of a column are then added in order
         const int G = 64 / ncol, g = t / ncol, jj = t - g * ncol;
+        // the other columns' scales (prep_ext_job)
+        const cplx others = J.ext_cols && t < ncol ? a.mat[J.mat_off + t] : cplx{0.0, 0.0};
         cdd s{{0.0, 0.0}, {0.0, 0.0}};
         if (g < G)
             for (int k = g; k < J.nchunks; k += G) {
@@ -85,7 +87,11 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
                         {__shfl(s.im.hi, from, 64), __shfl(s.im.lo, from, 64)}};
             if (g == 0) s = cdd_add(s, o);
         }
-        if (t < ncol) L[t] = cplx{(s.re.hi + s.re.lo) * J.scale, (s.im.hi + s.im.lo) * J.scale};
+        if (t < ncol) {
+            const int e = (int)others.re;
+            const cplx v{(s.re.hi + s.re.lo) * J.scale, (s.im.hi + s.im.lo) * J.scale};
+            L[t] = others.im != 0.0 ? cplx{0.0, 0.0} : cplx{ldexp(v.re, e), ldexp(v.im, e)};
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");

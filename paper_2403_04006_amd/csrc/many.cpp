@@ -98,11 +98,13 @@ struct ManyEntry {
     size_t bytes = 0;            // device block
     int mode = 0;                // kModeFwd (forward and extend jobs) or kModeAdj
     int npat = 0, ntab = 0;      // npat: distinct patterns (identical ones are swept once)
+    int nextcol = 0, nprep = 0;   // jobs swept over column signs, and beside such jobs the other swept ones
     int max_chunks = 0;          // most chunks of any pattern (1: nothing for a work queue to balance)
     int queue_pref = -1;         // the autotuner's schedule for pq_perm_batched (1 queue, 0 static, -1 none)
     size_t mat_elems = 0, partial_doubles = 0, dpat_elems = 0;
     cplx* d_ut = nullptr;        // columns of U, transposed (kTransposeMinJobs)
     int32_t* d_ut_col = nullptr; // which
+    int32_t* d_prep = nullptr;   // the others
     int nut = 0;
     std::vector<ManyClass> classes;
     ChunkPolicy policy;
@@ -283,6 +285,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     size_t mat_elems = 0, dpat_elems = 0;
     // columns of U that extend-row jobs use, and their places among them
     std::vector<int32_t> ut_col, ut_at;
+    std::vector<int32_t> others;   // jobs not swept over column signs
     if (!adj && pats.size() >= (size_t)kTransposeMinJobs) ut_at.assign((size_t)m, -1);
     int next = 0;
     Side rows, cols;
@@ -342,6 +345,8 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         b.m_inner = p.m_inner;
         b.m_out = ext ? m : 0;
         b.ext_cols = extcol ? 1 : 0;
+        E.nextcol += b.ext_cols;
+        if (!extcol) others.push_back((int32_t)k);
         b.transposed = p.transposed;
         b.time_states = p.time_states;
         b.scale = p.r == 0 ? 1.0 : p.scale;
@@ -571,6 +576,8 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         }
     }
 
+    if (E.nextcol == 0) others.clear();   // every job is theirs
+
     const size_t ut_bytes = sizeof(cplx) * ut_col.size() * (size_t)m;
     const bool ut = next >= kTransposeMinJobs && ut_bytes <= kTransposeMaxBytes;
     if (!ut) ut_col.clear();
@@ -596,6 +603,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     const size_t oDup = cv.take(sizeof(int32_t) * sz(dup_pat.size()));
     const size_t oDut = cv.take(sizeof(int64_t) * sz(dup_out.size()));
     const size_t oUc = cv.take(sizeof(int32_t) * sz(ut_col.size()));
+    const size_t oPr = cv.take(sizeof(int32_t) * sz(others.size()));
     const size_t upload_bytes = cv.off;
     const size_t oMat = cv.take(sizeof(cplx) * sz(mat_elems));
     const size_t oTab = cv.take(sizeof(StepEntry) * 2 * kMaxInner * sz(sigs.size()));
@@ -630,6 +638,8 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     E.d_ut = ut ? (cplx*)(E.dmem + oUt) : nullptr;
     E.d_ut_col = (int32_t*)(E.dmem + oUc);
     E.nut = (int)ut_col.size();
+    E.d_prep = (int32_t*)(E.dmem + oPr);
+    E.nprep = (int)others.size();
     E.d_mat = (cplx*)(E.dmem + oMat);
     E.d_tabs = (StepEntry*)(E.dmem + oTab);
     E.d_partials = (double*)(E.dmem + oPart);
@@ -656,6 +666,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     put(oDup, dup_pat.data(), sizeof(int32_t) * dup_pat.size());
     put(oDut, dup_out.data(), sizeof(int64_t) * dup_out.size());
     put(oUc, ut_col.data(), sizeof(int32_t) * ut_col.size());
+    put(oPr, others.data(), sizeof(int32_t) * others.size());
     return ctx->upload(E.dmem, stage, upload_bytes, st);
 }
 
@@ -718,7 +729,7 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     queue = queue && E.mode == kModeFwd;
     if (E.mat_elems > 0) {
         // BJob.nchunks > 0 marks every planned (non-trivial) pattern
-        BPrepArgs pa{U, ldu, E.d_jobs, E.npat, E.d_idx, E.d_mat};
+        BPrepArgs pa{U, ldu, E.d_jobs, E.npat, E.nextcol > 0 ? E.d_prep : nullptr, E.nprep, E.d_idx, E.d_mat};
         rc = ctx->check(launch_bprep(pa, st), "many prep");
         if (rc) return rc;
     }
@@ -737,6 +748,7 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     fa.ldu = ldu;
     fa.UT = E.d_ut;
     fa.m = m;
+    fa.mat = E.d_mat;
     fa.idx = E.d_idx;
     fa.dpat_off = E.d_dpat_off;
     fa.jobs = E.d_jobs;

@@ -101,6 +101,7 @@ struct ManyFinalArgs {
     const cplx* UT;            // columns of U, transposed, or null; their rows in it follow an
                                // extend-row job's modes in idx
     int32_t m;
+    const cplx* mat;
     const int32_t* idx;
     const int64_t* dpat_off;   // [npat]: complex offset of the pattern's D block
     const BJob* jobs;
