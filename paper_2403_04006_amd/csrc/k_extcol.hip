@@ -4,11 +4,8 @@
 
 namespace pq {
 
-PQ_XINST(2)
 PQ_XINST(4)
-PQ_XINST(6)
 PQ_XINST(8)
-PQ_XINST(10)
 PQ_XINST(12)
 PQ_XINST(14)
 PQ_XINST(16)

@@ -201,9 +201,14 @@ __global__ __launch_bounds__(64, NC <= 12 ? 4 : (NC <= 20 ? 3 : 2)) void extcol_
 template <int NC>
 hipError_t launch_extcol(int var, const ManyArgs& a, hipStream_t s) {
     const dim3 grid(a.nchunks > 0 ? a.nchunks : 1), block(64);
-    if (var & 1) hipLaunchKernelGGL((extcol_kernel<NC, true>), grid, block, 0, s, a);
-    else if constexpr (NC <= kExtColMaxPowers) hipLaunchKernelGGL((extcol_kernel<NC, false>), grid, block, 0, s, a);
-    else return hipErrorInvalidValue;
+    // (the classes that either variant has, PQ_XCLASS)
+    if (var & 1) {
+        if constexpr (NC >= 12) hipLaunchKernelGGL((extcol_kernel<NC, true>), grid, block, 0, s, a);
+        else return hipErrorInvalidValue;
+    } else {
+        if constexpr (NC <= 12) hipLaunchKernelGGL((extcol_kernel<NC, false>), grid, block, 0, s, a);
+        else return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -202,8 +202,13 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const FusedArgs a) {
 template <int NC>
 hipError_t launch_fused_nc(bool mix, const FusedArgs& a, int grid, hipStream_t s) {
     const size_t lds = sizeof(cplx) * (size_t)a.r * (NC <= 16 ? 16 : 32);
-    if (mix) hipLaunchKernelGGL((fused_kernel<NC, true>), dim3(grid), dim3(kBlock), lds, s, a);
-    else hipLaunchKernelGGL((fused_kernel<NC, false>), dim3(grid), dim3(kBlock), lds, s, a);
+    if (mix) {
+        hipLaunchKernelGGL((fused_kernel<NC, true>), dim3(grid), dim3(kBlock), lds, s, a);
+    } else {
+        // (collision-free patterns go by pairs of columns from there on)
+        if constexpr (NC < kPairMinCols) hipLaunchKernelGGL((fused_kernel<NC, false>), dim3(grid), dim3(kBlock), lds, s, a);
+        else return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

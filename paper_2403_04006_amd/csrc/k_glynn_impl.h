@@ -139,25 +139,35 @@ __global__ __launch_bounds__(kBlock) void glynn_mix(const GlynnArgs a) {
 
 // ------------------------------------------------------------- launchers
 // kind: kSweepMix (mixed digits, power steps within product_grouped's range),
-// kSweepBin (binary digits, unit powers), kSweepMixGeneral (any powers).
+// kSweepBin (binary digits, unit powers; from kPairMinCols to kPairMaxCols columns
+// the pair sweep takes these), kSweepMixGeneral (any powers).
+template <int NC>
+constexpr bool kHasBin = NC < kPairMinCols || NC > kPairMaxCols;
+
 template <int NC>
 static hipError_t launch_one(int kind, const GlynnArgs& a, int grid, hipStream_t st) {
-    if (kind == kSweepBin)
-        hipLaunchKernelGGL(glynn_bin<NC>, dim3(grid), dim3(kBlock), 0, st, a);
-    else if (kind == kSweepMix)
+    if (kind == kSweepBin) {
+        if constexpr (kHasBin<NC>) hipLaunchKernelGGL(glynn_bin<NC>, dim3(grid), dim3(kBlock), 0, st, a);
+        else return hipErrorInvalidValue;
+    } else if (kind == kSweepMix) {
         hipLaunchKernelGGL((glynn_mix<NC, false>), dim3(grid), dim3(kBlock), 0, st, a);
-    else
+    } else {
         hipLaunchKernelGGL((glynn_mix<NC, true>), dim3(grid), dim3(kBlock), 0, st, a);
+    }
     return hipGetLastError();
 }
 
 template <int NC>
 static int occupancy_one(int kind) {
     int nb = 0;
-    hipError_t e = kind == kSweepBin
-        ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_bin<NC>, kBlock, 0)
-        : (kind == kSweepMix ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_mix<NC, false>, kBlock, 0)
-                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_mix<NC, true>, kBlock, 0));
+    hipError_t e = hipErrorInvalidValue;
+    if (kind == kSweepBin) {
+        if constexpr (kHasBin<NC>) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_bin<NC>, kBlock, 0);
+    } else if (kind == kSweepMix) {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_mix<NC, false>, kBlock, 0);
+    } else {
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, glynn_mix<NC, true>, kBlock, 0);
+    }
     return e == hipSuccess ? nb : 0;
 }
 

@@ -213,14 +213,17 @@ uint64_t hash_pattern(const PatRef& p) {
 }
 
 // Photons up to which every EXTEND_ROW job with unit columns takes the sweep over
-// the columns' signs, in one kernel variant per four rows: 100 runs of 10 photons
-// 78 -> 47 us (91 us in a class for every two rows and either variant).
+// the columns' signs, in one kernel variant per four rows whatever the collisions:
+// 100 runs of 10 photons 78 -> 47 us (91 us in a class for every two rows and
+// either variant: a launch costs more than they save).
 constexpr int kExtColSmall = 12;
 
 // Plan of an EXTEND_ROW job over its columns' signs (k_extcol_impl.h), or false
 // where its row plan p is the better one: columns of multiplicity 1 only, and
-// fewer FP64 instructions by the count of either sweep's term (rows r with
-// repeats, columns k): 2^(k-1) (6 r + 4 rises + 4) against 16 k a row term.
+// beyond kExtColSmall rows of multiplicity 1 only.  By the FP64 instructions of
+// either sweep's terms k columns with all rows different take 2^(k-1) (6 k - 2)
+// here and 2^(k-2) 14 k over the rows; one repeated row makes that 2^(k-1) 6 k and
+// 3/4 of 2^(k-2) 14 k, and more of them favour the rows further.
 bool ext_over_columns(const Side& rows, const Side& cols, const Plan& p, Plan& pc) {
     if (rows.count < 1 || p.nc < 2) return false;
     for (int j = 0; j < cols.count; ++j)
@@ -229,13 +232,7 @@ bool ext_over_columns(const Side& rows, const Side& cols, const Plan& p, Plan& p
     if (pc.status || pc.trivial) return false;
     PowSteps ps;
     make_pow_steps(pc.col_kap, pc.nc, ps);
-    if (ps.general) return false;
-    const int rises = pc.col_kap[pc.nc - 1] - 1;
-    if (rises > 0 && pc.nc > kExtColMaxPowers) return false;
-    if (pc.n <= kExtColSmall) return true;   // three classes whatever the collisions (a launch costs more than they save)
-    const double by_cols = (double)pc.terms * (6.0 * pc.nc + 4.0 * (rises > 0 ? rises + 1 : 0) + 4.0);
-    const double by_rows = (double)p.terms * 16.0 * p.nc;
-    return by_cols < by_rows;
+    return !ps.general && (pc.n <= kExtColSmall || pc.col_kap[pc.nc - 1] == 1);
 }
 
 int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all, ManyEntry& E,

@@ -28,7 +28,6 @@ constexpr int kModeAdj = 2;       // reverse sweep: derivatives and forward sums
 constexpr int kModeAdjWalk = 3;   // reverse sweep of wide collision-free patterns (k_adjw_impl.h)
 constexpr int kModeExtCol = 4;    // EXTEND_ROW jobs over the signs of unit columns (k_extcol_impl.h)
 constexpr int kExtColDigits = 8;  // most time digits that move inside one of its chunks
-constexpr int kExtColMaxPowers = 20;   // most (padded) rows of theirs when some row repeats
 // Under pq_perm_batched its chunks are handed out by the dispatcher as in the
 // static schedule, longest first, which evens out the CUs as a queue would: popped
 // from one counter, 1000 runs of 20 photons in 400 modes take 5.7 ms instead of

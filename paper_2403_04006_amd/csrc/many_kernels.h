@@ -13,8 +13,9 @@ namespace pq {
 // reverse-sweep walk classes (binary digits, unit powers), padded column counts
 #define PQ_WCLASS(X) X(16) X(20) X(24) X(28) X(32)
 
-// extend-row sweeps over the columns' signs, padded row counts
-#define PQ_XCLASS(X) X(2) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24)
+// extend-row sweeps over the columns' signs, padded row counts: up to 12 columns in
+// fours with rows of any multiplicity, beyond in twos with unit ones
+#define PQ_XCLASS(X) X(4) X(8) X(12) X(14) X(16) X(18) X(20) X(22) X(24)
 
 // variant: 2 * binary_walk + unit_powers
 #define PQ_MDECL(MODE, NC) hipError_t launch_many_##MODE##_##NC(int var, const ManyArgs& a, hipStream_t s);

@@ -109,12 +109,15 @@ int pq_perm_noalloc(pq_ctx* ctx, const pq_c128* U, int64_t ldu, int32_t m,
     uint32_t* tickets = nullptr;
     char* ws = scratch_of(ctx->device, &tickets);
     if (!ws) return ctx->fail(PQ_EDEVICE, "pq_perm_noalloc: the static scratch of device %d was not resolved", ctx->device);
-    // what fits is decided by the sweep of single columns without the spread (its
-    // partials can need more scratch); other forms are taken where they fit too
-    const int kind = sweep_kind(p), plain = kind == kSweepPair ? kSweepBin : kind;
+    // what fits is decided by the sweep without the spread (its partials can need
+    // more scratch); other forms are taken where they fit too.  Every plan of the
+    // pair sweep is accepted (accept 0): the buffer holds its table, 73 KB at most,
+    // and its most workgroups' sums, 512 KB; and the single columns' sweep that
+    // decided before there were pairs needed at most 148 KB of the 160 for these
+    // plans under any tuned shape
+    const int kind = sweep_kind(p);
     const int wpc = single_waves_per_cu(ctx, p);
-    const int plain_wpc = std::max(1, wpc / resident_waves(ctx, p, kind)) * resident_waves(ctx, p, plain);
-    SingleLayout L = single_layout(ctx, p, plain, plain == kind ? wpc : plain_wpc, false);
+    SingleLayout L = single_layout(ctx, p, kind, wpc, false);
     if (L.accept > kNoAllocScratchBytes)
         return ctx->fail(PQ_ERANGE, "pq_perm_noalloc: this permanent needs %zu bytes of scratch, more than the %zu "
                          "bytes of the static buffer (use pq_perm)", L.accept, kNoAllocScratchBytes);

@@ -203,7 +203,7 @@ struct SingleLayout {
     int kind = 0;
     size_t oB = 0, oR = 0, oBase = 0, oTf = 0, oTb = 0, oP = 0, oL = 0, oLw = 0;
     size_t bytes = 0;
-    size_t accept = 0;   // without the lanes' sums: what pq_perm_noalloc measures
+    size_t accept = 0;   // without the lanes' sums: what pq_perm_noalloc measures (pairs: 0)
 };
 SingleLayout single_layout(pq_ctx* ctx, const Plan& p, int kind, int waves_per_cu, bool spread = true);
 
