@@ -63,20 +63,6 @@ __device__ __forceinline__ void halve_sums(cplx* x, int lane) {
     }
 }
 
-// A[i] += dd P for the uniform index i in [Q, T): one branch per entry (selects
-// over all of them would cost six instructions each).
-template <int Q, int T>
-__device__ __forceinline__ void flip_sums(cplx (&A)[T], int i, double dd, const cplx& P) {
-    if constexpr (Q < T) {
-        if (i == Q) {
-            cfma_to(A[Q], dd, P);
-            keep_branch(A[Q]);
-        } else {
-            flip_sums<Q + 1, T>(A, i, dd, P);
-        }
-    }
-}
-
 // Slots of the per-wavefront sums: the terms' sum, the six lane columns, then
 // the time columns.
 constexpr int kChainSums = 32;

@@ -21,20 +21,6 @@
 
 namespace pq {
 
-// A[i] += dd P for the uniform index i in [Q, T): one branch per entry
-// (selects over all of them would cost six instructions each).
-template <int Q, int T>
-__device__ __forceinline__ void extcol_flip(cplx (&A)[T], int i, double dd, const cplx& P) {
-    if constexpr (Q < T) {
-        if (i == Q) {
-            cfma_to(A[Q], dd, P);
-            keep_branch(A[Q]);
-        } else {
-            extcol_flip<Q + 1, T>(A, i, dd, P);
-        }
-    }
-}
-
 // Double-double sums over the 64 lanes of N (a power of two) values per lane
 // by recursive halving, in a fixed order: lane l ends with value
 // l / (64 / N) in x[0].
@@ -143,7 +129,7 @@ __global__ __launch_bounds__(64, NC <= 12 ? 4 : (NC <= 20 ? 3 : 2)) void extcol_
             if (b + 1 < blocks) {
                 const int i = 3 + __builtin_ctz(b + 1);
                 const int sel = (int)(((t + 8) >> (i + 1)) & 1u);
-                extcol_flip<3, T>(A, i, sel ? -2.0 : 2.0, P);
+                flip_sums<3, T>(A, i, sel ? -2.0 : 2.0, P);
                 add_row_at<NC, true>(c, trows, ((size_t)i * 2 + sel) * NC);
             }
         }

@@ -40,13 +40,6 @@ __device__ __forceinline__ HafLadderLds haf_ladder_setup(const HafLadderArgs& a,
     return L;
 }
 
-__device__ __forceinline__ void haf_madd(cplx& v, const cplx& a, const cplx& b) {
-    v.re = __builtin_fma(a.re, b.re, v.re);
-    v.re = __builtin_fma(-a.im, b.im, v.re);
-    v.im = __builtin_fma(a.re, b.im, v.im);
-    v.im = __builtin_fma(a.im, b.re, v.im);
-}
-
 // h of the vector of rank idx at level s from levels s - 1 (h1, loops only)
 // and s - 2 (h2).  Four photons' loads are issued before the first is used.
 __device__ __forceinline__ cplx haf_ladder_value(const HafLadderLds& L, int d, int P, int s, bool loops,
@@ -56,7 +49,7 @@ __device__ __forceinline__ cplx haf_ladder_value(const HafLadderLds& L, int d, i
     uint32_t rank = idx - row0[q0];
     const cplx* Aq = L.A + q0 * d;
     cplx v{0.0, 0.0};
-    if (loops) haf_madd(v, L.gamma[q0], h1[rank]);
+    if (loops) cmadd(v, L.gamma[q0], h1[rank]);
     uint32_t at = rank;
     for (int p0 = 1; p0 < s; p0 += 4) {
         cplx x[4];
@@ -75,7 +68,7 @@ __device__ __forceinline__ cplx haf_ladder_value(const HafLadderLds& L, int d, i
         }
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            if (p0 + g < s) haf_madd(v, Aq[qs[g]], x[g]);
+            if (p0 + g < s) cmadd(v, Aq[qs[g]], x[g]);
     }
     return v;
 }

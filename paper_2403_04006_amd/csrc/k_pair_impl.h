@@ -36,14 +36,6 @@ namespace pq {
 
 typedef const __attribute__((address_space(4))) cplx pair_kc;
 
-// acc += a * b, acc -= a * b
-__device__ __forceinline__ void pair_mac(cplx& acc, const cplx& a, const cplx& b) {
-    acc.re = __builtin_fma(a.re, b.re, acc.re);
-    acc.im = __builtin_fma(a.re, b.im, acc.im);
-    acc.re = __builtin_fma(-a.im, b.im, acc.re);
-    acc.im = __builtin_fma(a.im, b.re, acc.im);
-}
-
 // One pair's moves of a step (of its two sums and of O), and its a_k b_k.
 struct PairMove {
     cplx x, y, o[4];
@@ -122,7 +114,7 @@ __device__ __forceinline__ void pair_walk(const PairArgs& a, int lane, cplx (*bu
                 const cplx ak{v[8 * p + 2 * k].re, v[8 * p + 2 * k].im};
                 const cplx bk{v[8 * p + 2 * k + 1].re, v[8 * p + 2 * k + 1].im};
                 o[p][k] = cmul(c[p], bk);
-                pair_mac(o[p][k], d[p], ak);
+                cmadd(o[p][k], d[p], ak);
             }
     }
 
@@ -189,7 +181,7 @@ __device__ __forceinline__ void pair_walk(const PairArgs& a, int lane, cplx (*bu
 #pragma unroll
             for (int k = T0; k < T0 + TERMS; ++k) {
                 if (k >= EARLY) q[k] = s[k][lane];
-                pair_mac(k < 4 ? up : dn, pr[k], q[k]);
+                cmadd(k < 4 ? up : dn, pr[k], q[k]);
             }
             // block t - 1: a step changes the sign
             const double w = (t & 1) ? 1.0 : -1.0;

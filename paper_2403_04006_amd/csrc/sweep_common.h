@@ -145,4 +145,18 @@ __device__ __forceinline__ double lane_init(const GlynnArgs& a, int lane, cplx (
     return lane_init<NC>(a.base, a.rows2, a.n_lane, a.lane_states, a.lane_radix, lane, c);
 }
 
+// A[i] += dd P for the uniform index i in [Q, T): one branch per entry
+// (selects over all of them would cost six instructions each).
+template <int Q, int T>
+__device__ __forceinline__ void flip_sums(cplx (&A)[T], int i, double dd, const cplx& P) {
+    if constexpr (Q < T) {
+        if (i == Q) {
+            cfma_to(A[Q], dd, P);
+            keep_branch(A[Q]);
+        } else {
+            flip_sums<Q + 1, T>(A, i, dd, P);
+        }
+    }
+}
+
 }  // namespace pq
