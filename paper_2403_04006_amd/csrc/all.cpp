@@ -205,8 +205,13 @@ int all_cache(pq_ctx* ctx, AllCache** out) {
 int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int32_t* S, double norm_s,
                uint64_t outputs, cplx* perm, cplx* amp, hipStream_t st, bool& done) {
     done = false;
-    const uint64_t c1 = compositions(m, n - 1, (uint64_t)kAllMaxOutputs);
-    const uint64_t c2 = n > 1 ? compositions(m, n - 2, (uint64_t)kAllMaxOutputs) : 1;
+    int jmax = 0;
+    for (int j = 1; j < m; ++j)
+        if (S[j] > S[jmax]) jmax = j;
+    const int s1 = S[jmax] > 3 ? S[jmax] : 0;
+    // the levels n - 1 and n - 2, as far as there are any
+    const uint64_t c1 = s1 < n ? compositions(m, n - 1, (uint64_t)kAllMaxOutputs) : 1;
+    const uint64_t c2 = s1 < n - 1 && n > 1 ? compositions(m, n - 2, (uint64_t)kAllMaxOutputs) : 1;
     if ((c1 + c2) * sizeof(cplx) > kAllLadderBytes) return PQ_OK;
     Carve cv;
     const size_t oBuf[2] = {cv.take(sizeof(cplx) * (size_t)c1), cv.take(sizeof(cplx) * (size_t)c2)};
@@ -221,20 +226,23 @@ int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int3
     a.m = m;
     a.n = n;
     int k = 0;
+    for (; k < s1; ++k) a.col[k] = (uint8_t)jmax;
     for (int j = 0; j < m; ++j)
-        for (int c = 0; c < S[j]; ++c) a.col[k++] = (uint8_t)j;
+        for (int c = 0; c < S[j] && (s1 == 0 || j != jmax); ++c) a.col[k++] = (uint8_t)j;
+    a.s1 = s1;
     a.norm_s = norm_s;
     a.perm = perm;
     a.amp = amp;
     // level n - 1 goes to the first buffer, n - 2 to the second, and so on
     auto level_buf = [&](int lv) { return (cplx*)(ws + oBuf[(n - 1 - lv) & 1]); };
-    // the small kernel starts at level 3 at the latest (levels 1 to 3 need no
-    // level below); every level but its last stays in LDS
+    // the small kernel's first level is the last of those that need none below
+    // (1 to 3, or s1); every level but its last stays in LDS
     auto small = [&](int lv, int limit) {
         return m * lv <= kAllLadderCols && compositions(m, lv, (uint64_t)kAllMaxOutputs) <= (uint64_t)limit;
     };
-    a.k0 = 1;
-    while (a.k0 < n && small(a.k0 + 1, kAllLadderFirst) && (a.k0 < 3 || small(a.k0, kAllLadderSmall))) ++a.k0;
+    a.k0 = s1 == 0 ? 1 : small(s1, kAllLadderFirst) ? s1 : 0;
+    const int direct = s1 ? s1 : 3;
+    while (a.k0 > 0 && a.k0 < n && small(a.k0 + 1, kAllLadderFirst) && (a.k0 < direct || small(a.k0, kAllLadderSmall))) ++a.k0;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc;
     if (ctx->profiling) {
@@ -244,9 +252,11 @@ int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int3
         rc = ctx->check(hipEventRecord(e0, st), "profile: record");
         if (rc) return rc;
     }
-    rc = ctx->check(launch_all_ladder_small(a, a.k0 < n ? level_buf(a.k0) : nullptr, st), "all-outputs ladder");
-    if (rc) return rc;
-    for (int lv = a.k0 + 1; lv <= n; ++lv) {
+    if (a.k0 > 0) {
+        rc = ctx->check(launch_all_ladder_small(a, a.k0 < n ? level_buf(a.k0) : nullptr, st), "all-outputs ladder");
+        if (rc) return rc;
+    }
+    for (int lv = a.k0 > 0 ? a.k0 + 1 : s1; lv <= n; ++lv) {
         const uint64_t count = lv == n ? outputs : compositions(m, lv, (uint64_t)kAllMaxOutputs);
         la.k = lv;
         la.count = (uint32_t)count;
@@ -254,7 +264,7 @@ int run_ladder(pq_ctx* ctx, const cplx* U, int64_t ldu, int m, int n, const int3
         const uint64_t most = (uint64_t)ctx->num_cu * 16;
         const uint64_t per = (count + most - 1) / most;
         la.run = (uint32_t)((per + kBlock - 1) / kBlock * kBlock);
-        la.in = level_buf(lv - 1);
+        la.in = lv == s1 ? nullptr : level_buf(lv - 1);
         la.out = lv < n ? level_buf(lv) : nullptr;
         rc = ctx->check(launch_all_ladder_level(la, st), "all-outputs ladder");
         if (rc) return rc;

@@ -70,10 +70,18 @@ struct AllOutArgs {
 // in the same step, the searches for q_p and the loads run without branches.
 // One workgroup runs the levels of a few thousand values in LDS, one launch
 // each of the others; two levels below the outputs live in workspace.
+// The first level needs none below: levels 1 to 3 directly, and s photons in one
+// input mode j at once,
+//   perm_s(T) = s! prod_i U[i][j]^{t_i},
+// so the input mode of the most photons goes first where these are four or more.
 // Whole calls (sweep or contraction -> ladder): 23 -> 16 us at 5 photons in 12
 // modes, 47 -> 31 us at 8 in 12, 97 -> 44 us at 8 in 16, 1268 -> 111 us at 11 in
-// 14 and 850 -> 112 us at 10 in 16; no measured size was faster in another form,
-// so by default it is taken whenever its two lower levels fit kAllLadderBytes.
+// 14 and 850 -> 112 us at 10 in 16.  Photons of one input mode: 16 in 8 modes
+// 35 -> 17 us, 48 in 3 70 -> 28, 10 in 16 187 -> 49 (92, 362 and 119 when every
+// photon was a level).  What is slower than the sweep are many photons of two input
+// modes in few modes, where that has few terms: 7 + 7 in 6 modes 41 -> 58 us, 8 + 8
+// in 8 61 -> 70; its sums cancel there (5e-15 of the value against 6e-16), so by
+// default the ladder is taken whenever its two lower levels fit kAllLadderBytes.
 constexpr uint64_t kAllLadderBytes = 1ull << 30;   // workspace of the two lower levels
 constexpr int kAllLadderSmall = 2048;              // values of a level kept in LDS
 constexpr int kAllLadderFirst = 4096;              // values of the last level that the small kernel takes
@@ -85,7 +93,8 @@ struct AllLadderArgs {
     const cplx* U;
     int64_t ldu;
     int32_t m, n;
-    int32_t k0;                        // levels 1..k0 of the first kernel
+    int32_t s1;                        // photons of the first input mode where they make the first level, or 0
+    int32_t k0;                        // last level of the first kernel (0: there is none)
     uint8_t col[kAllMaxPhotons];       // input mode of photon k + 1
     double norm_s;                     // 1 / sqrt(prod S!)
     cplx* perm;
@@ -96,7 +105,7 @@ struct AllLadderArgs {
 // k == n (perm and amp of AllLadderArgs).
 struct AllLevelArgs {
     AllLadderArgs a;
-    int32_t k;
+    int32_t k;                         // (a.s1: the first level, which has no input)
     uint32_t count;                    // outputs of level k
     uint32_t run;                      // consecutive outputs per workgroup, a multiple of kBlock
     const cplx* in;

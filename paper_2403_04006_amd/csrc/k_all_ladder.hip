@@ -1,6 +1,8 @@
 // Kernels of the all-outputs ladder (see all.h).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "all.h"
 #include "device.h"
 #include "ladder.h"
@@ -82,6 +84,31 @@ __device__ __forceinline__ cplx ladder_first(int k, int m, int P, const uint32_t
     return v;
 }
 
+// The first level where its k photons are in one input mode: k! times the product
+// of its column u over the output's photons (the factors of k! one by one, so that
+// nothing over- or underflows that the value itself does not).
+template <bool LAST>
+__device__ __forceinline__ cplx ladder_direct(int k, int P, const uint32_t* G, const cplx* u, const double* rs,
+                                              uint32_t idx, double& nrm) {
+    uint32_t rank = idx;
+    int qlast = -1, run = 0;
+    cplx v{1.0, 0.0};
+    for (int p = 0; p < k; ++p) {
+        const uint32_t* row = G + (k - p) * P;
+        const int q = ladder_mode(row, P, rank);
+        rank -= row[q];
+        const cplx f = u[q];
+        const double c = (double)(p + 1);
+        v = cmul(v, cplx{c * f.re, c * f.im});
+        if (LAST) {
+            run = q == qlast ? run + 1 : 1;
+            qlast = q;
+            nrm *= rs[run];
+        }
+    }
+    return v;
+}
+
 // Levels up to k0 by one workgroup in LDS (at most kAllLadderSmall values, the
 // last one, which goes to `out` or the outputs, kAllLadderFirst).  Bound by the
 // latency of its dependent rounds, not by work: 11 us for the first four levels
@@ -102,7 +129,8 @@ __global__ __launch_bounds__(kAllLadderBlock) void all_ladder_small_kernel(const
             u[e] = a.U[(size_t)(m - 1 - q) * (size_t)a.ldu + a.col[k]];
         }
     __syncthreads();
-    for (int k = a.k0 < 3 ? a.k0 : 3; k <= a.k0; ++k) {
+    const int first = a.s1 ? a.s1 : (a.k0 < 3 ? a.k0 : 3);
+    for (int k = first; k <= a.k0; ++k) {
         // vectors of k photons in m modes: those of the last m - 1 with at
         // most k, i.e. the sum of a column of G
         uint32_t count = 0;
@@ -112,10 +140,12 @@ __global__ __launch_bounds__(kAllLadderBlock) void all_ladder_small_kernel(const
         for (uint32_t idx = (uint32_t)tid; idx < count; idx += kAllLadderBlock) {
             double nrm = a.norm_s;
             const cplx* uk = u + (k - 1) * m;
-            const cplx v = k < n ? (k <= 3 ? ladder_first<false>(k, m, P, G, u, rs, idx, nrm)
-                                           : ladder_value<false>(k, P, G, uk, rs, in, idx, nrm))
-                                 : (k <= 3 ? ladder_first<true>(k, m, P, G, u, rs, idx, nrm)
-                                           : ladder_value<true>(k, P, G, uk, rs, in, idx, nrm));
+            auto value = [&](auto last) {
+                constexpr bool LAST = decltype(last)::value;
+                if (k > first) return ladder_value<LAST>(k, P, G, uk, rs, in, idx, nrm);
+                return a.s1 ? ladder_direct<LAST>(k, P, G, u, rs, idx, nrm) : ladder_first<LAST>(k, m, P, G, u, rs, idx, nrm);
+            };
+            const cplx v = k < n ? value(std::false_type{}) : value(std::true_type{});
             if (k == n) {
                 a.perm[idx] = v;
                 if (a.amp) a.amp[idx] = cplx{v.re * nrm, v.im * nrm};
@@ -138,7 +168,7 @@ __global__ __launch_bounds__(kAllLadderBlock) void all_ladder_small_kernel(const
 // the outputs: 52 us for the 3,268,760 outputs of 10 photons in 16 modes
 // (2.0 TB/s written).  Walking the modes instead of the photons took 79 us, the
 // wavefronts splitting at every mode.
-template <bool LAST>
+template <bool LAST, bool FIRST>
 __global__ __launch_bounds__(kBlock) void all_ladder_level_kernel(const AllLevelArgs p) {
     extern __shared__ double lds[];
     const AllLadderArgs& a = p.a;
@@ -162,7 +192,9 @@ __global__ __launch_bounds__(kBlock) void all_ladder_level_kernel(const AllLevel
     for (uint64_t e = first + (uint64_t)tid; e < last; e += kBlock) {
         const uint32_t idx = (uint32_t)e;
         double nrm = a.norm_s;
-        const cplx v = ladder_value<LAST>(p.k, P, G, u, rs, p.in, idx, nrm);
+        cplx v;
+        if constexpr (FIRST) v = ladder_direct<LAST>(p.k, P, G, u, rs, idx, nrm);
+        else v = ladder_value<LAST>(p.k, P, G, u, rs, p.in, idx, nrm);
         if (LAST) {
             a.perm[idx] = v;
             if (a.amp) a.amp[idx] = cplx{v.re * nrm, v.im * nrm};
@@ -174,22 +206,25 @@ __global__ __launch_bounds__(kBlock) void all_ladder_level_kernel(const AllLevel
 
 hipError_t launch_all_ladder_small(const AllLadderArgs& a, cplx* out, hipStream_t s) {
     if (a.m < 1 || a.m > kAllMaxModes || a.n < 1 || a.n > kAllMaxPhotons || a.k0 < 1 || a.k0 > a.n ||
-        a.m * a.k0 > kAllLadderCols || (a.k0 < a.n && !out))
+        a.s1 > a.k0 || a.m * a.k0 > kAllLadderCols || (a.k0 < a.n && !out))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(all_ladder_small_kernel, dim3(1), dim3(kAllLadderBlock), 0, s, a, out);
     return hipGetLastError();
 }
 
 hipError_t launch_all_ladder_level(const AllLevelArgs& a, hipStream_t s) {
-    if (a.run == 0 || a.run % kBlock || a.k < 2 || a.k > a.a.n) return hipErrorInvalidValue;
+    const bool first = a.k == a.a.s1;
+    if (a.run == 0 || a.run % kBlock || a.k < 2 || a.k > a.a.n || (!first && !a.in)) return hipErrorInvalidValue;
     // whole eighths, so that the permuted run index covers every run (runs
     // past the last output are empty)
     const uint64_t runs = ((uint64_t)a.count + a.run - 1) / a.run;
     const dim3 grid((unsigned)((runs + 7) / 8 * 8)), block(kBlock);
     const size_t k = (size_t)a.k, m = (size_t)a.a.m;
     const size_t lds = sizeof(cplx) * m + sizeof(double) * (k + 1) + sizeof(uint32_t) * (size_t)ladder_stride(a.a.m) * (k + 1);
-    if (a.k == a.a.n) hipLaunchKernelGGL(all_ladder_level_kernel<true>, grid, block, lds, s, a);
-    else hipLaunchKernelGGL(all_ladder_level_kernel<false>, grid, block, lds, s, a);
+    if (first && a.k == a.a.n) hipLaunchKernelGGL((all_ladder_level_kernel<true, true>), grid, block, lds, s, a);
+    else if (first) hipLaunchKernelGGL((all_ladder_level_kernel<false, true>), grid, block, lds, s, a);
+    else if (a.k == a.a.n) hipLaunchKernelGGL((all_ladder_level_kernel<true, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((all_ladder_level_kernel<false, false>), grid, block, lds, s, a);
     return hipGetLastError();
 }
 
