@@ -229,13 +229,19 @@ int describe(pq_ctx* ctx, const int32_t* reps, int d, int N, bool loops, HafDesc
 
 // The table form (see haf.h): plan for a list of patterns, or false where it
 // does not apply (an invalid pattern, left to the sweeps' checks, included).
-// Taken when it is the cheaper one, in ns: about 5000 per launch and 2 per 1000
-// photon steps, against the sweeps' 25000, 120 per pattern (the host plans
-// each) and 2 (loops: 6) per 1000 Gray terms.  Both sides measured (sweeps ->
-// table, us a call): 10 patterns of 2 photons 28 -> 16; 1820 of 12 in 5 modes
-// 248 -> 33; 6435 of 8 in 8 with loops 872 -> 60; 20349 of 16 in 6 2830 -> 125
-// (3070 -> 132 with loops), there 50 us of kernels and 75 us of packing the
-// patterns on the host.
+// Taken when it is the cheaper one, in ns:
+//   the table: 5000 per launch, 400 and 160 per photon and round of the workgroup
+//     for a level of the small kernel, 160 per photon of another level, and 2 per
+//     1000 photon steps (a level's photons are a chain of dependent searches);
+//   the sweeps: 22000, 120 per pattern (the host plans each), 2000 per kernel
+//     variant that the list's patterns may need, 2 (loops: 6) per 1000 Gray terms,
+//     and 250 more where the patterns' step tables differ, which the host makes.
+// Both sides measured (sweeps -> table, us a call): 10 patterns of 2 photons 28 ->
+// 16; 1820 of 12 in 5 modes 248 -> 33; 6435 of 8 in 8 with loops 872 -> 60; 20349
+// of 16 in 6 2830 -> 125 (3070 -> 132 with loops), there 50 us of kernels and 75 us
+// of packing the patterns on the host; 200 of 24 in 6 252 -> 97.  The other way:
+// one pattern of 32 photons in 2 modes 21 and 57, of 64 in 2 24 and 186, four of
+// 60 in 3 101 and 337, one of 24 in 4 24 and 69.
 bool plan_ladder(const int32_t* reps, int d, int npat, bool loops, HafLadderArgs& a) {
     memset(&a, 0, sizeof(a));
     std::vector<int32_t> top((size_t)d, 0);
@@ -267,7 +273,7 @@ bool plan_ladder(const int32_t* reps, int d, int npat, bool loops, HafLadderArgs
     a.N = N;
     a.npat = npat;
     // vectors per level: C(s + d - 1, s); odd levels are empty without loops
-    double steps = 0.0;
+    double steps = 0.0, chain = 0.0;
     uint64_t off = 0, count = 1;
     int launches = 1;
     for (int s = 0; s <= N; ++s) {
@@ -278,16 +284,23 @@ bool plan_ladder(const int32_t* reps, int d, int npat, bool loops, HafLadderArgs
         off += here;
         a.off[s + 1] = (uint32_t)off;
         steps += (double)here * s;
-        if (here <= (uint64_t)kHafLadderSmall && a.s0 + 1 >= s) a.s0 = s;
-        else if (here) ++launches;
+        if (here <= (uint64_t)kHafLadderSmall && a.s0 + 1 >= s) {
+            a.s0 = s;
+            if (here) chain += 400.0 + 160.0 * s * (double)((here + kHafLadderBlock - 1) / kHafLadderBlock);
+        } else if (here) {
+            ++launches;
+            chain += 160.0 * s;
+        }
     }
     if (a.s0 < N) ++launches;
-    const double ladder_ns = 5000.0 * launches + 0.002 * steps;
-    double sweep_ns = 25000.0 + 120.0 * npat;
+    const double ladder_ns = 5000.0 * launches + chain + 0.002 * steps;
+    double sweep_ns = 22000.0 + 120.0 * npat;
+    if (a.d > 2) sweep_ns += 2000.0 * std::min(npat - 1, 6) * std::min(1.0, (a.d - 2) / 6.0);
+    const double per_term = (loops ? 0.006 : 0.002) + 0.25 * std::min(1.0, std::max(0, a.d - 2) / 2.0);
     for (int q = 0; q < npat && ladder_ns >= sweep_ns; ++q) {
         double terms = 0.5;
         for (int i = 0; i < d; ++i) terms *= (double)(reps[(size_t)q * d + i] + 1);
-        sweep_ns += (loops ? 0.006 : 0.002) * terms;
+        sweep_ns += per_term * terms;
     }
     return ladder_ns < sweep_ns;
 }

@@ -1,7 +1,7 @@
 """Tables of (loop) hafnians at the most photons that a pattern may have (64),
-and one and two fewer, on few modes: every vector of the totals, or as many as
-the level-by-level form needs to be the cheaper one, against the recursion over
-the last mode in 80-bit arithmetic."""
+and one and two fewer, on few modes, in lists as long as the level-by-level form
+needs to be the cheaper one, against the recursion over the last mode in 80-bit
+arithmetic."""
 import numpy as np
 import pytest
 
@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 EPS = float(np.finfo(np.float64).eps)
+LIST = 8000   # patterns that make a table of 64 photons the cheaper form
 
 
 @pytest.fixture(scope="module")
@@ -68,6 +69,7 @@ def test_tables_up_to_64_photons(eng, d, cap, totals, loops):
     gamma = 0.5 * (rng.standard_normal(d) + 1j * rng.standard_normal(d)) if loops else None
     caps = [cap] * d
     reps = patterns(d, [n for n in totals if n <= d * cap], caps, 2500)
+    reps = np.tile(reps, (-(-LIST // len(reps)), 1))
     got = eng.lhaf_many(torch.from_numpy(A).cuda(), None if gamma is None else torch.from_numpy(gamma).cuda(), reps)
     got = got.cpu().numpy()
     base = np.cumprod([1] + [cap + 1] * (d - 1))
@@ -87,8 +89,10 @@ def test_one_pattern_of_64_photons(eng, reps, loops):
     A = 0.3 * (rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))
     A = np.triu(A) + np.triu(A, 1).T
     gamma = 0.5 * (rng.standard_normal(d) + 1j * rng.standard_normal(d)) if loops else None
-    got = complex(eng.lhaf_many(torch.from_numpy(A).cuda(), None if gamma is None else torch.from_numpy(gamma).cuda(),
-                                [reps]).cpu()[0])
+    out = eng.lhaf_many(torch.from_numpy(A).cuda(), None if gamma is None else torch.from_numpy(gamma).cuda(),
+                        np.tile(np.array([reps], np.int32), (LIST, 1))).cpu().numpy()
+    got = complex(out[0])
+    assert np.array_equal(out, np.full_like(out, got))
     g = gamma if loops else np.zeros(d)
     ref = complex(recursion(A, g, reps)[-1])
     size = abs(complex(recursion(np.abs(A), np.abs(g), reps)[-1]))
