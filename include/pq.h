@@ -437,7 +437,9 @@ int pq_all_outputs_gemm(pq_ctx* ctx, int mode);
  *           |perm(U_{r_1..r_{k-1}, l ; order[0..k-1]})|^2,
  * and writes out[s][k-1] = r_k.  Averaged over uniformly random orders and
  * uniforms, the multiset {r_k} follows the Born rule of Eq. BS_prob.
- *   U         device, m x m, leading dimension ldu >= m.
+ *   U         device, m x m, leading dimension ldu >= m; an interferometer's
+ *             columns, of like norms (the sums' rounding is relative to the
+ *             largest's).
  *   order     device int32[samples * n], input modes in [0, m), repeats allowed.
  *   uniforms  device double[samples * n].
  *   out       device int32[samples * n], written.

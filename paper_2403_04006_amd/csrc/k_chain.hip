@@ -30,6 +30,12 @@
 // the card holds under them.  4.7 ms against 6.3 for the row form with four lanes
 // a term; 100 such samples (eight wavefronts each) 1.00 ms against 2.12, 529 of 12
 // photons 70 us against 104 (there the draws, which one thread made mode by mode).
+// Small calls are level, or a little slower: one sample of 8 photons in 16 modes
+// 41 us against 37, in 30 modes 41 against 43.
+//
+// Every term sums over all k columns, so the M_j carry an error relative to the
+// largest column's; the columns of an interferometer, lossless or dilated, are
+// unit vectors.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

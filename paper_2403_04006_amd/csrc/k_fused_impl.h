@@ -12,10 +12,11 @@
 // 1; so the weight follows from the product over the digits above, which lane k
 // keeps for digit k.
 //
-// Bound by the host's part of a call up to 20 photons (16 us at 40 modes; 24 with
-// three launches), beyond by latency: the launch, one round of loads of U, a
-// start-up of r rows' additions (as long as seven steps at 20 rows) and the
-// ticket.
+// Bound by the host's part of a call up to about 16 photons (13 us for 6 photons in
+// 12 modes, where the kernel takes 4); at 20 photons in 40 modes the two are level
+// (16.4 us to submit a call, 16 to 16.6 for the kernel).  The kernel is bound by
+// latency: the launch, one round of loads of U, a start-up of r rows' additions (as
+// long as seven steps at 20 rows) and the ticket.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -53,6 +53,8 @@ static_assert(kTuneCandidates[0].waves_per_cu == ChunkPolicy().waves_per_cu &&
 // From this many time states on, a forward job of 13..22 columns is padded to an
 // even number of them instead of a multiple of four: two columns less are a
 // tenth of its work, where a class more is one more launch and its uneven end.
+// 256 patterns of 40 photons, both ways in turn on one card: 100.0 and 96.0 ms,
+// 98.1 and 95.1 (runs of one side differ by 0.4 %).
 constexpr uint64_t kEvenClassStates = 1 << 18;
 // From this many extend-row jobs on, their final step reads the columns of U that
 // they use, transposed (one launch more; 19,000 jobs on 400 modes: 230 us of final
@@ -64,7 +66,10 @@ constexpr size_t kTransposeMaxBytes = (size_t)32 << 20;
 // holds a forward and a reverse plan for each of its pattern sets; 4096 patterns
 // of 8 photons take 5 MB).  A block of its own costs a large new list more than
 // one given back just before: gradients of new 23-photon patterns (19 MB each)
-// 430 us a call with 16 of them kept, 250 with four.
+// 430 us a call with 16 of them kept, 250 with four.  Small new lists pay it from
+// the fifth to the sixteenth of a ctx, 20 to 30 us each (16 gradients of 8 photons
+// 74 -> 105 us, 64 permanents of 12 128 -> 172); from then on a new list takes the
+// place of the oldest.
 constexpr int kMinManyEntries = 4;
 constexpr int kMaxManyEntries = 16;
 constexpr size_t kMaxManyBytes = (size_t)64 << 20;
