@@ -24,7 +24,7 @@ sys.path.insert(0, ROOT)
 
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # 256 CUs x 2.4 GHz x 128 FP64 flop/clk/CU
 
-# HBM traffic of one n=30 sweep launch, from two rocprofv3 --pmc passes
+# HBM traffic of one n=30 sweep launch of the one-by-one walk, from two rocprofv3 --pmc passes
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) over this script with
 # --calib-copy-mib 256; each scaled by what the same counter read for a plain
 # 256 MiB device-to-device copy in the same run (FETCH 131089.2 KiB, WRITE
@@ -37,6 +37,16 @@ SWEEP_TRAFFIC = {
     "n": 30,
     "fetch_kib": 242.2, "write_kib": 48.0,
     "fetch_factor": 262144.0 / 131089.2, "write_factor": 1.0,
+}
+
+# The same for the pair sweep of n=30 (pair_kernel<8, 7>).
+PAIR_TRAFFIC = {
+    "sources": ["k_pair_impl.h", "k_pair_p1.hip", "device.h", "pq_common.h", "kernels.h", "runtime.cpp", "runtime.h",
+                "plan.cpp", "plan.h", "api.cpp", "k_misc.hip"],
+    "sha256": "0769a278cb7c5fa34828911384b49c4c59ebd0e5a929ed585e67ec8bd976cdce",
+    "n": 30,
+    "fetch_kib": 447.8, "write_kib": 705.2,
+    "fetch_factor": 262144.0 / 131088.6, "write_factor": 1.0,
 }
 
 
@@ -62,11 +72,10 @@ def repeated_flops(S, T) -> tuple:
     return float(info["terms"]) * nominal, float(info["terms"]) * executed
 
 
-def sweep_traffic_bytes(n: int):
+def sweep_traffic_bytes(n: int, t: dict = SWEEP_TRAFFIC):
     """Calibrated HBM bytes per sweep launch, or None when the kernel sources
     differ from those the counters were taken on."""
     import hashlib
-    t = SWEEP_TRAFFIC
     if n != t["n"]:
         return None
     h = hashlib.sha256()
@@ -648,7 +657,7 @@ def main() -> int:
             "peak": FP64_VECTOR_PEAK_TFLOPS,
             "unit": "TFLOP/s",
             "frac": achieved_tflops / FP64_VECTOR_PEAK_TFLOPS,
-            "traffic": sweep_traffic_bytes(n),
+            "traffic": sweep_traffic_bytes(n, PAIR_TRAFFIC if 23 <= n <= 32 else SWEEP_TRAFFIC),
             "kernel": f"pair_kernel<{(n + 3) // 4}, {(n + 1) // 4}>" if 23 <= n <= 32 else f"glynn_bin<{n}>",
             "flops_per_launch": executed_flops,
             # of the walk that takes one term at a time

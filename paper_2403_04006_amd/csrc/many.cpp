@@ -290,6 +290,11 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     std::vector<int32_t> others;   // jobs not swept over column signs
     if (!adj && pats.size() >= (size_t)kTransposeMinJobs) ut_at.assign((size_t)m, -1);
     int next = 0;
+    {
+        size_t ints = 0;   // iterated modes and multiplicities, the other side's modes, places
+        for (const PatRef& p : pats) ints += 2 * (size_t)std::max(p.nr, p.nc) + (size_t)std::min(p.nr, p.nc) + (size_t)p.nc;
+        hidx.reserve(ints);
+    }
     Side rows, cols;
     for (size_t k = 0; k < pats.size(); ++k) {
         const PatRef& ps = pats[k];
