@@ -28,8 +28,7 @@ struct BJob {
     int32_t m_out;        // EXTEND: number of output modes
     int32_t ext_cols;     // EXTEND: 1 when the sweep runs over the columns' signs (kModeExtCol)
     int64_t mat_off;      // complex offset of B [r][ncmax] (ext_cols: scales [r]) | rows2 [r][2][ncmax] | base [ncmax]
-    int64_t idx_off;      // int32 offset of row_mode[r], row_mu[r], col_mode[nc] (extend-row jobs of a long
-                          // list: and the columns' rows in ManyFinalArgs::UT)
+    int64_t idx_off;      // int32 offset of row_mode[r], row_mu[r], col_mode[nc]
     int64_t out_offset;
     uint64_t time_states;
     double scale;         // 2^{-(n-1)} of the swept sum (1 when no row is swept)

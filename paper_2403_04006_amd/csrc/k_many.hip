@@ -9,8 +9,8 @@ namespace pq {
 
 // Final step of distinct pattern p, run by one whole wavefront (t = lane):
 // add its chunk slots in slot order and write the value to every copy's
-// output.  L is LDS scratch of kMaxExtendCols entries (extend-row jobs).
-__device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int t, cplx* L) {
+// output.  L and C are LDS scratch of kMaxExtendCols entries (extend-row jobs).
+__device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int t, cplx* L, int* C) {
     const int cls = a.pat_class[p];
     const int q0 = a.dup_off[p], q1 = a.dup_off[p + 1];
     if (a.adjoint && t == 0) {
@@ -73,6 +73,11 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
         // lane (g, j) adds slots g, g + G, ... of column j in order; the G groups
         // of a column are then added in order
         const int G = 64 / ncol, g = t / ncol, jj = t - g * ncol;
+        if (t < ncol) {
+            // the column, or its row among the transposed ones
+            const int c = a.idx[J.idx_off + (J.ext_cols ? 0 : 2 * J.r) + t];
+            C[t] = a.UT ? a.ut_at[c] : c;
+        }
         // the other columns' scales (prep_ext_job)
         const cplx others = J.ext_cols && t < ncol ? a.mat[J.mat_off + t] : cplx{0.0, 0.0};
         cdd s{{0.0, 0.0}, {0.0, 0.0}};
@@ -95,12 +100,11 @@ __device__ __forceinline__ void final_pattern(const ManyFinalArgs& a, int p, int
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const int32_t* cmode = a.idx + J.idx_off + (a.UT ? 2 * J.r + J.nc : J.ext_cols ? 0 : 2 * J.r);
         for (int l = t; l < J.m_out; l += 64) {
             const cplx* Ul = a.U + (size_t)l * (size_t)a.ldu;
             double re = 0.0, im = 0.0;
             for (int j = 0; j < ncol; ++j) {
-                const cplx u = a.UT ? a.UT[(size_t)cmode[j] * (size_t)a.m + l] : Ul[cmode[j]];
+                const cplx u = a.UT ? a.UT[(size_t)C[j] * (size_t)a.m + l] : Ul[C[j]];
                 re = __builtin_fma(u.re, L[j].re, re);
                 re = __builtin_fma(-u.im, L[j].im, re);
                 im = __builtin_fma(u.re, L[j].im, im);
@@ -143,8 +147,9 @@ __device__ __forceinline__ void reduce_slots(const ManyFinalArgs& a, const DRedI
 // One workgroup per distinct pattern, then one per stage-1 item.
 __global__ __launch_bounds__(64) void many_final_kernel(const ManyFinalArgs a) {
     __shared__ cplx L[kMaxExtendCols];
+    __shared__ int C[kMaxExtendCols];
     const int p = blockIdx.x;
-    if (p < a.npat) final_pattern(a, p, (int)threadIdx.x, L);
+    if (p < a.npat) final_pattern(a, p, (int)threadIdx.x, L, C);
     else if (p - a.npat < a.nred) reduce_slots(a, a.red[p - a.npat], (int)threadIdx.x);
 }
 

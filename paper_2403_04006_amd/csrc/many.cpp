@@ -109,6 +109,7 @@ struct ManyEntry {
     size_t mat_elems = 0, partial_doubles = 0, dpat_elems = 0;
     cplx* d_ut = nullptr;        // columns of U, transposed (kTransposeMinJobs)
     int32_t* d_ut_col = nullptr; // which
+    int32_t* d_ut_at = nullptr;  // mode -> row of d_ut
     int32_t* d_prep = nullptr;   // the others
     int nut = 0;
     std::vector<ManyClass> classes;
@@ -291,8 +292,8 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     if (!adj && pats.size() >= (size_t)kTransposeMinJobs) ut_at.assign((size_t)m, -1);
     int next = 0;
     {
-        size_t ints = 0;   // iterated modes and multiplicities, the other side's modes, places
-        for (const PatRef& p : pats) ints += 2 * (size_t)std::max(p.nr, p.nc) + (size_t)std::min(p.nr, p.nc) + (size_t)p.nc;
+        size_t ints = 0;   // iterated modes and multiplicities, the other side's modes
+        for (const PatRef& p : pats) ints += 2 * (size_t)std::max(p.nr, p.nc) + (size_t)std::min(p.nr, p.nc);
         hidx.reserve(ints);
     }
     Side rows, cols;
@@ -402,12 +403,11 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
         if (ext) {
             ++next;
             for (int j = 0; !ut_at.empty() && j < ps.nc; ++j) {
-                const int c = extcol ? p.row_mode[j] : p.col_mode[j];
+                const int c = ps.col_idx[j];
                 if (ut_at[(size_t)c] < 0) {
                     ut_at[(size_t)c] = (int32_t)ut_col.size();
                     ut_col.push_back(c);
                 }
-                hidx.push_back(ut_at[(size_t)c]);
             }
         }
         if (adj) {
@@ -587,7 +587,10 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
 
     const size_t ut_bytes = sizeof(cplx) * ut_col.size() * (size_t)m;
     const bool ut = next >= kTransposeMinJobs && ut_bytes <= kTransposeMaxBytes;
-    if (!ut) ut_col.clear();
+    if (!ut) {
+        ut_col.clear();
+        ut_at.clear();
+    }
 
     // one device block: uploaded descriptors first, kernel-written arrays after
     Carve cv;
@@ -610,6 +613,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     const size_t oDup = cv.take(sizeof(int32_t) * sz(dup_pat.size()));
     const size_t oDut = cv.take(sizeof(int64_t) * sz(dup_out.size()));
     const size_t oUc = cv.take(sizeof(int32_t) * sz(ut_col.size()));
+    const size_t oUa = cv.take(sizeof(int32_t) * sz(ut_at.size()));
     const size_t oPr = cv.take(sizeof(int32_t) * sz(others.size()));
     const size_t upload_bytes = cv.off;
     const size_t oMat = cv.take(sizeof(cplx) * sz(mat_elems));
@@ -644,6 +648,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     E.d_qzero = (unsigned*)(E.dmem + oQz);
     E.d_ut = ut ? (cplx*)(E.dmem + oUt) : nullptr;
     E.d_ut_col = (int32_t*)(E.dmem + oUc);
+    E.d_ut_at = (int32_t*)(E.dmem + oUa);
     E.nut = (int)ut_col.size();
     E.d_prep = (int32_t*)(E.dmem + oPr);
     E.nprep = (int)others.size();
@@ -673,6 +678,7 @@ int build_many(pq_ctx* ctx, int mode, int32_t m, const std::vector<PatRef>& all,
     put(oDup, dup_pat.data(), sizeof(int32_t) * dup_pat.size());
     put(oDut, dup_out.data(), sizeof(int64_t) * dup_out.size());
     put(oUc, ut_col.data(), sizeof(int32_t) * ut_col.size());
+    put(oUa, ut_at.data(), sizeof(int32_t) * ut_at.size());
     put(oPr, others.data(), sizeof(int32_t) * others.size());
     return ctx->upload(E.dmem, stage, upload_bytes, st);
 }
@@ -754,6 +760,7 @@ int run_many(pq_ctx* ctx, ManyEntry& E, const cplx* U, int64_t ldu, int32_t m, c
     fa.U = U;
     fa.ldu = ldu;
     fa.UT = E.d_ut;
+    fa.ut_at = E.d_ut_at;
     fa.m = m;
     fa.mat = E.d_mat;
     fa.idx = E.d_idx;

@@ -97,8 +97,8 @@ struct DRedArgs {
 struct ManyFinalArgs {
     const cplx* U;
     int64_t ldu;
-    const cplx* UT;            // columns of U, transposed, or null; their rows in it follow an
-                               // extend-row job's modes in idx
+    const cplx* UT;            // columns of U, transposed, or null (extend-row jobs)
+    const int32_t* ut_at;      // [m]: a column's row in it
     int32_t m;
     const cplx* mat;
     const int32_t* idx;
