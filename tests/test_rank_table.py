@@ -9,7 +9,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-DRIVER = r"""
+PROGRAM = r"""
 #include <stdio.h>
 #include <stdlib.h>
 #include <vector>
@@ -34,10 +34,10 @@ int main(int argc, char** argv) {
 
 
 @pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("rank")
     src, exe = d / "rank.cpp", d / "rank"
-    src.write_text(DRIVER)
+    src.write_text(PROGRAM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2403_04006_amd", "csrc"), str(src),
                     "-o", str(exe)], check=True)
     return str(exe)
@@ -45,8 +45,8 @@ def driver(tmp_path_factory):
 
 @pytest.mark.parametrize("m,n", [(1, 1), (1, 64), (2, 1), (2, 62), (2, 63), (2, 64), (3, 64), (4, 63), (8, 64), (9, 48),
                                  (16, 10), (32, 4), (64, 5)])
-def test_rank_table_holds_the_binomials(driver, m, n):
-    got = [int(v) for v in subprocess.run([driver, str(m), str(n)], check=True, capture_output=True, text=True).stdout.split()]
+def test_rank_table_holds_the_binomials(program, m, n):
+    got = [int(v) for v in subprocess.run([program, str(m), str(n)], check=True, capture_output=True, text=True).stdout.split()]
     want = [0 if q == 0 else math.comb(r + q - 1, r) for r in range(n + 1) for q in range(m)]
     assert max(want) < 2**32 - 1
     assert got == want
